@@ -266,6 +266,7 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
             gidx.emplace(key, g);
             H.g0_tgt8.resize(8 * H.ngroups0, -1);
             H.g0_src64.resize(64 * H.ngroups0, (int32_t)nblocks);
+            H.g0_coord.insert(H.g0_coord.end(), {P[0] >> 1, P[1] >> 1, P[2] >> 1, 0});
             for (int sidx = 0; sidx < 64; ++sidx) {
                 const int32_t q = source_at(2 * (int64_t)(P[0] >> 1) + (sidx & 3) - 1,
                                             2 * (int64_t)(P[1] >> 1) + ((sidx >> 2) & 3) - 1,
@@ -277,7 +278,57 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
         }
         H.g0_tgt8[8 * g + ((P[0] & 1) | ((P[1] & 1) << 1) | ((P[2] & 1) << 2))] = act[b];
     }
+    order_groups(H);
     return LGF_OK;
+}
+
+// Longest run of the level-0 Prod, 8, 4, 2 or 1 groups: a wave marching through R stacked groups
+// reads 2R + 2 source slabs for 2R target slabs, but leaves R times fewer waves, and below
+// about 4096 (four per SIMD) the lost waves cost more than the reads save.  Measured on
+// MI355X, us in FP64 / FP32: 16^3 blocks of 16^3, R = 1, 2, 4, 8: 782, 631, 559, 524 / 413, 337,
+// 301, 294; 8^3 blocks of 16^3, R = 1, 2, 4: 100, 86, 75 / 50, 46, 46; 4224 blocks of 6^3,
+// R = 1, 2, 4 (FP32): 35, 30, 39; 552 blocks of 8^3, R = 1, 2 (FP64): 25, 26.
+static int run_length(const HostPlan& H) {
+    const int64_t waves = H.ngroups0 * (spec_padded(2 * H.n * 2 * H.n * (H.n + 1)) / kSpecChunk);
+    int R = 8;
+    while (R > 1 && waves / R < 4096) R /= 2;
+    return R;
+}
+
+void order_groups(HostPlan& H) {
+    const int64_t ng = H.ngroups0;
+    const int R = run_length(H);
+    std::vector<int32_t> ord(ng);
+    for (int64_t g = 0; g < ng; ++g) ord[g] = (int32_t)g;
+    const int32_t* C = H.g0_coord.data();
+    // by layout, layer of R groups, then column (y, x), then z
+    std::sort(ord.begin(), ord.end(), [&](int32_t i, int32_t j) {
+        const int32_t *a = C + 4 * i, *b = C + 4 * j;
+        const std::array<int32_t, 5> ka{a[3], a[2] / R, a[1], a[0], a[2]}, kb{b[3], b[2] / R, b[1], b[0], b[2]};
+        return ka < kb;
+    });
+    std::vector<int32_t> tgt(8 * ng), src(64 * ng), coord(4 * ng);
+    H.g0_runs.clear();
+    H.g0_flags.assign(ng, 0);
+    for (int64_t g = 0; g < ng; ++g) {
+        const int32_t o = ord[g];
+        std::copy_n(&H.g0_tgt8[8 * o], 8, &tgt[8 * g]);
+        std::copy_n(&H.g0_src64[64 * o], 64, &src[64 * g]);
+        std::copy_n(C + 4 * o, 4, &coord[4 * g]);
+        for (int i = 0; i < 64; ++i)
+            if (src[64 * g + i] != (int32_t)H.nsrc) H.g0_flags[g] |= 1 << (i >> 3);
+        for (int c = 0; c < 8; ++c)
+            if (tgt[8 * g + c] >= 0) H.g0_flags[g] |= 1 << (8 + (c >> 2));
+        const int32_t *k = &coord[4 * g], *q = g > 0 ? &coord[4 * (g - 1)] : nullptr;
+        const bool next = q && k[3] == q[3] && k[0] == q[0] && k[1] == q[1] && k[2] == q[2] + 1 && k[2] / R == q[2] / R;
+        if (next)
+            ++H.g0_runs.back();
+        else
+            H.g0_runs.insert(H.g0_runs.end(), {(int32_t)g, 1});
+    }
+    H.g0_tgt8.swap(tgt);
+    H.g0_src64.swap(src);
+    H.g0_coord.swap(coord);
 }
 
 // Every index a kernel will follow lies inside the buffer it addresses (checked on the host
@@ -293,8 +344,14 @@ lgf_status check_host(const HostPlan& H) {
               within(H.eval_l1, 0, H.nb - 1) && within(H.near_out, 0, H.neval - 1) &&
               (H.near_out.empty() || (int64_t)H.near_out.size() == H.ntgt0) &&
               (H.near_flag.empty() || (int64_t)H.near_flag.size() == H.neval) &&
-              (int64_t)H.g0_tgt8.size() == 8 * H.ngroups0 && (int64_t)H.g0_src64.size() == 64 * H.ngroups0 &&
+              (int64_t)H.g0_flags.size() == H.ngroups0 && (int64_t)H.g0_tgt8.size() == 8 * H.ngroups0 && (int64_t)H.g0_src64.size() == 64 * H.ngroups0 &&
               H.ntgt0 <= H.neval && H.nsrc <= H.nb && (H.eval_l1.empty() || (int64_t)H.eval_l1.size() == H.neval);
+    int64_t g = 0;  // the runs cover the groups in order
+    for (size_t r = 0; ok && r + 1 < H.g0_runs.size(); r += 2) {
+        ok = H.g0_runs[r] == g && H.g0_runs[r + 1] >= 1;
+        g += H.g0_runs[r + 1];
+    }
+    ok = ok && g == H.ngroups0;
     for (int l = 2; ok && l <= H.L && l < (int)H.lv.size(); ++l) {
         const HostLevel& Lv = H.lv[l];
         const int64_t nc = H.lv[l - 1].nint;
@@ -338,8 +395,11 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
     }
     U.solve_offsets = {0};
     std::vector<int64_t> off(U.L + 1, 0);  // running item offset per level (level 1 = blocks)
+    int32_t part = 0;
     for (const auto& P : parts) {
         const int64_t ob = off[1];
+        for (size_t i = 0; i < P.g0_coord.size(); ++i) U.g0_coord.push_back(i % 4 == 3 ? part : P.g0_coord[i]);
+        ++part;
         for (int32_t t : P.g0_tgt8) U.g0_tgt8.push_back(t < 0 ? -1 : (int32_t)(t + ob));
         for (int32_t q : P.g0_src64) U.g0_src64.push_back(q == (int32_t)P.nsrc ? (int32_t)U.nsrc : (int32_t)(q + ob));
         for (int l = 1; l <= P.L; ++l) {
@@ -364,6 +424,7 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
         for (int l = 1; l <= P.L; ++l) off[l] += P.lv[l].nint;
         U.solve_offsets.push_back(off[1]);
     }
+    order_groups(U);
     return U;
 }
 
@@ -389,7 +450,7 @@ int64_t workspace_need(const HostPlan& H, lgf_precision prec) {
     const int64_t S1 = spec_padded(2 * p * 2 * p * (p + 1));
     const int64_t p3 = (int64_t)p * p * p;
     const int topc = std::min(H.Ltop + 1, H.L);
-    int64_t need = H.ngroups0 * 72 * 4 + (p * n + 2 * p * p) * 8 + (H.nsrc + 1 + H.ntgt0) * S0 * 2 * esz +
+    int64_t need = (H.ngroups0 * 73 + (int64_t)H.g0_runs.size()) * 4 + (p * n + 2 * p * p) * 8 + (H.nsrc + 1 + H.ntgt0) * S0 * 2 * esz +
                    (int64_t)(H.eval_l1.size() + H.near_out.size() + H.near_flag.size()) * 4;
     for (int l = 1; l <= H.Ltop; ++l) {
         const HostLevel& h = H.lv[l];

@@ -87,6 +87,10 @@ struct HostPlan {
     std::vector<int32_t> near_out;            // split sets: evaluation block of each level-0 target
     std::vector<int32_t> near_flag;           // split sets: 1 if the evaluation block has a near field
     std::vector<int32_t> g0_tgt8, g0_src64;  // targets: evaluation numbering; sources: sentinel = nsrc
+    // group coordinates (x, y, z, layout of a batch); runs of groups stacked in z (first group,
+    // count), numbered consecutively; per group: bit 2 sz + h = half h (rows sy = 2h, 2h + 1) of
+    // source slab sz holds a source, bit 8 + cz = target slab cz holds a target
+    std::vector<int32_t> g0_coord, g0_runs, g0_flags;
     std::vector<HostLevel> lv;               // index 0 unused, 1..L
     std::vector<int64_t> solve_offsets{0};   // block offsets of the layouts of a batch
     // levels >= 1: does an interval hold a source / an evaluation block below it (index = level)
@@ -104,6 +108,10 @@ struct HostPlan {
 // groups hold evaluation blocks (numbered as given) and their sources (numbered as given).
 lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int levels, HostPlan& H,
                       const int32_t* eval_ijk = nullptr, int64_t neval = 0);
+
+// Level-0 groups renumbered so that the groups of a run are consecutive, runs of neighbouring
+// columns following each other; fills g0_runs and g0_flags.
+void order_groups(HostPlan& H);
 
 // Every list index within its array's range; LGF_ERR_LAYOUT otherwise.
 lgf_status check_host(const HostPlan& H);

@@ -178,11 +178,24 @@ template <> struct FarAcc<float> { using type = ff32; };
 // Level 0 over groups of 2x2x2 target blocks (tgt8) with their 4^3 source neighbourhood (src64).
 // Sources and targets are numbered separately: fhat holds nsrc + 1 items (sentinel nsrc),
 // uhat ntgt items.
-// prefetch: 1 = the next source slab's loads are issued before the current slab is used.
+// Groups stacked in z are numbered consecutively; a run (first group, count) is such a stack,
+// which one wave marches through.  flags: per group, bit 2 sz + h = half h of source slab sz
+// holds a source, bit 8 + cz = target slab cz holds a target.
 template <typename T>
-hipError_t launch_prod_near(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* tgt8, const int32_t* src64,
-                            cplx<T>* uhat, int64_t ngroups, int64_t nsrc, int64_t ntgt, int S, int waves,
-                            int prefetch, hipStream_t s, const SpecSym& sym = SpecSym{});
+struct NearLevel {
+    const cplx<T>* fhat;
+    const cplx<T>* khat;
+    const int32_t* tgt8;
+    const int32_t* src64;
+    const int32_t* runs;
+    const int32_t* flags;
+    cplx<T>* uhat;
+    int64_t nruns, nsrc, ntgt;
+    int S;
+    SpecSym sym;
+};
+template <typename T>
+hipError_t launch_prod_near(const NearLevel<T>& near, int waves, hipStream_t s);
 // sym: a reduced kernel table (khat then holds sym.ncls spectra) must match the spectrum
 // size S = M^2 (M/2 + 1) and hold at most 65536 spectra
 inline bool sym_fits(const SpecSym& y, int S) {
@@ -225,7 +238,7 @@ hipError_t launch_prod_far(const cplx<T>* fhat, const cplx<T>* khat, const int32
 struct TuneConfig {
     int fft0_threads = 0;  // 0 = default per tile size, else 128 / 256 / 512
     int near_waves = 4;    // waves per workgroup of the level-0 Prod kernel: 2, 4, 8
-    int near_prefetch = 0; // that kernel's source loads half a z slab ahead: 0, 1 (by plan size)
+    int near_prefetch = 0; // 0, 1: without effect (kept in the ABI and in tuning files)
     int far_waves = 0;     // parent groups per workgroup of the level >= 1 Prod kernel: 1, 2, 4, 0 = by level size
     int far_children = 0;  // children per lane of that kernel: 8, 4, 2, 1, or 0 = by level size
     int overlap = 0;       // far-field chain on a second stream: 1 = yes, 2 = no, 0 = default (yes)

@@ -101,7 +101,7 @@ struct lgf_plan_s {
     int n = 0, p = 0, L = 0, Ltop = 0;
     double kappa = 0.0;  // screening of the operator L - kappa (0: the Laplace operator)
     lgf_precision prec = LGF_F64;
-    int64_t nb = 0, near_pairs = 0, ngroups0 = 0;
+    int64_t nb = 0, near_pairs = 0, ngroups0 = 0, nruns0 = 0;
     int64_t nsrc = 0, neval = 0;        // blocks of f / of u (nb for both unless the sets differ)
     int64_t ntgt0 = 0;                  // level-0 targets (evaluation blocks with a near field)
     int32_t* d_eval_l1 = nullptr;       // level-1 interval of each evaluation block (split sets)
@@ -112,7 +112,7 @@ struct lgf_plan_s {
     std::vector<int64_t> solve_offsets;
     std::vector<LevelPlan> lv;  // index 0 unused, 1..L
     std::shared_ptr<SpectraEntry> spectra0;
-    int32_t *d_g0_tgt8 = nullptr, *d_g0_src64 = nullptr;
+    int32_t *d_g0_tgt8 = nullptr, *d_g0_src64 = nullptr, *d_g0_runs = nullptr, *d_g0_flags = nullptr;
     double *d_A = nullptr, *d_C01 = nullptr;
     void *d_fhat0 = nullptr, *d_uhat0 = nullptr;
     std::vector<DevBuf> allocs;
@@ -331,6 +331,9 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
                  lvN(l) * 2.0 * 3.0 * p3 * p);
         return hipSuccess;
     };
+    const NearLevel<T> near0{(const C*)pl->d_fhat0, (const C*)pl->spectra0->dev, pl->d_g0_tgt8, pl->d_g0_src64,
+                             pl->d_g0_runs,         pl->d_g0_flags,              (C*)pl->d_uhat0, pl->nruns0,
+                             pl->nsrc,              pl->ntgt0,                   pl->spectra0->S, pl->spectra0->sym};
     // level-0 PadFFT: first when level 1 reads its spectra (the lattice scheme), else at the
     // head of the near field
     auto fwd0 = [&]() -> hipError_t {
@@ -482,10 +485,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     // ---- near field (level 0) on the caller's stream
     if (!pl->lat1 && !fwd0_first && (e = fwd0()) != hipSuccess) return e;
     {
-        LGF_STEP(s,
-                 launch_prod_near<T>((const C*)pl->d_fhat0, (const C*)pl->spectra0->dev, pl->d_g0_tgt8,
-                                     pl->d_g0_src64, (C*)pl->d_uhat0, pl->ngroups0, pl->nsrc, pl->ntgt0,
-                                     pl->spectra0->S, tc.near_waves, tc.near_prefetch, s, pl->spectra0->sym),
+        LGF_STEP(s, launch_prod_near<T>(near0, tc.near_waves, s),
                  "prod_l0", (ns + nt0 + khat_rows(*pl->spectra0, 27)) * S0 * cs, (double)pl->near_pairs * S0 * 8.0);
         LGF_STEP(s,
                  (launch_ifft_trunc<T, T, T>(n, (const C*)pl->d_uhat0, u, pl->ntgt0, s, tc.fft0_threads,
@@ -524,6 +524,7 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     pl->Ltop = H.Ltop;
     pl->near_pairs = H.near_pairs;
     pl->ngroups0 = H.ngroups0;
+    pl->nruns0 = (int64_t)H.g0_runs.size() / 2;
     pl->solve_offsets = H.solve_offsets;
     hipGetDevice(&pl->device);
     if (hipStreamCreateWithFlags(&pl->far_stream, hipStreamNonBlocking) != hipSuccess ||
@@ -597,7 +598,9 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     if (!budget_reserve(need)) return fail(LGF_ERR_BUDGET, "plan workspace exceeds the device-memory budget");
     pl->ws_bytes = need;
     bool ok = dev_alloc(pl, &pl->d_g0_tgt8, H.ngroups0 * 8 * 4) &&
-              dev_alloc(pl, &pl->d_g0_src64, H.ngroups0 * 64 * 4) && dev_alloc(pl, &pl->d_A, p * n * 8) &&
+              dev_alloc(pl, &pl->d_g0_src64, H.ngroups0 * 64 * 4) &&
+              dev_alloc(pl, &pl->d_g0_runs, (int64_t)H.g0_runs.size() * 4) &&
+              dev_alloc(pl, &pl->d_g0_flags, H.ngroups0 * 4) && dev_alloc(pl, &pl->d_A, p * n * 8) &&
               dev_alloc(pl, &pl->d_C01, 2 * p * p * 8) &&
               dev_alloc(pl, &pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz) &&
               dev_alloc(pl, &pl->d_uhat0, H.ntgt0 * S0 * 2 * esz) &&
@@ -627,6 +630,8 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     if (!ok) return fail(LGF_ERR_OOM, "device allocation failed for the plan workspace");
     hipError_t e = upload(pl->d_g0_tgt8, H.g0_tgt8, s);
     if (e == hipSuccess) e = upload(pl->d_g0_src64, H.g0_src64, s);
+    if (e == hipSuccess) e = upload(pl->d_g0_runs, H.g0_runs, s);
+    if (e == hipSuccess) e = upload(pl->d_g0_flags, H.g0_flags, s);
     if (e == hipSuccess) e = upload(pl->d_A, A, s);
     if (e == hipSuccess) e = upload(pl->d_C01, C01, s);
     if (e == hipSuccess) e = upload(pl->d_eval_l1, H.eval_l1, s);
@@ -891,10 +896,6 @@ static lgf_status make_plan(HostPlan& H, lgf_precision prec, void* hip_stream, l
         delete pl;
         return st;
     }
-    // the level-0 Prod's pipelined half slabs: faster in graph solves of large plans (256^3,
-    // 512 groups: FP32 0.924 -> 0.913 ms), slower in small ones (128^3, 64 groups: FP32
-    // 0.151 -> 0.156 ms)
-    pl->tune.near_prefetch = pl->ngroups0 >= 256 ? 1 : 0;
     apply_cached_tune(pl);
     *out = pl;
     return LGF_OK;
@@ -1117,16 +1118,15 @@ lgf_status lgf_plan_autotune(lgf_plan_t plan, const void* f, void* u, void* hip_
     TuneConfig best = start;
     best.overlap = 2;
     float best_ms = timed(best);
-    const std::vector<std::vector<int>> opts = {{128, 256, 512}, {2, 4, 8}, {0, 1}, {0, 1, 2, 4, 8, 16}, {0, 8, 4, 2, 1}};
+    const std::vector<std::vector<int>> opts = {{128, 256, 512}, {2, 4, 8}, {0, 1, 2, 4, 8, 16}, {0, 8, 4, 2, 1}};
     for (int sweep = 0; sweep < 2; ++sweep) {
-        for (int knob = 0; knob < 5; ++knob) {
+        for (int knob = 0; knob < 4; ++knob) {
             for (int v : opts[knob]) {
                 TuneConfig c = best;
                 if (knob == 0) c.fft0_threads = v;
                 if (knob == 1) c.near_waves = v;
-                if (knob == 2) c.near_prefetch = v;
-                if (knob == 3) c.far_waves = v;
-                if (knob == 4) c.far_children = v;
+                if (knob == 2) c.far_waves = v;
+                if (knob == 3) c.far_children = v;
                 const float ms = timed(c);
                 if (ms < best_ms) {
                     best_ms = ms;

@@ -33,13 +33,6 @@ __device__ __forceinline__ bool xcd_tile_at(int L, int nchunks, int ngroupblocks
     gblock = k % ngroupblocks;
     return chunk < nchunks;
 }
-__device__ __forceinline__ bool xcd_tile(int nchunks, int ngroupblocks, int& chunk, int& gblock) {
-    const int L = blockIdx.x;
-    const int xcd = L % kXcds, k = L / kXcds;
-    chunk = (k / ngroupblocks) * kXcds + xcd;
-    gblock = k % ngroupblocks;
-    return chunk < nchunks;
-}
 __host__ __forceinline__ unsigned xcd_grid(int nchunks, int ngroupblocks) {
     const int padded = (nchunks + kXcds - 1) / kXcds * kXcds;
     return (unsigned)padded * (unsigned)ngroupblocks;
@@ -75,6 +68,45 @@ __host__ __forceinline__ bool chunk_fits_u32(int64_t items) {
     return items * 64 * (int64_t)sizeof(cplx<T>) <= (int64_t)UINT32_MAX;
 }
 
+// A plan's list read at wave-uniform indices: lists do not change during a launch, so the reads
+// may be scalar loads (constant address space).
+typedef const __attribute__((address_space(4))) int32_t* ScalarList;
+__device__ __forceinline__ ScalarList scalar_list(const int32_t* p) {
+    return (ScalarList)(uintptr_t)p;
+}
+
+// 16 bytes per lane at p + off of a wave-uniform p, within [p, p + bytes): a lane out of range
+// reads zeros or stores nothing (the buffer instructions' own range check), with no access to
+// memory.  The address arithmetic stays in scalar registers.
+template <typename T>
+constexpr uint32_t kItemBytes = 64u * (uint32_t)sizeof(cplx<T>);  // an item's coefficients in one chunk
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kRawBuffer = 0x00020000;  // resource word 3: 32-bit elements, no swizzle
+constexpr int kStream = 2;              // cache policy bit: nontemporal
+template <typename V>
+__device__ __forceinline__ V buffer_read(const char* p, uint32_t bytes, uint32_t off) {
+    static_assert(sizeof(V) == 16, "one 16-byte access per lane");
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(
+                                     __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, bytes, kRawBuffer), off, 0, 0));
+}
+template <typename V>
+__device__ __forceinline__ void buffer_stream(char* p, uint32_t bytes, uint32_t off, const V& v) {
+    static_assert(sizeof(V) == 16, "one 16-byte access per lane");
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v),
+                                           __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, kRawBuffer), off, 0, kStream);
+}
+// The buffered loads have arrived: placed before a branch on their use, so that the wait is
+// outside it and both ways leave the same loads in flight.
+template <typename V>
+__device__ __forceinline__ void arrived(V (&x)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        u32x4 r = __builtin_bit_cast(u32x4, x[i]);
+        asm volatile("" : "+v"(r));
+        x[i] = __builtin_bit_cast(V, r);
+    }
+}
+
 // ------------------------------------------------------------------ level 0
 // Groups g: tgt8[g][c] = block 2J + c (c = cx | cy<<1 | cz<<2) or -1;
 // src64[g][s] = source block 2J + (sx-1, sy-1, sz-1), s = sx + 4 sy + 16 sz, or the zero
@@ -85,29 +117,54 @@ __host__ __forceinline__ bool chunk_fits_u32(int64_t items) {
 // FPL = 2 (FP32), a wave covers two consecutive chunks, lanes 0-31 the first and 32-63 the
 // second, each lane loading 16 bytes per item as the FP64 lanes do.  The waves of a
 // workgroup are different groups of the same chunk(s) and share the kernel tile in LDS: the
-// 27 near offsets, row (dx+1) + 3 (dy+1) + 9 (dz+1).  A workgroup serves `rounds` blocks of
-// groups in turn with that tile.  Every frequency is computed with the
-// same arithmetic in the same order whatever FPL and the number of waves.
+// 27 near offsets, row (dx+1) + 3 (dy+1) + 9 (dz+1).  Every frequency is computed with the
+// same arithmetic in the same order whatever FPL, the number of waves and the runs.
+//
+// A wave marches through a run, a stack of groups in z: source slab after source slab (16
+// sources), each applied to the up to three target slabs it reaches, so a source slab inside
+// the run is read once instead of once per group: 2R + 2 slabs for the 2R target slabs of R
+// groups (4.5 reads per target at R = 8, 8 at R = 1).  Bound by those reads from L2, and now near
+// the HBM rate: the 256^3 Prod went 612 -> 507 us in FP64 (3.7 -> 4.5 TB/s of its 2.3 GB, 80-90%
+// of a copy's rate) and 330 -> 286 us in FP32 with runs of 8, the 128^3 one 82 -> 71 us and 50 ->
+// 45 us with runs of 4.
 template <typename T, int FPL>
 struct alignas(FPL * sizeof(cplx<T>)) LaneCoef {
     cplx<T> v[FPL];
 };
 
-template <typename T, int kNearWaves, bool kPrefetch, int FPL>
-__global__ void __launch_bounds__(64 * kNearWaves)
-    k_prod_near_grouped(const cplx<T>* __restrict__ fhat, const cplx<T>* __restrict__ khat,
-                        const int32_t* __restrict__ tgt8, const int32_t* __restrict__ src64,
-                        cplx<T>* __restrict__ uhat, int S, int ngroups, int nsrc, int ntgt, const SpecSym sym,
-                        int rounds) {
+template <typename T>
+struct NearArgs {
+    const cplx<T>* fhat;
+    const cplx<T>* khat;
+    const int32_t* tgt8;
+    const int32_t* src64;
+    const int32_t* runs;
+    const int32_t* flags;
+    cplx<T>* uhat;
+    int S, nruns, nsrc, ntgt;
+    SpecSym sym;
+};
+
+// Runs long enough for a workgroup's waves to march in lockstep (measured: 256^3, runs of 8,
+// 540 -> 524 us in FP64 and 303 -> 294 us in FP32; 128^3, runs of 4, 75 -> 79 us).
+constexpr int kLockstepRun = 8;
+
+template <typename T, int kNearWaves, int FPL>
+__global__ void __launch_bounds__(64 * kNearWaves) k_prod_near_grouped(const NearArgs<T> a) {
     using V = LaneCoef<T, FPL>;
     __shared__ V tile[27 * 64];
+    constexpr int NT = 64 * kNearWaves, NR = (27 * 64 + NT - 1) / NT;
+    const cplx<T>* __restrict__ fhat = a.fhat;
+    const cplx<T>* __restrict__ khat = a.khat;
+    const ScalarList tgt8 = scalar_list(a.tgt8), src64 = scalar_list(a.src64), runs = scalar_list(a.runs),
+                     flags = scalar_list(a.flags);
+    cplx<T>* __restrict__ uhat = a.uhat;
+    const int S = a.S, nruns = a.nruns, nsrc = a.nsrc, ntgt = a.ntgt;
+    const SpecSym& sym = a.sym;
     const int lane = threadIdx.x & 63;
     const int nchunks = (S + 63) / 64;  // the last chunk may be partial (frequencies w >= S unused)
-    // a workgroup serves `rounds` blocks of kNearWaves groups of one chunk (block gb, then
-    // gb + gstride, ...) with one kernel tile
-    const int gstride = ((ngroups + kNearWaves - 1) / kNearWaves + rounds - 1) / rounds;
     int unit, gb;
-    if (!xcd_tile((nchunks + FPL - 1) / FPL, gstride, unit, gb)) return;
+    if (!xcd_tile_at((int)blockIdx.x, (nchunks + FPL - 1) / FPL, (nruns + kNearWaves - 1) / kNearWaves, unit, gb)) return;
     // this thread's chunk and first frequency in it; with FPL = 2 the second half of the
     // wave may fall past the last chunk, and then reads the first half's chunk and stores
     // nothing
@@ -121,10 +178,15 @@ __global__ void __launch_bounds__(64 * kNearWaves)
     const bool live = my_chunk < nchunks;
     if (!live) my_chunk = unit * FPL;
     const int w = my_chunk * 64 + wl;  // first frequency of this lane (S is a multiple of 64)
+    // this wave's run (waves past the last run only help to fill the tile)
+    const int run = wave_uniform(gb * kNearWaves + (int)(threadIdx.x >> 6));
+    const bool active = run < nruns;
+    const int g0 = runs[active ? 2 * run : 0], len = active ? runs[2 * run + 1] : 0;
+    // The kernel tile: every load of a thread is issued before the first is stored.
+    V kv[NR];
     if (sym.info != nullptr) {
         // reduced spectra: each thread fills rows of its own frequencies (the loop steps by
         // whole waves), decoded once; the rows' descriptions first, then all the gathers
-        constexpr int NT = 64 * kNearWaves, NR = (27 * 64 + NT - 1) / NT;
         Freq3 om[FPL];
 #pragma unroll
         for (int q = 0; q < FPL; ++q) om[q] = freq_of(w + q, sym.M);
@@ -136,203 +198,177 @@ __global__ void __launch_bounds__(64 * kNearWaves)
             use[k] = i < 27 * 64;
             inf[k] = use[k] ? sym.info[i >> 6] : 0u;
         }
-        V kv[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k)
 #pragma unroll
             for (int q = 0; q < FPL; ++q)
                 kv[k].v[q] = use[k] && w + q < S ? sym_coef(khat, inf[k], om[q], sym.ncls, sym.M) : cplx<T>{T(0), T(0)};
+    } else {
+        const int wt = w < S ? w : 0;  // (S is even: a lane's two frequencies are both below it or not)
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
-            const int i = (int)threadIdx.x + k * NT;
-            if (i < 27 * 64) tile[i] = kv[k];
+            const int row = (int)(threadIdx.x >> 6) + k * kNearWaves;
+            kv[k] = *reinterpret_cast<const V*>(khat + spec_at(row < 27 ? row : 26, wt, 27));
         }
-    } else {
-        for (int i = threadIdx.x; i < 27 * 64; i += 64 * kNearWaves) {
-            int ch, wi;
-            lane_pos(i & 63, ch, wi);
-            if (ch >= nchunks) ch = unit * FPL;
-            const int wt = ch * 64 + wi;
-            tile[i] = wt < S ? *reinterpret_cast<const V*>(khat + spec_at(i >> 6, wt, 27)) : V{};
+        if (w >= S) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) kv[k] = V{};
         }
     }
+    // this lane's byte offset from an item's coefficients in the unit's first chunk: its chunk,
+    // then its frequencies; dead lanes read as live ones do and store out of range (dropped)
+    const uint32_t lbytes = (uint32_t)(my_chunk - unit * FPL) * (uint32_t)(nsrc + 1) * kItemBytes<T> +
+                            (uint32_t)wl * (uint32_t)sizeof(cplx<T>);
+    const uint32_t sbytes = live ? (uint32_t)(my_chunk - unit * FPL) * (uint32_t)ntgt * kItemBytes<T> +
+                                       (uint32_t)wl * (uint32_t)sizeof(cplx<T>)
+                                 : ~0u;
+    const char* const fbase = reinterpret_cast<const char*>(fhat + (int64_t)(unit * FPL) * (nsrc + 1) * 64);
+    char* const ubase = reinterpret_cast<char*>(uhat + (int64_t)(unit * FPL) * ntgt * 64);
+    // bytes from an item's first coefficient to the end of the lanes' last (0: reads as zeros,
+    // stores nothing, without memory traffic)
+    const uint32_t fspan = (FPL - 1) * (uint32_t)(nsrc + 1) * kItemBytes<T> + kItemBytes<T>;
+    const uint32_t uspan = (FPL - 1) * (uint32_t)ntgt * kItemBytes<T> + kItemBytes<T>;
+    auto load = [&](int item, bool on) -> V {
+        return buffer_read<V>(fbase + (uint64_t)(uint32_t)item * kItemBytes<T>, on && item != nsrc ? fspan : 0u, lbytes);
+    };
+    // 4-wave workgroups whose runs all exist, equally long and long enough, step through the
+    // source slabs together (a barrier before each half slab's loads): the waves' groups are
+    // neighbours and share half their sources, which the lockstep serves from L1.  The
+    // condition is uniform over the workgroup, so every wave meets the same barriers.
+    bool lockstep = kNearWaves == 4 && len >= kLockstepRun && gb * kNearWaves + kNearWaves <= nruns;
+    if (lockstep)
+        for (int k = 0; k < kNearWaves; ++k) lockstep = lockstep && runs[2 * (gb * kNearWaves + k) + 1] == len;
+    lockstep = wave_uniform(lockstep);
+    // source slab s = 0 .. 2 len + 1 of the run: slabs 0 and 1 of the first group, then slabs
+    // 2 and 3 of each group in turn (flags: bit 2 sz + h = half slab h of slab sz holds a
+    // source, bit 8 + cz = target slab cz holds a target)
+    ScalarList sg = nullptr;
+    uint32_t have = 0;
+    auto at = [&](int s) {
+        const int g = s < 2 ? g0 : g0 + (s >> 1) - 1, sz = s < 2 ? s : 2 + (s & 1);
+        sg = src64 + (int64_t)g * 64 + 16 * sz;
+        have = (uint32_t)flags[g] >> (2 * sz);
+    };
+    auto target = [&](int t) {  // target slab t of the run exists and holds a target
+        return t >= 0 && t < 2 * len && ((flags[g0 + (t >> 1)] >> (8 + (t & 1))) & 1);
+    };
+    // Every load and store from here on is issued whatever the layout (an absent item's with an
+    // empty range), so the loads in flight are counted exactly: a wait for one half never waits
+    // for the next one's loads or for the stores.
+    V fa[8], fb[8];
+    bool ha, hb;  // the buffered halves hold a source
+    auto ld = [&](int h, bool on, V(&x)[8]) {
+        if (lockstep) __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = load(sg[8 * h + i], on);
+        return (bool)((have >> h) & 1);
+    };
+    at(0);
+    ha = ld(0, active, fa);
+    hb = ld(1, active, fb);
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        const int i = (int)threadIdx.x + k * NT;
+        if (i < 27 * 64) tile[i] = kv[k];
+    }
     __syncthreads();
-    T ar[FPL][8], ai[FPL][8];
-    const int32_t* sg = src64;  // this round's group: its 64 source items
-    // the first chunk's items (wave-uniform base) and this lane's offset from it, in
-    // coefficients: its chunk, then its frequencies within the item
-    const cplx<T>* fbase = fhat + (int64_t)(unit * FPL) * (nsrc + 1) * 64;
-    const uint32_t loff = ((uint32_t)(my_chunk - unit * FPL) * (uint32_t)(nsrc + 1) * 64u + (uint32_t)wl) *
-                          (uint32_t)sizeof(cplx<T>);
-    auto load = [&](int item) -> V {
-        const uint32_t off = (uint32_t)item * 64u * (uint32_t)sizeof(cplx<T>) + loff;
-        return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(fbase) + off);
-    };
-    // source z slab sz contributes to target slab cz through kernel rows dz = cz - (sz - 1).
-    // Each of the slab's 18 kernel values (9 (dx, dy) x 2 target slabs) is read from LDS once
-    // and applied to the 4 targets (cx, cy) whose source cx - dx, cy - dy lies in the slab.
-    // (dy, dx) run from +1 down to -1, so every target still adds its sources in increasing
-    // (sy, sx) order: the same terms in the same order as a loop over the sources.  The end
-    // slabs reach one target slab only (sz = 0: cz = 0; sz = 3: cz = 1): the other row would
-    // be |dz| = 2, outside the near field.  The end slabs are unrolled out of the slab loop
-    // with that row dropped at compile time (measured: the 256^3 FP64 Prod 698 -> 677 us,
-    // FP32 371 -> 364 us, against one wave-uniform branch per row).
-    // END: 0 for the first slab, 3 for the last, -1 for a middle one, so the end slabs'
-    // skipped row is a compile-time choice and no slab body has a branch
-    auto slab = [&](auto endc, int sz, const V(&f)[16]) {
-        constexpr int END = decltype(endc)::value;
-        // kernel row bases for cz = 0 (dz = 1 - sz) and cz = 1 (dz = 2 - sz); an end slab's
-        // unused one is pointed at row 0
-        const V* t0 = tile + 9 * (sz < 3 ? 2 - sz : 0) * 64 + lane;
-        const V* t1 = tile + 9 * (sz > 0 ? 3 - sz : 0) * 64 + lane;
+    if (!active) return;
+    // accumulators of the three target slabs a source slab reaches: [d] holds target slab
+    // s - d, which meets source slab s (block plane s - 1 of the run) at dz = 1 - d;
+    // targets c = cx | cy << 1
+    T ar[3][FPL][4], ai[3][FPL][4];
+    auto clear = [&](int d) {
 #pragma unroll
-        for (int dy = 1; dy >= -1; --dy) {
+        for (int q = 0; q < FPL; ++q)
 #pragma unroll
-            for (int dx = 1; dx >= -1; --dx) {
-#pragma unroll
-                for (int cz = 0; cz < 2; ++cz) {
-                    if (cz ? END == 0 : END == 3) continue;  // |dz| = 2 (compile-time)
-                    const V k = (cz ? t1 : t0)[((dx + 1) + 3 * (dy + 1)) * 64];
-#pragma unroll
-                    for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-                        for (int cx = 0; cx < 2; ++cx) {
-                            const int c = cx | (cy << 1) | (cz << 2);
-                            const int sxy = (cx - dx + 1) + 4 * (cy - dy + 1);
-#pragma unroll
-                            for (int q = 0; q < FPL; ++q) cmac(ar[q][c], ai[q][c], f[sxy].v[q], k.v[q]);
-                        }
-                }
+            for (int c = 0; c < 4; ++c) {
+                ar[d][q][c] = T(0);
+                ai[d][q][c] = T(0);
             }
-        }
     };
-    // the half h of slab sz: source rows sy = 2h + j (j = 0, 1) in f[4 j + sx]; a target
-    // row cy meets them through dy = cy - sy + 1, so half 0 uses dy = 1, 0 and half 1
-    // dy = 0, -1
-    auto half = [&](auto endc, int sz, auto hc, const V(&f)[8]) {
-        constexpr int END = decltype(endc)::value, h = decltype(hc)::value;
-        const V* t0 = tile + 9 * (sz < 3 ? 2 - sz : 0) * 64 + lane;
-        const V* t1 = tile + 9 * (sz > 0 ? 3 - sz : 0) * 64 + lane;
+    clear(0);
+    clear(1);
+    clear(2);
+    // the half h of a source slab: source rows sy = 2h + j (j = 0, 1) in f[4 j + sx]; a target
+    // row cy meets them through dy = cy - sy + 1, so half 0 uses dy = 1, 0 and half 1 dy = 0, -1.
+    // (dy, dx) run from +1 down to -1, so every target adds its sources in increasing
+    // (sz, sy, sx) order whatever the run.
+    auto half = [&](auto hc, const V(&f)[8], const bool(&use)[3]) {
+        constexpr int h = decltype(hc)::value;
 #pragma unroll
-        for (int dy = 1; dy >= -1; --dy) {
+        for (int d = 0; d < 3; ++d) {
+            if (!use[d]) continue;  // wave-uniform: no such target slab, or none of its blocks
+            const V* t = tile + 9 * (2 - d) * 64 + lane;
 #pragma unroll
-            for (int dx = 1; dx >= -1; --dx) {
+            for (int dy = 1 - h; dy >= -h; --dy) {
 #pragma unroll
-                for (int cz = 0; cz < 2; ++cz) {
-                    if (cz ? END == 0 : END == 3) continue;  // |dz| = 2 (compile-time)
-                    if (h == 0 ? dy < 0 : dy > 0) continue;  // no target row meets this half
-                    const V k = (cz ? t1 : t0)[((dx + 1) + 3 * (dy + 1)) * 64];
+                for (int dx = 1; dx >= -1; --dx) {
+                    const V k = t[((dx + 1) + 3 * (dy + 1)) * 64];
 #pragma unroll
                     for (int cy = 0; cy < 2; ++cy) {
                         const int sy = cy - dy + 1;
                         if (sy < 2 * h || sy > 2 * h + 1) continue;
 #pragma unroll
                         for (int cx = 0; cx < 2; ++cx) {
-                            const int c = cx | (cy << 1) | (cz << 2);
+                            const int c = cx | (cy << 1);
                             const int sxy = (cx - dx + 1) + 4 * (sy - 2 * h);
 #pragma unroll
-                            for (int q = 0; q < FPL; ++q) cmac(ar[q][c], ai[q][c], f[sxy].v[q], k.v[q]);
+                            for (int q = 0; q < FPL; ++q) cmac(ar[d][q][c], ai[d][q][c], f[sxy].v[q], k.v[q]);
                         }
                     }
                 }
             }
         }
     };
-    using First = std::integral_constant<int, 0>;
-    using Mid = std::integral_constant<int, -1>;
-    using Last = std::integral_constant<int, 3>;
+    // target slab ar[2] / ai[2] to the items tg[0..3].  Streamed past the caches: the output is
+    // read once, by the inverse transform, and must not evict the source spectra this kernel
+    // re-reads (measured: this Prod 15% faster, the inverse 10% slower, the pair 7% faster at
+    // 128^3 FP64)
+    auto store = [&](bool on, ScalarList tg) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int t = tg[c];
+            V o;
+#pragma unroll
+            for (int q = 0; q < FPL; ++q) o.v[q] = cplx<T>{ar[2][q][c], ai[2][q][c]};
+            buffer_stream(ubase + (int64_t)(t < 0 ? 0 : t) * kItemBytes<T>, on && t >= 0 ? uspan : 0u, sbytes, o);
+        }
+    };
+    store(false, tgt8);  // (as every pass through the loop does)
+    issue_fence();
     using H0 = std::integral_constant<int, 0>;
     using H1 = std::integral_constant<int, 1>;
+    const int nslab = 2 * len + 2;
+    bool use[3] = {false, false, false};
 #pragma unroll 1
-    for (int r = 0; r < rounds; ++r) {
-        const int g = wave_uniform((gb + r * gstride) * kNearWaves + (threadIdx.x >> 6));
-        if (g >= ngroups) break;
-        // 4-wave workgroups whose groups all exist step through the source slabs together
-        // (a barrier before each slab's, or half slab's, loads): the waves' groups are
-        // neighbours and share half their sources, which the lockstep serves from L1 (the
-        // 256^3 Prod 689 -> 662 us FP64, 363 -> 353 us FP32; with 8 waves it was slower).
-        // The condition is uniform over the workgroup, so every wave meets the same barriers.
-        const bool lockstep = kNearWaves == 4 && (gb + r * gstride) * kNearWaves + kNearWaves <= ngroups;
+    for (int s = 0; s < nslab; ++s) {
+        use[2] = use[1];
+        use[1] = use[0];
+        use[0] = target(s);
+        const bool more = s + 1 < nslab;
+        const ScalarList tg = tgt8 + (int64_t)(g0 + ((s > 1 ? s - 2 : 0) >> 1)) * 8 + 4 * (s & 1);
+        // half slabs through two buffers of 8 values: the next slab's first half is in flight
+        // while this one's second half is consumed, and so on
+        arrived(fa);
+        if (ha) half(H0{}, fa, use);
+        at(more ? s + 1 : s);
+        ha = ld(0, more, fa);
+        issue_fence();
+        arrived(fb);
+        if (hb) half(H1{}, fb, use);
+        hb = ld(1, more, fb);
+        issue_fence();
+        store(use[2], tg);
 #pragma unroll
         for (int q = 0; q < FPL; ++q)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                ar[q][c] = T(0);
-                ai[q][c] = T(0);
+            for (int c = 0; c < 4; ++c) {
+                ar[2][q][c] = ar[1][q][c];
+                ai[2][q][c] = ai[1][q][c];
+                ar[1][q][c] = ar[0][q][c];
+                ai[1][q][c] = ai[0][q][c];
             }
-        sg = src64 + (int64_t)g * 64;
-        if constexpr (kPrefetch) {
-            // half slabs (source rows sy = 2h, 2h + 1) through two buffers of 8 values: the next
-            // half's loads are in flight while this half is consumed, in the registers the
-            // one-slab form uses for its 16 values.  A target meets the rows of the first half
-            // before those of the second, so it adds the same terms in the same order.
-            V fa[8], fb[8];
-            auto ld = [&](int sz, int h, V(&x)[8]) {
-                if (lockstep) __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[i] = load(sg[sz * 16 + 8 * h + i]);
-            };
-            ld(0, 0, fa);
-            ld(0, 1, fb);
-            issue_fence();
-            half(First{}, 0, H0{}, fa);
-            ld(1, 0, fa);
-            issue_fence();
-            half(First{}, 0, H1{}, fb);
-#pragma unroll 1
-            for (int sz = 1; sz < 3; ++sz) {
-                ld(sz, 1, fb);
-                issue_fence();
-                half(Mid{}, sz, H0{}, fa);
-                ld(sz + 1, 0, fa);
-                issue_fence();
-                half(Mid{}, sz, H1{}, fb);
-            }
-            ld(3, 1, fb);
-            issue_fence();
-            half(Last{}, 3, H0{}, fa);
-            issue_fence();
-            half(Last{}, 3, H1{}, fb);
-        } else {
-            V f[16];
-            if (lockstep) __syncthreads();
-#pragma unroll
-            for (int sxy = 0; sxy < 16; ++sxy) f[sxy] = load(sg[sxy]);
-            issue_fence();
-            slab(First{}, 0, f);
-#pragma unroll 1
-            for (int sz = 1; sz < 3; ++sz) {  // the middle source z slabs; x and y unrolled
-                if (lockstep) __syncthreads();
-#pragma unroll
-                for (int sxy = 0; sxy < 16; ++sxy) f[sxy] = load(sg[sz * 16 + sxy]);
-                issue_fence();
-                slab(Mid{}, sz, f);
-            }
-            if (lockstep) __syncthreads();
-#pragma unroll
-            for (int sxy = 0; sxy < 16; ++sxy) f[sxy] = load(sg[48 + sxy]);
-            issue_fence();
-            slab(Last{}, 3, f);
-        }
-        if (!live || w >= S) continue;  // (S is even, so a lane's two frequencies are both below it or not)
-        const int32_t* tg = tgt8 + (int64_t)g * 8;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int t = tg[c];
-            if (t >= 0) {
-                // streamed past the caches: the output is read once, by the inverse transform, and
-                // must not evict the source spectra this kernel re-reads (measured: this Prod 15%
-                // faster, the inverse 10% slower, the pair 7% faster at 128^3 FP64)
-                typedef T vec_t __attribute__((ext_vector_type(2 * FPL)));  // one store per lane
-                vec_t o;
-#pragma unroll
-                for (int q = 0; q < FPL; ++q) {
-                    o[2 * q] = ar[q][c];
-                    o[2 * q + 1] = ai[q][c];
-                }
-                __builtin_nontemporal_store(o, reinterpret_cast<vec_t*>(uhat + spec_at(t, w, ntgt)));
-            }
-        }
+        clear(0);
     }
 }
 
@@ -735,48 +771,38 @@ __global__ void __launch_bounds__(kProdThreads)
 template <typename T>
 constexpr int kNearFpl = sizeof(T) == 4 ? 2 : 1;
 
-// Group blocks per workgroup of the level-0 Prod: every round reuses the workgroup's kernel
-// tile, and the smaller grid leaves CUs to the far-field kernels running beside it (graph
-// solves, 4-wave workgroups: 256^3 FP32 0.947 -> 0.929 ms with 2 rounds, 128^3 FP64
-// 0.277 -> 0.259 ms and FP32 0.154 -> 0.149 ms with 4; the same bits)
-static int near_rounds(int nunits, int nblocks) {
-    const int64_t wgs = (int64_t)nunits * nblocks;
-    return wgs >= 16384 ? 2 : (wgs >= 1024 ? 4 : 1);
+// Grid and arguments of the level-0 Prod in workgroups of nw waves.
+template <typename T>
+static NearArgs<T> near_args(const NearLevel<T>& n, int nw, unsigned& grid) {
+    const int nunits = ((n.S + 63) / 64 + kNearFpl<T> - 1) / kNearFpl<T>, nblocks = (int)((n.nruns + nw - 1) / nw);
+    grid = xcd_grid(nunits, nblocks);
+    return NearArgs<T>{n.fhat, n.khat, n.tgt8,       n.src64,     n.runs,      n.flags, n.uhat,
+                       n.S,    (int)n.nruns, (int)n.nsrc, (int)n.ntgt, n.sym};
 }
 
-template <typename T, int NW, bool PF>
-static hipError_t near_nw(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* tgt8, const int32_t* src64,
-                          cplx<T>* uhat, int64_t ngroups, int64_t nsrc, int64_t ntgt, int S, hipStream_t s,
-                          const SpecSym& sym) {
-    constexpr int FPL = kNearFpl<T>;
-    const int nunits = ((S + 63) / 64 + FPL - 1) / FPL, nblocks = (int)((ngroups + NW - 1) / NW);
-    const int rounds = near_rounds(nunits, nblocks);
-    const unsigned grid = xcd_grid(nunits, (nblocks + rounds - 1) / rounds);
-    return lgf_launch(k_prod_near_grouped<T, NW, PF, FPL>, dim3(grid), dim3(64 * NW), 0, s, fhat, khat, tgt8,
-                      src64, uhat, S, (int)ngroups, (int)nsrc, (int)ntgt, sym, rounds);
+template <typename T, int NW>
+static hipError_t near_nw(const NearLevel<T>& n, hipStream_t s) {
+    unsigned grid;
+    const NearArgs<T> a = near_args<T>(n, NW, grid);
+    return lgf_launch(k_prod_near_grouped<T, NW, kNearFpl<T>>, dim3(grid), dim3(64 * NW), 0, s, a);
 }
 
-template <typename T, bool PF>
-static hipError_t near_pf(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* tgt8, const int32_t* src64,
-                          cplx<T>* uhat, int64_t ngroups, int64_t nsrc, int64_t ntgt, int S, int waves,
-                          hipStream_t s, const SpecSym& sym) {
-    switch (waves) {
-        case 2: return near_nw<T, 2, PF>(fhat, khat, tgt8, src64, uhat, ngroups, nsrc, ntgt, S, s, sym);
-        case 8: return near_nw<T, 8, PF>(fhat, khat, tgt8, src64, uhat, ngroups, nsrc, ntgt, S, s, sym);
-        default: return near_nw<T, 4, PF>(fhat, khat, tgt8, src64, uhat, ngroups, nsrc, ntgt, S, s, sym);
-    }
+// a lane's 32-bit offsets span kNearFpl consecutive chunks of the source spectra and of the output
+template <typename T>
+static bool near_fits(const NearLevel<T>& n) {
+    return n.S > 0 && n.S % 2 == 0 && chunk_fits_u32<T>((n.nsrc + 1) * kNearFpl<T>) &&
+           chunk_fits_u32<T>(n.ntgt * kNearFpl<T>) && sym_fits(n.sym, n.S);
 }
 
 template <typename T>
-hipError_t launch_prod_near(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* tgt8, const int32_t* src64,
-                            cplx<T>* uhat, int64_t ngroups, int64_t nsrc, int64_t ntgt, int S, int waves,
-                            int prefetch, hipStream_t s, const SpecSym& sym) {
-    if (ngroups <= 0) return hipSuccess;
-    // a lane's 32-bit offsets span kNearFpl consecutive chunks of the source spectra
-    if (S <= 0 || S % 2 || !chunk_fits_u32<T>((nsrc + 1) * kNearFpl<T>) || !sym_fits(sym, S))
-        return hipErrorInvalidValue;
-    return prefetch ? near_pf<T, true>(fhat, khat, tgt8, src64, uhat, ngroups, nsrc, ntgt, S, waves, s, sym)
-                    : near_pf<T, false>(fhat, khat, tgt8, src64, uhat, ngroups, nsrc, ntgt, S, waves, s, sym);
+hipError_t launch_prod_near(const NearLevel<T>& n, int waves, hipStream_t s) {
+    if (n.nruns <= 0) return hipSuccess;
+    if (!near_fits(n)) return hipErrorInvalidValue;
+    switch (waves) {
+        case 2: return near_nw<T, 2>(n, s);
+        case 8: return near_nw<T, 8>(n, s);
+        default: return near_nw<T, 4>(n, s);
+    }
 }
 
 // LGF_M2L_WIDE_LISTS=1 in the environment keeps the 32-bit list entries at every level
@@ -787,10 +813,10 @@ static bool m2l_wide_lists() {
     return v && v[0] == '1';
 }
 
-template <typename T, int NW, int CPL>
-static hipError_t far_nw(const FarLevel<T>* lv, int nlev, hipStream_t s) {
-    constexpr int F = M2LShape<T>::F, PPG = M2LShape<T>::PPW * NW;
-    FarSegs<T> segs{};
+// Segments of one launch for workgroups of PPG parents; returns the grid.
+template <typename T>
+static unsigned far_segments(const FarLevel<T>* lv, int nlev, int PPG, FarSegs<T>& segs) {
+    constexpr int F = M2LShape<T>::F;
     unsigned grid = 0;
     for (int k = 0; k < nlev; ++k) {
         const int ngb = (int)((lv[k].nparents + PPG - 1) / PPG);
@@ -802,11 +828,23 @@ static hipError_t far_nw(const FarLevel<T>* lv, int nlev, hipStream_t s) {
         grid += xcd_grid(nchunks, ngb);  // a multiple of the XCD count
     }
     segs.n = nlev;
-    // 16-bit list entries in LDS when every level's items (and the sentinel) fit: less LDS
-    // per workgroup, so more workgroups share a CU
+    return grid;
+}
+
+// 16-bit list entries in LDS when every level's items (and the sentinel) fit: less LDS per
+// workgroup, so more workgroups share a CU
+template <typename T>
+static bool far_idx16(const FarLevel<T>* lv, int nlev) {
     bool idx16 = !m2l_wide_lists();
     for (int k = 0; k < nlev; ++k) idx16 = idx16 && lv[k].nsrc < 65535;
-    if (idx16)
+    return idx16;
+}
+
+template <typename T, int NW, int CPL>
+static hipError_t far_nw(const FarLevel<T>* lv, int nlev, hipStream_t s) {
+    FarSegs<T> segs{};
+    const unsigned grid = far_segments<T>(lv, nlev, M2LShape<T>::PPW * NW, segs);
+    if (far_idx16<T>(lv, nlev))
         return lgf_launch(k_prod_far_sib<T, NW, CPL, uint16_t>, dim3(grid), dim3(64 * NW * (8 / CPL)), 0, s, segs);
     return lgf_launch(k_prod_far_sib<T, NW, CPL, int32_t>, dim3(grid), dim3(64 * NW * (8 / CPL)), 0, s, segs);
 }
@@ -862,46 +900,61 @@ void m2l_default(int64_t nparents, bool idx16, int& waves, int& cpl) {
     if (cpl == 0) cpl = big ? 4 : 2;
 }
 
+// Number of levels with parents (empty levels only at the end), or -1 where a level does not
+// fit what the kernels assume; most: parents of the largest.
+template <typename T>
+static int far_check(const FarLevel<T>* lv, int nlev, int64_t& most) {
+    int k = 0;
+    most = 0;
+    for (int i = 0; i < nlev; ++i) {
+        if (lv[i].nparents <= 0) continue;
+        if (k != i || !chunk_fits_u32<T>(lv[i].nsrc + 1) || !sym_fits(lv[i].sym, lv[i].S)) return -1;
+        most = lv[i].nparents > most ? lv[i].nparents : most;
+        ++k;
+    }
+    return k > kMaxFarSegs ? -1 : k;
+}
+
+// With the variant left open, a level whose workgroups in the largest level's variant would
+// exceed half that level's count (many frequency chunks, few parents: the 34-point levels of
+// the lattice scheme) gets a launch of its own with its own default variant; the others
+// (returned in keep) stay in one launch.
+template <typename T>
+static hipError_t far_split(const FarLevel<T>* lv, int k, int waves, int cpl, hipStream_t s, FarLevel<T>* keep,
+                            int& nk) {
+    constexpr int F = M2LShape<T>::F;
+    const int groups = std::min(waves, (sizeof(T) == 8 ? 8 : 16) / (8 / cpl));
+    const int64_t ppg = (int64_t)M2LShape<T>::PPW * groups;
+    auto wgs = [&](const FarLevel<T>& l) {
+        return (int64_t)xcd_grid((l.S + F - 1) / F, 1) * ((l.nparents + ppg - 1) / ppg);
+    };
+    int64_t wmax = 0;
+    for (int i = 0; i < k; ++i) wmax = std::max(wmax, wgs(lv[i]));
+    nk = 0;
+    for (int i = 0; i < k; ++i) {
+        if (wgs(lv[i]) == wmax || 2 * wgs(lv[i]) <= wmax) {
+            keep[nk++] = lv[i];
+        } else {
+            const hipError_t e = launch_prod_far_sib_levels<T>(&lv[i], 1, 0, 0, s);
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
+}
+
 template <typename T>
 hipError_t launch_prod_far_sib_levels(const FarLevel<T>* lv, int nlev, int waves, int cpl, hipStream_t s) {
     int64_t most = 0;
-    int k = 0;
-    bool idx16 = !m2l_wide_lists();
-    for (int i = 0; i < nlev; ++i) {
-        if (lv[i].nparents <= 0) continue;
-        if (k != i || !chunk_fits_u32<T>(lv[i].nsrc + 1) || !sym_fits(lv[i].sym, lv[i].S))
-            return hipErrorInvalidValue;  // empty levels only at the end
-        most = lv[i].nparents > most ? lv[i].nparents : most;
-        idx16 = idx16 && lv[i].nsrc < 65535;
-        ++k;
-    }
+    const int k = far_check<T>(lv, nlev, most);
+    if (k < 0) return hipErrorInvalidValue;
     if (k == 0) return hipSuccess;
-    if (k > kMaxFarSegs) return hipErrorInvalidValue;
     const bool open = waves == 0 && cpl == 0;
-    m2l_default<T>(most, idx16, waves, cpl);
+    m2l_default<T>(most, far_idx16<T>(lv, k), waves, cpl);
     if (open && k > 1) {
-        // with the variant left open, a level whose workgroups in the largest level's variant
-        // would exceed half that level's count (many frequency chunks, few parents: the
-        // 34-point levels of the lattice scheme) gets a launch of its own with its own
-        // default variant; the others stay in one launch
-        constexpr int F = M2LShape<T>::F;
-        const int groups = std::min(waves, (sizeof(T) == 8 ? 8 : 16) / (8 / cpl));
-        const int64_t ppg = (int64_t)M2LShape<T>::PPW * groups;
-        auto wgs = [&](const FarLevel<T>& l) {
-            return (int64_t)xcd_grid((l.S + F - 1) / F, 1) * ((l.nparents + ppg - 1) / ppg);
-        };
-        int64_t wmax = 0;
-        for (int i = 0; i < k; ++i) wmax = std::max(wmax, wgs(lv[i]));
         FarLevel<T> keep[kMaxFarSegs];
         int nk = 0;
-        for (int i = 0; i < k; ++i) {
-            if (wgs(lv[i]) == wmax || 2 * wgs(lv[i]) <= wmax) {
-                keep[nk++] = lv[i];
-            } else {
-                const hipError_t e = launch_prod_far_sib_levels<T>(&lv[i], 1, 0, 0, s);
-                if (e != hipSuccess) return e;
-            }
-        }
+        const hipError_t e = far_split<T>(lv, k, waves, cpl, s, keep, nk);
+        if (e != hipSuccess) return e;
         if (nk < k) return launch_prod_far_sib_levels<T>(keep, nk, waves, cpl, s);
     }
     switch (cpl) {
@@ -934,9 +987,7 @@ hipError_t launch_prod_far(const cplx<T>* fhat, const cplx<T>* khat, const int32
 }
 
 #define LGF_INST(T)                                                                                              \
-    template hipError_t launch_prod_near<T>(const cplx<T>*, const cplx<T>*, const int32_t*, const int32_t*,      \
-                                            cplx<T>*, int64_t, int64_t, int64_t, int, int, int, hipStream_t,     \
-                                            const SpecSym&);                                                     \
+    template hipError_t launch_prod_near<T>(const NearLevel<T>&, int, hipStream_t);                         \
     template hipError_t launch_prod_far_sib<T>(const cplx<T>*, const cplx<T>*, const int32_t*, const int32_t*,   \
                                                cplx<T>*, int64_t, int64_t, int64_t, int, int, int, hipStream_t,  \
                                                const SpecSym&);                                                  \

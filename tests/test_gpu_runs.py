@@ -1,0 +1,64 @@
+"""GPU test of the level-0 Prod's runs: stacks of 2^3-block groups in z that one wave marches
+through.  A plan's runs are longer the more groups it has, so a tall layout alone (runs of one
+group) and a batch of many copies of it (runs of up to eight) take different paths.  Every target
+adds its sources in one order whatever the run, so the two agree bit for bit; the layout alone is
+checked against the oracle with the bars of tolerances.py (rounding order only).
+"""
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import flgf
+from paper_1402_6081_amd import workloads as W
+from tolerances import FP32_BAR, fp64_tol, rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible GPU")
+    import paper_1402_6081_amd.lgf as L
+    L.library()
+    return L
+
+
+def _tower(kind, rng):
+    """Layouts of 36 to 198 blocks whose columns of groups have every length up to 17."""
+    if kind == "column":  # one column of 17 groups and a lone block beside its foot
+        b = [(0, 0, z) for z in range(34)] + [(1, 1, 0), (2, 0, 33)]
+    elif kind == "steps":  # columns of 1, 2, 3, 5, 8 and 9 groups side by side, odd tops
+        b = [(2 * i + dx, dy, z) for i, h in enumerate((1, 3, 5, 9, 15, 18)) for dx in (0, 1) for dy in (0, 1)
+             for z in range(h) if not (dx and dy and z == h - 1)]
+    else:  # "gaps": a ragged 3 x 3 tower with an empty group layer and empty planes
+        b = [(x, y, z) for x in range(3) for y in range(3) for z in range(22)
+             if z not in (4, 5, 11, 12, 13) and rng.random() > 0.2]
+    return np.array(sorted(set(b), key=lambda t: (t[2], t[1], t[0])), dtype=np.int32)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("kind", ["column", "steps", "gaps"])
+def test_run_lengths(L, kind, prec):
+    n, p = 8, 6
+    rng = np.random.default_rng(zlib.crc32(kind.encode()))
+    blocks = _tower(kind, rng)
+    print("case: runs", kind, prec, len(blocks), "blocks", flush=True)
+    if prec == "f64":
+        f = rng.standard_normal((len(blocks), n, n, n))
+    else:
+        f, _ = W.zero_mean_gaussians(blocks, n, rng, max(2, len(blocks) // 8))
+    plan = L.Plan(blocks, n, p, 0, prec)
+    fd = torch.from_numpy(f).to("cuda:0", plan.dtype)
+    u = plan.solve(fd)
+    ref = flgf.FLGF(blocks, n, p, 0).solve(fd.cpu().numpy().astype(np.float64))
+    assert rel(u.cpu().numpy().astype(np.float64), ref) <= (fp64_tol(p) if prec == "f64" else FP32_BAR)
+    copies = 56
+    batch = L.Plan.batch([blocks] * copies, n, p, 0, prec)
+    ub = batch.solve(fd.repeat(copies, 1, 1, 1).contiguous())
+    for part in batch.split(ub):
+        assert torch.equal(part, u)
+    batch.close()
+    plan.close()
