@@ -67,6 +67,12 @@ struct HostLevel {
     std::vector<int32_t> coords;  // [nint][3] (single layouts only; empty in unions)
     std::vector<int32_t> child8;  // [nint][8] children at level l-1 (levels >= 2)
     std::vector<int32_t> src216;  // [nint][216] children of the 27 neighbours, sentinel = N_{l-1}
+    // the M2L of the level below over these parents: the parents by decreasing number of
+    // neighbours that hold a source, and in that order their children, lists and neighbours (bit
+    // e of 27, the parent itself left out); spread: the average is below two thirds of the most
+    std::vector<int32_t> m2l_ord;
+    std::vector<uint32_t> m2l_mask;
+    bool m2l_spread = false;
     int64_t sib_pairs = 0;        // interaction-list entries of targets served through parents
     // top level of a truncated tree: explicit lists over a target subset
     std::vector<int32_t> csr_tgt, csr_ptr{0}, csr_src;
@@ -112,6 +118,9 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
 // Level-0 groups renumbered so that the groups of a run are consecutive, runs of neighbouring
 // columns following each other; fills g0_runs and g0_flags.
 void order_groups(HostPlan& H);
+
+// Fills m2l_ord, m2l_mask and m2l_spread of the levels >= 2.
+void order_parents(HostPlan& H);
 
 // Every list index within its array's range; LGF_ERR_LAYOUT otherwise.
 lgf_status check_host(const HostPlan& H);

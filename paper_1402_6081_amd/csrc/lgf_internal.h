@@ -202,17 +202,12 @@ inline bool sym_fits(const SpecSym& y, int S) {
     return !y.info || (y.M > 0 && y.ncls > 0 && y.ncls <= 65536 && S == y.M * y.M * (y.M / 2 + 1));
 }
 // Levels >= 1 below the top: over parents (child8 and the 216 candidate sources src216 of
-// each parent), offsets radius 3.
-// waves: parent groups per workgroup (1, 2, 4); cpl: children accumulated per lane (8, 4, 2,
-// 1); 0 = chosen from the level's size.
-template <typename T>
-// fhat holds nsrc + 1 items (sentinel nsrc), uhat nitems items; nsrc = nitems unless the
-// level reads another level's spectra (level 1 of the lattice scheme reads the blocks').
-hipError_t launch_prod_far_sib(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* child8,
-                               const int32_t* src216, cplx<T>* uhat, int64_t nparents, int64_t nitems, int64_t nsrc,
-                               int S, int waves, int cpl, hipStream_t s, const SpecSym& sym = SpecSym{});
-// The same over several levels in one launch, each with its own spectrum size S (at most
-// kMaxFarSegs levels, each with nparents > 0, in the order given).
+// each parent), offsets radius 3; several levels in one launch, each with its own spectrum
+// size S (at most kMaxFarSegs levels, each with nparents > 0, in the order given).
+// waves: parent groups per workgroup; cpl: children accumulated per lane (8, 4, 2, 1);
+// 0 = chosen from the level's size.  fhat holds nsrc + 1 items (sentinel nsrc), uhat nitems
+// items; nsrc = nitems unless the level reads another level's spectra (level 1 of the lattice
+// scheme reads the blocks').
 constexpr int kMaxFarSegs = 8;
 template <typename T>
 struct FarLevel {
@@ -224,6 +219,10 @@ struct FarLevel {
     int64_t nparents, nitems, nsrc;
     int S;
     SpecSym sym;  // reduced kernel spectra, or none
+    // the neighbours of each parent that hold a source, bit e of 27 (bit 13 clear); the parents
+    // (mask, child8, src216) by decreasing number of neighbours
+    const uint32_t* mask;
+    bool heavy_first;  // the parents' numbers of neighbours spread widely (HostLevel::m2l_spread)
 };
 template <typename T>
 hipError_t launch_prod_far_sib_levels(const FarLevel<T>* lv, int nlev, int waves, int cpl, hipStream_t s);

@@ -91,7 +91,12 @@ struct LevelPlan {
     int64_t sib_pairs = 0, csr_entries = 0, ncsr = 0;
     bool zero_uhat = false;
     std::shared_ptr<SpectraEntry> spectra, spectra_csr;  // radius 3 / radius of the CSR offsets
-    int32_t *d_child8 = nullptr, *d_src216 = nullptr;
+    int32_t* d_child8 = nullptr;
+    // these intervals as parents of the M2L below: children, candidate sources and neighbours
+    // holding a source, by decreasing number of neighbours
+    int32_t *d_m2l_child8 = nullptr, *d_m2l_src216 = nullptr;
+    uint32_t* d_m2l_mask = nullptr;
+    bool m2l_spread = false;
     int32_t *d_csr_tgt = nullptr, *d_csr_ptr = nullptr, *d_csr_src = nullptr, *d_csr_off = nullptr;
     void *d_ftil = nullptr, *d_fhat = nullptr, *d_uhat = nullptr, *d_util = nullptr;
     int64_t pairs() const { return sib_pairs + csr_entries; }
@@ -185,6 +190,13 @@ hipError_t upload(void* dst, const std::vector<V>& v, hipStream_t s) {
     return hipMemcpyAsync(dst, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice, s);
 }
 
+// The rows of a parent list in the M2L's order of parents.
+std::vector<int32_t> m2l_sorted(const HostLevel& P, const std::vector<int32_t>& list, size_t per) {
+    std::vector<int32_t> out(list.size());
+    for (size_t i = 0; i < P.m2l_ord.size(); ++i) std::copy_n(&list[per * P.m2l_ord[i]], per, &out[per * i]);
+    return out;
+}
+
 // Profiling: a solve records [solve start, solve end] and, per step, [start, end] events on
 // the stream the step runs on (the step list is described on the first recorded solve).
 struct Marker {
@@ -262,6 +274,24 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     const bool split = overlap && ov == 1;
     hipStream_t s2 = overlap ? pl->far_stream : s;
     hipStream_t s3 = split ? pl->far_stream2 : s2;
+    // the M2L of level l over its parents' lists (level 1 of the lattice scheme reads the blocks'
+    // own spectra)
+    auto far_level = [&](int l) -> FarLevel<T> {
+        const LevelPlan &L = pl->lv[l], &Pp = pl->lv[l + 1];
+        const bool reuse0 = l == 1 && pl->lat1;
+        return FarLevel<T>{reuse0 ? (const C*)pl->d_fhat0 : (const C*)L.d_fhat,
+                           (const C*)L.spectra->dev,
+                           Pp.d_m2l_child8,
+                           Pp.d_m2l_src216,
+                           (C*)L.d_uhat,
+                           Pp.nint,
+                           L.nint,
+                           reuse0 ? pl->nsrc : L.nint,
+                           L.spectra->S,
+                           L.spectra->sym,
+                           Pp.d_m2l_mask,
+                           Pp.m2l_spread};
+    };
     // forward work of level l: PadFFT and the M2L products (Steps 1-2)
     auto level_up = [&](int l, hipStream_t st, bool sib = true, bool fwd = true) -> hipError_t {
         LevelPlan& L = pl->lv[l];
@@ -283,11 +313,8 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             LGF_STEP(st, zero_fill(L.d_uhat, L.nint * Slp(l) * 2 * (int64_t)sizeof(T), st), lname("zero_uhat_l", l),
                      lvN(l) * S1 * cs, 0.0);
         if (sib && L.sib_pairs > 0) {
-            const LevelPlan& Pp = pl->lv[l + 1];
-            LGF_STEP(st,
-                     (launch_prod_far_sib<T>(fhat, (const C*)L.spectra->dev, Pp.d_child8, Pp.d_src216, (C*)L.d_uhat,
-                                             Pp.nint, L.nint, nsrc_items, L.spectra->S, tc.far_waves,
-                                             tc.far_children, st, L.spectra->sym)),
+            const FarLevel<T> one = far_level(l);
+            LGF_STEP(st, (launch_prod_far_sib_levels<T>(&one, 1, tc.far_waves, tc.far_children, st)),
                      lname("prod_l", l), ((double)L.nsrc_int + lvN(l) + khat_rows(*L.spectra, 316)) * S1 * cs,
                      (double)L.sib_pairs * S1 * 8.0);
         }
@@ -405,12 +432,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             for (int l = 1; l <= pl->Ltop; ++l) {
                 LevelPlan& L = pl->lv[l];
                 if (L.pairs() == 0 || L.sib_pairs == 0) continue;
-                const LevelPlan& Pp = pl->lv[l + 1];
-                // level 1 of the lattice scheme reads the blocks' own spectra
-                const bool reuse0 = l == 1 && pl->lat1;
-                fl.push_back(FarLevel<T>{reuse0 ? (const C*)pl->d_fhat0 : (const C*)L.d_fhat,
-                                         (const C*)L.spectra->dev, Pp.d_child8, Pp.d_src216, (C*)L.d_uhat, Pp.nint,
-                                         L.nint, reuse0 ? pl->nsrc : L.nint, L.spectra->S, L.spectra->sym});
+                fl.push_back(far_level(l));
                 bytes += ((double)L.nsrc_int + lvN(l) + khat_rows(*L.spectra, 316)) * Sl(l) * cs;
                 flops += (double)L.sib_pairs * Sl(l) * 8.0;
                 if (!lo) lo = l;
@@ -593,7 +615,7 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     const int64_t S1 = spec_padded(2 * p * 2 * p * (p + 1));
     const int64_t p3 = (int64_t)p * p * p;
     const int64_t nb = H.nb;
-    const int topc = std::min(pl->Ltop + 1, H.L);  // highest level whose child8 / src216 is used
+    const int topc = std::min(pl->Ltop + 1, H.L);  // highest level whose lists are used
     const int64_t need = workspace_need(H, prec);
     if (!budget_reserve(need)) return fail(LGF_ERR_BUDGET, "plan workspace exceeds the device-memory budget");
     pl->ws_bytes = need;
@@ -624,10 +646,14 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     }
     for (int l = 2; ok && l <= topc && pl->Ltop >= 1; ++l)
         ok = dev_alloc(pl, &pl->lv[l].d_child8, H.lv[l].nint * 32) &&
-             dev_alloc(pl, &pl->lv[l].d_src216, H.lv[l].nint * 216 * 4);
+             dev_alloc(pl, &pl->lv[l].d_m2l_src216, H.lv[l].nint * 216 * 4) &&
+             dev_alloc(pl, &pl->lv[l].d_m2l_child8, H.lv[l].nint * 32) &&
+             dev_alloc(pl, &pl->lv[l].d_m2l_mask, H.lv[l].nint * 4);
     if (ok) ok = dev_alloc(pl, &pl->d_scratch, scratch_need(H));
     if (ok) ok = dev_alloc(pl, &pl->d_flag, 4);
     if (!ok) return fail(LGF_ERR_OOM, "device allocation failed for the plan workspace");
+    // (the uploads read these until the synchronisation below)
+    std::vector<std::vector<int32_t>> src_sorted(H.L + 1), child_sorted(H.L + 1);
     hipError_t e = upload(pl->d_g0_tgt8, H.g0_tgt8, s);
     if (e == hipSuccess) e = upload(pl->d_g0_src64, H.g0_src64, s);
     if (e == hipSuccess) e = upload(pl->d_g0_runs, H.g0_runs, s);
@@ -647,8 +673,14 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
         }
     }
     for (int l = 2; e == hipSuccess && l <= topc && pl->Ltop >= 1; ++l) {
-        e = upload(pl->lv[l].d_child8, H.lv[l].child8, s);
-        if (e == hipSuccess) e = upload(pl->lv[l].d_src216, H.lv[l].src216, s);
+        LevelPlan& Lv = pl->lv[l];
+        e = upload(Lv.d_child8, H.lv[l].child8, s);
+        Lv.m2l_spread = H.lv[l].m2l_spread;
+        src_sorted[l] = m2l_sorted(H.lv[l], H.lv[l].src216, 216);
+        child_sorted[l] = m2l_sorted(H.lv[l], H.lv[l].child8, 8);
+        if (e == hipSuccess) e = upload(Lv.d_m2l_src216, src_sorted[l], s);
+        if (e == hipSuccess) e = upload(Lv.d_m2l_child8, child_sorted[l], s);
+        if (e == hipSuccess) e = upload(Lv.d_m2l_mask, H.lv[l].m2l_mask, s);
     }
     // the source-spectra arrays start zeroed: their last item is the zero sentinel
     if (e == hipSuccess) e = zero_fill(pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz, s);

@@ -97,11 +97,12 @@ __device__ __forceinline__ void buffer_stream(char* p, uint32_t bytes, uint32_t 
 }
 // The buffered loads have arrived: placed before a branch on their use, so that the wait is
 // outside it and both ways leave the same loads in flight.
-template <typename V>
-__device__ __forceinline__ void arrived(V (&x)[8]) {
+template <typename V, int N>
+__device__ __forceinline__ void arrived(V (&x)[N]) {
+    typedef unsigned int words __attribute__((ext_vector_type(sizeof(V) / 4)));
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        u32x4 r = __builtin_bit_cast(u32x4, x[i]);
+    for (int i = 0; i < N; ++i) {
+        words r = __builtin_bit_cast(words, x[i]);
         asm volatile("" : "+v"(r));
         x[i] = __builtin_bit_cast(V, r);
     }
@@ -375,7 +376,9 @@ __global__ void __launch_bounds__(64 * kNearWaves) k_prod_near_grouped(const Nea
 // ------------------------------------------------------------------ levels >= 1, sibling blocked
 // Parents J (level l+1): src216[J][e * 8 + cs] = level-l interval 2(J + e') + cs with
 // e' = (ex-1, ey-1, ez-1), e = ex + 3 ey + 9 ez, or the zero sentinel item (index nitems);
-// child8[J][c] = target 2J + c (or -1).  khat: 343 offsets, id (Dx+3) + 7 (Dy+3) + 49 (Dz+3).
+// child8[J][c] = target 2J + c (or -1); mask[J]: bit e set when neighbour e holds a source (never
+// bit 13, the parent itself, all of whose pairs are near).  khat: 343 offsets, id
+// (Dx+3) + 7 (Dy+3) + 49 (Dz+3).
 //
 // The target child c receives source child cs of neighbour e at offset D = c - cs - 2e'.
 // Register blocking: a lane owns one frequency of one parent and accumulates CPL of its 8
@@ -384,232 +387,109 @@ __global__ void __launch_bounds__(64 * kNearWaves) k_prod_near_grouped(const Nea
 // (child, source child) pairs need only the kernel values at delta = c - cs, each read once
 // from LDS and applied to every pair with that delta.  The delta loop is unrolled and has
 // no branch: the interaction-list condition |D|_inf >= 2 is met by zero kernel rows at the
-// near offsets (the centre neighbour, all of whose pairs are near, is skipped whole).
-// Every child sums its terms in the same order (neighbour e, then delta) whatever CPL and
-// the number of waves, so all variants give identical results.  A neighbour whose children
-// are all the zero sentinel for every parent of a wave (absent intervals, or intervals
-// without sources) is skipped by that wave: the terms it would add are exact zeros.
+// near offsets.  Every child sums its terms in the same order (its parent's neighbours by
+// increasing e, then delta) whatever CPL, the number of waves and the order of the parents, so
+// all variants give identical results; neighbours that hold no source would add exact zeros.
 // Lanes: F consecutive frequencies (one 128-byte segment of a spectrum) x 64/F parents.
-// The workgroup's waves share the [343][F] kernel tile (its Dz >= 0 half, below) and the
-// parents' source indices in LDS.
+//
+// Each parent steps through its own neighbours, not through all that a wave's parents have: on
+// small levels, ragged layouts and batches the parents of a wave share few (a 2^3-parent level:
+// 7 of 26 each, all 26 together), and the plan sorts the parents by their number of neighbours,
+// so the lanes of a wave finish together.  The lanes' kernel rows then differ, so the tile holds
+// all 343 rows (44 KB), and a neighbour step's rows are constant offsets from the lane's own
+// base.  Bound by the vector units and, on small levels, by the longest parent's chain of steps.
+// Against a wave stepping through every neighbour of its parents (and a half tile), us per step
+// with its event: 256^3 FP64 350 -> 308, FP32 209 -> 175 (the n = 16, p = 8 cubes); 128^3 72 -> 50
+// and 43 -> 33; 48 ragged layouts FP32 259 -> 134; separate-set ring FP64 287 -> 176; the n_I = 17
+// scheme FP64 384 -> 272; 64 blocks of 8^3 FP64 18 -> 9.
 template <typename T>
 struct M2LShape {
     static constexpr int F = 128 / (int)sizeof(cplx<T>);  // frequencies per chunk: 8 FP64, 16 FP32
     static constexpr int PPW = 64 / F;                     // parents per wave
 };
-// The kernel tile keeps the half with Dz >= 0 (196 of its 343 rows): FP64 25 instead of
-// 44 KB of LDS, so four 4-wave workgroups share a CU (FP32 five).  The kernel spectra of opposite
-// offsets are complex conjugates (the kernel is real and even, Sec. 2.1, and its padded
-// tile is placed symmetrically about the origin: offset r at circulant index r mod M, zero
-// at M/2; so the -D tile is the D tile reflected, and its DFT the conjugate).  An offset
-// with Dz < 0 is read as the conjugate of the row of -D.  In a neighbour step the deltas of
-// one dz slab share Dz = dz - 2 ez, so a slab either reads D or conjugates throughout.
-template <typename T>
-struct M2LTile {
-    static constexpr bool kHalf = true;  // (the full tile: kRow0 = 0, every slab reads D)
-    static constexpr int kRow0 = kHalf ? 147 : 0;  // first row id kept: D = (-3, -3, 0)
-    static constexpr int kRows = 343 - kRow0;
-};
-
-// v with its sign flipped when flip (wave-uniform): one integer XOR on the sign bit
-template <typename T>
-__device__ __forceinline__ T neg_if(T v, bool flip) {
-    if constexpr (sizeof(T) == 8) {
-        const unsigned long long m = (unsigned long long)flip << 63;
-        return __longlong_as_double(__double_as_longlong(v) ^ (long long)m);
-    } else {
-        const unsigned m = (unsigned)flip << 31;
-        return __uint_as_float(__float_as_uint(v) ^ m);
-    }
-}
-
-// ar + i ai += f * conj(k): the conjugate's sign goes into the FMAs' operands (the same
-// roundings as cmac with the sign-flipped k)
-template <typename T>
-__device__ __forceinline__ void cmac_conj(T& ar, T& ai, const cplx<T>& f, const cplx<T>& k) {
-    ar = fma(f.x, k.x, ar);
-    ar = fma(f.y, k.y, ar);
-    ai = fma(-f.x, k.y, ai);
-    ai = fma(f.y, k.x, ai);
-}
 
 // child i of subset Q when a lane accumulates CPL children (subsets split z, then y, then x)
 template <int CPL, int Q>
 __device__ constexpr int m2l_child(int i) { return Q * CPL + i; }
 
-// The deltas of one dz slab applied to this lane's children.  kb points at the row of
-// delta d = 0; delta d reads kb[s (dx + 7 dy) F] with s = 1, or s = -1 when the slab reads
-// the rows of -D.  CONJ: 0 reads D, 1 conjugates (compile-time), 2 decides by flip
-// (wave-uniform, one sign-bit XOR per kernel value).  (ex, ey, ez) is the neighbour's
-// offset e': a delta whose offset D = d - 2e' is near (|D|_inf <= 1, a zero row of the
-// tile) adds nothing and is skipped; with e' known at compile time, as in the unrolled
-// neighbour loops, that costs no instruction.
-template <typename T, int CPL, int Q, int CONJ>
-__device__ __forceinline__ void m2l_slab(int dz, const cplx<T>* kb, bool flip, const cplx<T> (&fa)[8],
-                                         T (&ar)[CPL], T (&ai)[CPL], int ex, int ey, int ez) {
+// The contribution of one neighbour to this lane's children, with source values fa.  kb points
+// at the tile row of delta (-1, -1, -1) for the lane's neighbour, so every delta's row is a
+// constant offset away whatever the neighbour.  The deltas of one dz slab form one scheduling
+// region, so the multiply-adds of several deltas interleave (deeper prefetches of the kernel
+// values, 3 to 6 in flight, were 2-4% slower on large levels).
+template <typename T, int CPL, int Q>
+__device__ __forceinline__ void m2l_neighbour(const cplx<T>* kb, const cplx<T> (&fa)[8], T (&ar)[CPL], T (&ai)[CPL]) {
     constexpr int F = M2LShape<T>::F;
-#pragma unroll
-    for (int dd = 0; dd < 9; ++dd) {
-        const int dx = dd % 3 - 1, dy = dd / 3 - 1;
-        const int Dx = dx - 2 * ex, Dy = dy - 2 * ey, Dz = dz - 2 * ez;
-        if (Dx >= -1 && Dx <= 1 && Dy >= -1 && Dy <= 1 && Dz >= -1 && Dz <= 1) continue;  // near
-        bool used = false;  // compile-time: does a child of this subset pair with delta d?
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            const int c = m2l_child<CPL, Q>(i);
-            const int csx = (c & 1) - dx, csy = ((c >> 1) & 1) - dy, csz = (c >> 2) - dz;
-            used |= csx >= 0 && csx <= 1 && csy >= 0 && csy <= 1 && csz >= 0 && csz <= 1;
-        }
-        if (!used) continue;
-        cplx<T> k;
-        if constexpr (CONJ == 2) {
-            k = kb[(flip ? -(dx + 7 * dy) : dx + 7 * dy) * F];
-            k.y = neg_if<T>(k.y, flip);
-        } else {
-            k = kb[(CONJ ? -(dx + 7 * dy) : dx + 7 * dy) * F];
-        }
-#pragma unroll
-        for (int i = 0; i < CPL; ++i) {
-            const int c = m2l_child<CPL, Q>(i);
-            const int csx = (c & 1) - dx, csy = ((c >> 1) & 1) - dy, csz = (c >> 2) - dz;
-            if (csx < 0 || csx > 1 || csy < 0 || csy > 1 || csz < 0 || csz > 1) continue;  // compile-time
-            if constexpr (CONJ == 1)
-                cmac_conj(ar[i], ai[i], fa[csx | (csy << 1) | (csz << 2)], k);
-            else
-                cmac(ar[i], ai[i], fa[csx | (csy << 1) | (csz << 2)], k);
-        }
-    }
-}
-
-// The contribution of neighbour e to this lane's children, with source values fa.  The
-// kernel tile holds zeros in the near-offset rows (|D| <= 1), which only near pairs would
-// read; the slabs skip those deltas (exact zero terms: the sums' bits are the same either
-// way).  The deltas of one dz slab form one scheduling region, so the multiply-adds of
-// several deltas interleave.  LAYER = ez of the neighbours this code serves when known at
-// compile time (each slab then reads D or conjugates in code of its own), else 2.
-template <typename T, int CPL, int Q, int LAYER = 2>
-__device__ __forceinline__ void m2l_neighbour(int e, const cplx<T> (&fa)[8], const cplx<T>* tk, T (&ar)[CPL],
-                                              T (&ai)[CPL]) {
-    constexpr int F = M2LShape<T>::F;
-    const int ex = e % 3 - 1, ey = (e / 3) % 3 - 1, ez = LAYER == 2 ? e / 9 - 1 : LAYER;  // wave-uniform
 #pragma unroll
     for (int dz = -1; dz <= 1; ++dz) {
-        if constexpr (M2LTile<T>::kHalf) {
-            // the halved tile's row (Dx+3) + 7 (Dy+3) + 49 Dz holds D, Dz = dz - 2 ez
-            const cplx<T>* plain = tk + ((3 - 2 * ex) + 7 * (3 - 2 * ey) + 49 * (dz - 2 * ez)) * F;
-            const cplx<T>* mirror = tk + ((3 + 2 * ex) + 7 * (3 + 2 * ey) + 49 * (2 * ez - dz)) * F;
-            if constexpr (LAYER == 2) {
-                const bool flip = dz - 2 * ez < 0;
-                m2l_slab<T, CPL, Q, 2>(dz, flip ? mirror : plain, flip, fa, ar, ai, ex, ey, ez);
-            } else if constexpr (LAYER < 0) {
-                m2l_slab<T, CPL, Q, 0>(dz, plain, false, fa, ar, ai, ex, ey, ez);
-            } else {
-                // LAYER = 1: every slab conjugates; LAYER = 0: the dz = -1 slab only
-                if (LAYER == 1 || dz < 0)
-                    m2l_slab<T, CPL, Q, 1>(dz, mirror, true, fa, ar, ai, ex, ey, ez);
-                else
-                    m2l_slab<T, CPL, Q, 0>(dz, plain, false, fa, ar, ai, ex, ey, ez);
+#pragma unroll
+        for (int dd = 0; dd < 9; ++dd) {
+            const int dx = dd % 3 - 1, dy = dd / 3 - 1;
+            bool used = false;  // compile-time: does a child of this subset pair with delta d?
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) {
+                const int c = m2l_child<CPL, Q>(i);
+                const int csx = (c & 1) - dx, csy = ((c >> 1) & 1) - dy, csz = (c >> 2) - dz;
+                used |= csx >= 0 && csx <= 1 && csy >= 0 && csy <= 1 && csz >= 0 && csz <= 1;
             }
-        } else {
-            m2l_slab<T, CPL, Q, 0>(dz, tk + ((3 - 2 * ex) + 7 * (3 - 2 * ey) + 49 * (3 + dz - 2 * ez)) * F, false,
-                                   fa, ar, ai, ex, ey, ez);
+            if (!used) continue;
+            const cplx<T> k = kb[((dx + 1) + 7 * (dy + 1) + 49 * (dz + 1)) * F];
+#pragma unroll
+            for (int i = 0; i < CPL; ++i) {
+                const int c = m2l_child<CPL, Q>(i);
+                const int csx = (c & 1) - dx, csy = ((c >> 1) & 1) - dy, csz = (c >> 2) - dz;
+                if (csx < 0 || csx > 1 || csy < 0 || csy > 1 || csz < 0 || csz > 1) continue;  // compile-time
+                cmac(ar[i], ai[i], fa[csx | (csy << 1) | (csz << 2)], k);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-template <typename T, typename IdxT>
-__device__ __forceinline__ void m2l_load(int e, const cplx<T>* __restrict__ fb, int wl, const IdxT* si,
-                                         cplx<T> (&f)[8]) {
-    const int ee = e < 27 ? e : 26;  // past the end: a harmless reload of the last neighbour
-#pragma unroll
-    for (int cs = 0; cs < 8; ++cs) f[cs] = load_item(fb, (int)si[ee * 8 + cs], wl);
-}
-
-// Neighbours in order e = 0..26 through a pipeline of source buffers: with three, the
-// sources of e+1 and e+2 are in flight while e is consumed.
-// live: wave-uniform mask, bit e set when neighbour e holds a source for some parent of
-// the wave.
+// This lane's neighbours, the set bits of mask in order; n: the most any lane of the wave has.
+// Two source buffers, the next neighbour's sources in flight while one is consumed (a third
+// buffer was 5-8% slower: registers).  A lane that has run out takes entry 13, whose list
+// entries are the zero sentinel and whose kernel rows are zeros.
 template <typename T, int CPL, int Q, typename IdxT>
-__device__ __forceinline__ void m2l_lane(const cplx<T>* __restrict__ fb, int wl, const IdxT* si,
-                                         const cplx<T>* tk, uint32_t live, T (&ar)[CPL], T (&ai)[CPL]) {
-    if constexpr (CPL >= 4) {
-        // 4 or 8 children per lane: two buffers, the next neighbour's sources in flight
-        // while one is consumed.  The FP64 four-children lane then needs 90 registers
-        // instead of 164 (9-12% faster on the larger levels); the all-children lane 116
-        // instead of 152, and with the halved kernel tile four 4-wave workgroups share a CU
-        // (with the conjugation compiled per layer, below: the 256^3 M2L 550 -> 432 us, the
-        // 128^3 one 97 -> 81 us, the Table 2 scheme cubes 11-12% faster than with the full
-        // tile).  FP32 with the unrolled layers: 74 instead of 92 registers, six waves per
-        // SIMD instead of five, the 256^3 M2L 252 -> 234 us.  The one- and two-children
-        // lanes keep three buffers, which measured faster for them.
-        // one loop per layer ez of neighbours (9 each), so that every slab's conjugation is
-        // known at compile time; the buffer holding the next neighbour alternates between
-        // layers (9 is odd).  The loops are unrolled: each neighbour's offset is then a
-        // constant and its near deltas drop out of the code (the 256^3 M2L 435 -> 400 us
-        // FP64, 273 -> 245 us FP32; the n_I = 17 scheme's 416 -> 394 us, same bits)
-        cplx<T> fa[8], fbuf[8];
-        auto layer = [&](auto lc, int e0, cplx<T>(&x)[8], cplx<T>(&y)[8]) {
-            constexpr int LY = decltype(lc)::value;
+__device__ __forceinline__ void m2l_lane(const cplx<T>* __restrict__ fb, int wl, const IdxT* si, const cplx<T>* tk,
+                                         const int* rows, uint32_t mask, int n, T (&ar)[CPL], T (&ai)[CPL]) {
+    cplx<T> fa[8], fbuf[8];
+    const cplx<T>*ka, *kb;
+    auto take = [&](cplx<T>(&f)[8], const cplx<T>*& k) {
+        const int e = mask ? __builtin_ctz(mask) : 13;
+        mask &= mask - 1;
 #pragma unroll
-            for (int e = e0; e < e0 + 9; e += 2) {
-                m2l_load<T, IdxT>(e + 1, fb, wl, si, y);
-                issue_fence();
-                if (live & (1u << e)) m2l_neighbour<T, CPL, Q, LY>(e, x, tk, ar, ai);
-                if (e + 1 < e0 + 9) {
-                    m2l_load<T, IdxT>(e + 2, fb, wl, si, x);
-                    issue_fence();
-                    if (live & (2u << e)) m2l_neighbour<T, CPL, Q, LY>(e + 1, y, tk, ar, ai);
-                }
-            }
-        };
-        m2l_load<T, IdxT>(0, fb, wl, si, fa);
-        layer(std::integral_constant<int, -1>{}, 0, fa, fbuf);  // leaves neighbour 9 in fbuf
-        layer(std::integral_constant<int, 0>{}, 9, fbuf, fa);   // leaves neighbour 18 in fa
-        layer(std::integral_constant<int, 1>{}, 18, fa, fbuf);
-    } else {
-        cplx<T> fa[8], fbuf[8], fc[8];
-        m2l_load<T, IdxT>(0, fb, wl, si, fa);
-        m2l_load<T, IdxT>(1, fb, wl, si, fbuf);
-        // one loop per layer ez (9 neighbours, three per iteration, so the buffers line up),
-        // so that every slab's conjugation is known at compile time (the halved tile: the
-        // 256^3 FP32 M2L 282 -> 266 us, the n_I = 17 scheme's 340 -> 267 us)
-        auto layer = [&](auto lc, int e0) {
-            constexpr int LY = decltype(lc)::value;
-#pragma unroll
-            for (int e = e0; e < e0 + 9; e += 3) {
-                m2l_load<T, IdxT>(e + 2, fb, wl, si, fc);
-                issue_fence();
-                if (live & (1u << e)) m2l_neighbour<T, CPL, Q, LY>(e, fa, tk, ar, ai);
-                m2l_load<T, IdxT>(e + 3, fb, wl, si, fa);
-                issue_fence();
-                if (live & (2u << e)) m2l_neighbour<T, CPL, Q, LY>(e + 1, fbuf, tk, ar, ai);
-                m2l_load<T, IdxT>(e + 4, fb, wl, si, fbuf);
-                issue_fence();
-                if (live & (4u << e)) m2l_neighbour<T, CPL, Q, LY>(e + 2, fc, tk, ar, ai);
-            }
-        };
-        layer(std::integral_constant<int, -1>{}, 0);
-        layer(std::integral_constant<int, 0>{}, 9);
-        layer(std::integral_constant<int, 1>{}, 18);
+        for (int cs = 0; cs < 8; ++cs) f[cs] = load_item(fb, (int)si[e * 8 + cs], wl);
+        k = tk + rows[e];
+    };
+    take(fa, ka);
+#pragma unroll 1
+    for (int i = 0; i < n; i += 2) {
+        take(fbuf, kb);
+        issue_fence();
+        m2l_neighbour<T, CPL, Q>(ka, fa, ar, ai);
+        take(fa, ka);
+        issue_fence();
+        arrived(fbuf);
+        if (i + 1 < n) m2l_neighbour<T, CPL, Q>(kb, fbuf, ar, ai);
     }
 }
 
 template <typename T, int CPL, int Q = 0, typename IdxT>
-__device__ __forceinline__ void m2l_dispatch(int q, const cplx<T>* fb, int wl, const IdxT* si,
-                                             const cplx<T>* tk, uint32_t live, T (&ar)[CPL], T (&ai)[CPL]) {
+__device__ __forceinline__ void m2l_dispatch(int q, const cplx<T>* fb, int wl, const IdxT* si, const cplx<T>* tk,
+                                             const int* rows, uint32_t mask, int n, T (&ar)[CPL], T (&ai)[CPL]) {
     if constexpr (Q + 1 < 8 / CPL) {
         if (q != Q) {
-            m2l_dispatch<T, CPL, Q + 1, IdxT>(q, fb, wl, si, tk, live, ar, ai);
+            m2l_dispatch<T, CPL, Q + 1, IdxT>(q, fb, wl, si, tk, rows, mask, n, ar, ai);
             return;
         }
     }
-    m2l_lane<T, CPL, Q, IdxT>(fb, wl, si, tk, live, ar, ai);
+    m2l_lane<T, CPL, Q, IdxT>(fb, wl, si, tk, rows, mask, n, ar, ai);
 }
 
 // One launch may cover several levels (segments of the grid, each with its own spectra,
 // lists, kernel spectra and spectrum size S): the coarse levels' small
-// M2L then runs inside the level-1 launch instead of as latency-bound launches of its own.
+// M2L then runs inside the level-1 launch instead of as latency-bound launches of their own.
 // Segment k owns the workgroups [start_k, start_{k+1}); each start is a multiple of the
 // XCD count, so every segment keeps the XCD-aware chunk mapping.
 template <typename T>
@@ -619,7 +499,9 @@ struct FarSeg {
     const int32_t* child8;
     const int32_t* src216;
     cplx<T>* uhat;
+    const uint32_t* mask;
     int nparents, nitems, nsrc, ngroupblocks, start, S;
+    bool heavy_first;
     SpecSym sym;  // reduced kernel spectra (sym.info == nullptr: one spectrum per offset)
 };
 template <typename T>
@@ -628,39 +510,26 @@ struct FarSegs {
     int n;
 };
 
-// tile row r = (Dx+3) + 7 (Dy+3) + 49 (Dz+3) of a near offset (|D| <= 1 on every axis)
+// table row r = (Dx+3) + 7 (Dy+3) + 49 (Dz+3) of a near offset (|D| <= 1 on every axis)
 __device__ __forceinline__ bool m2l_near_row(int r) {
     const int dx = r % 7 - 3, dy = (r / 7) % 7 - 3, dz = r / 49 - 3;
     return dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1;
 }
 
-template <typename T, int kFarWaves, int CPL, typename IdxT>
-__global__ void __launch_bounds__(64 * kFarWaves * (8 / CPL))
-    k_prod_far_sib(const FarSegs<T> segs) {
-    constexpr int F = M2LShape<T>::F;
-    constexpr int PPW = M2LShape<T>::PPW;
-    constexpr int NQ = 8 / CPL;             // waves per group of parents (one per child subset)
-    constexpr int PPG = PPW * kFarWaves;    // parents per workgroup
-    constexpr int NT = 64 * kFarWaves * NQ;
-    constexpr int kRows = M2LTile<T>::kRows, kRow0 = M2LTile<T>::kRow0;
-    __shared__ cplx<T> tile[kRows * F];
-    __shared__ IdxT sidx[PPG * 216];  // 16-bit when every level's items fit (less LDS)
-    __shared__ uint32_t live[kFarWaves];  // per group of PPW parents: neighbours holding a source
-    // this workgroup's segment (uniform selects over the kernel arguments)
-    FarSeg<T> g = segs.s[0];
-#pragma unroll
-    for (int k = 1; k < kMaxFarSegs; ++k)
-        if (k < segs.n && (int)blockIdx.x >= segs.s[k].start) g = segs.s[k];
-    const cplx<T>* __restrict__ fhat = g.fhat;
-    const cplx<T>* __restrict__ khat = g.khat;
-    const int32_t* __restrict__ child8 = g.child8;
-    const int32_t* __restrict__ src216 = g.src216;
-    cplx<T>* __restrict__ uhat = g.uhat;
-    const int nparents = g.nparents, nitems = g.nitems, nsrc = g.nsrc, S = g.S;
-    const int nchunks = (S + F - 1) / F;
-    int chunk, pb;
-    if (!xcd_tile_at((int)blockIdx.x - g.start, nchunks, g.ngroupblocks, chunk, pb)) return;
-    const int w0 = chunk * F;
+// The kernel tile of one frequency chunk into LDS, zeros at the near offsets.  Only the 196
+// rows with Dz >= 0 are read: the kernel spectra of opposite offsets are complex conjugates (the
+// kernel is real and even, Sec. 2.1, and its padded tile is placed symmetrically about the
+// origin: offset r at circulant index r mod M, zero at M/2; so the -D tile is the D tile
+// reflected, and its DFT the conjugate).
+template <typename T, int NT>
+__device__ __forceinline__ void m2l_fill_tile(const FarSeg<T>& g, int w0, cplx<T>* tile) {
+    constexpr int F = M2LShape<T>::F, kRows = 196, kRow0 = 147;  // first row read: D = (-3, -3, 0)
+    const int S = g.S;
+    auto put = [&](int i, const cplx<T>& v) {
+        const int r = kRow0 + i / F, j = i % F;
+        tile[r * F + j] = v;
+        if (r >= kRow0 + 49) tile[(342 - r) * F + j] = cplx<T>{v.x, -v.y};
+    };
     // reduced spectra: NT is a multiple of F, so every row a thread fills has the same
     // frequency, decoded once
     if (g.sym.info != nullptr) {
@@ -681,59 +550,123 @@ __global__ void __launch_bounds__(64 * kFarWaves * (8 / CPL))
         for (int k = 0; k < NR; ++k) {
             const int i = (int)threadIdx.x + k * NT;
             kv[k] = (i < kRows * F && wok && !m2l_near_row(kRow0 + i / F))
-                        ? sym_coef(khat, inf[k], om, g.sym.ncls, g.sym.M)
+                        ? sym_coef(g.khat, inf[k], om, g.sym.ncls, g.sym.M)
                         : cplx<T>{T(0), T(0)};
         }
 #pragma unroll
         for (int k = 0; k < NR; ++k) {
             const int i = (int)threadIdx.x + k * NT;
-            if (i < kRows * F) tile[i] = kv[k];
+            if (i < kRows * F) put(i, kv[k]);
         }
     } else {
-        for (int i = threadIdx.x; i < kRows * F; i += NT) {
-            const int r = kRow0 + i / F, jj = i % F;
-            tile[i] = (w0 + jj < S && !m2l_near_row(r)) ? khat[spec_at(r, w0 + jj, 343)] : cplx<T>{T(0), T(0)};
+        // all of a thread's loads are issued before the first is stored (a loop of one load and
+        // one store each waited for every load in turn)
+        constexpr int NR = (kRows * F + NT - 1) / NT;
+        cplx<T> kv[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = (int)threadIdx.x + k * NT, r = kRow0 + (i < kRows * F ? i / F : 0), jj = i % F;
+            kv[k] = g.khat[spec_at(r, w0 + jj < S ? w0 + jj : w0, 343)];
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const int i = (int)threadIdx.x + k * NT;
+            if (i < kRows * F) put(i, w0 + i % F < S && !m2l_near_row(kRow0 + i / F) ? kv[k] : cplx<T>{T(0), T(0)});
         }
     }
-    for (int i = threadIdx.x; i < PPG * 216; i += NT) {
-        const int Jl = i / 216, k = i - Jl * 216;
-        const int J = pb * PPG + Jl;
-        sidx[i] = (IdxT)(J < nparents ? src216[(int64_t)J * 216 + k] : nsrc);  // padding parents read zeros
-    }
-    if (threadIdx.x < kFarWaves) live[threadIdx.x] = 0u;
-    __syncthreads();
-    for (int i = threadIdx.x; i < kFarWaves * 27; i += NT) {
-        const int g = i / 27, e = i - g * 27;
-        bool any = false;
-        for (int jl = g * PPW; jl < (g + 1) * PPW; ++jl)
+}
+
+// The source lists of the workgroup's PPG parents into LDS.
+template <typename IdxT, int PPG, int NT>
+__device__ __forceinline__ void m2l_stage_lists(const int32_t* __restrict__ src216, int pb, int nparents, int nsrc,
+                                                IdxT* sidx) {
+    {
+        // the parents' lists, four entries a load, in batches issued together
+        constexpr int N4 = PPG * 54, NB = (N4 + NT - 1) / NT, B = NB < 7 ? NB : 7;
+        const int have4 = (nparents - pb * PPG) * 54;  // padding parents read zeros
+        const int4* src4 = reinterpret_cast<const int4*>(src216 + (int64_t)pb * PPG * 216);
+#pragma unroll 1
+        for (int k0 = 0; k0 < NB; k0 += B) {
+            int4 v[B];
 #pragma unroll
-            for (int cs = 0; cs < 8; ++cs) any |= (int)sidx[jl * 216 + e * 8 + cs] != nsrc;
-        if (any) atomicOr(&live[g], 1u << e);
+            for (int k = 0; k < B; ++k) {
+                const int i = (int)threadIdx.x + (k0 + k) * NT;
+                v[k] = src4[i < have4 ? i : 0];
+            }
+#pragma unroll
+            for (int k = 0; k < B; ++k) {
+                const int i = (int)threadIdx.x + (k0 + k) * NT;
+                const int* e = reinterpret_cast<const int*>(&v[k]);
+                if (i < N4)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) sidx[4 * i + j] = (IdxT)(i < have4 ? e[j] : nsrc);
+            }
+        }
     }
-    __syncthreads();
+}
+
+template <typename T, int kGroups, int CPL, typename IdxT>
+__global__ void __launch_bounds__(64 * kGroups * (8 / CPL)) k_prod_far_sib(const FarSegs<T> segs) {
+    constexpr int F = M2LShape<T>::F;
+    constexpr int PPW = M2LShape<T>::PPW;
+    constexpr int NQ = 8 / CPL;           // waves per group of parents (one per child subset)
+    constexpr int PPG = PPW * kGroups;    // parents per workgroup
+    constexpr int NT = 64 * kGroups * NQ;
+    __shared__ cplx<T> tile[343 * F];
+    __shared__ alignas(16) IdxT sidx[PPG * 216];  // 16-bit when every level's items fit (less LDS)
+    __shared__ int rows[27];  // tile offset of delta (-1, -1, -1) for each neighbour
+    // this workgroup's segment (uniform selects over the kernel arguments)
+    FarSeg<T> g = segs.s[0];
+#pragma unroll
+    for (int k = 1; k < kMaxFarSegs; ++k)
+        if (k < segs.n && (int)blockIdx.x >= segs.s[k].start) g = segs.s[k];
+    const int nparents = g.nparents, nitems = g.nitems, nsrc = g.nsrc, S = g.S;
+    const int L = (int)blockIdx.x - g.start, nchunks = (S + F - 1) / F;
+    int chunk, pb;
+    if (g.heavy_first) {
+        // an XCD takes the first parents (those with the most neighbours) of all its chunks, then
+        // the next ones: the short workgroups come last and fill the launch's tail
+        const int per_xcd = (nchunks + kXcds - 1) / kXcds;
+        chunk = (L / kXcds) % per_xcd * kXcds + L % kXcds;
+        pb = (L / kXcds) / per_xcd;
+        if (chunk >= nchunks) return;
+    } else if (!xcd_tile_at(L, nchunks, g.ngroupblocks, chunk, pb)) {
+        return;
+    }
+    const int w0 = chunk * F;
     const int lane = threadIdx.x & 63;
     const int wave = wave_uniform(threadIdx.x >> 6);
     const int q = wave % NQ, pw = wave / NQ;
     const int j = lane % F;
     const int Jl = pw * PPW + lane / F;
     const int J = pb * PPG + Jl;
+    const uint32_t mask = J < nparents ? g.mask[J] : 0u;
+    m2l_fill_tile<T, NT>(g, w0, tile);
+    m2l_stage_lists<IdxT, PPG, NT>(g.src216, pb, nparents, nsrc, sidx);
+    if (threadIdx.x < 27) {
+        const int e = threadIdx.x;
+        rows[e] = (228 - 2 * (e % 3 + 7 * (e / 3 % 3) + 49 * (e / 9))) * F;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < PPG * 8; i += NT) sidx[(i >> 3) * 216 + 13 * 8 + (i & 7)] = (IdxT)nsrc;
+    __syncthreads();
     const int w = w0 + j;  // may exceed S in the last chunk: computed, never stored
-    const cplx<T>* fb = fhat + (int64_t)(w0 >> 6) * (nsrc + 1) * 64;  // this chunk's items (uniform)
+    const cplx<T>* fb = g.fhat + (int64_t)(w0 >> 6) * (nsrc + 1) * 64;  // this chunk's items (uniform)
     T ar[CPL], ai[CPL];
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
         ar[i] = T(0);
         ai[i] = T(0);
     }
-    // the centre neighbour (the parent itself) holds only near pairs
-    m2l_dispatch<T, CPL, 0, IdxT>(q, fb, w & 63, sidx + Jl * 216, tile + j,
-                                  (uint32_t)wave_uniform((int)live[pw]) & ~(1u << 13), ar, ai);
+    // the wave's first parent has the most neighbours
+    const int n = wave_uniform(__builtin_popcount(mask));
+    m2l_dispatch<T, CPL, 0, IdxT>(q, fb, w & 63, sidx + Jl * 216, tile + j, rows, mask, n, ar, ai);
     if (J >= nparents || w >= S) return;
-    const int32_t* c8 = child8 + (int64_t)J * 8 + q * CPL;
+    const int32_t* c8 = g.child8 + (int64_t)J * 8 + q * CPL;
 #pragma unroll
     for (int i = 0; i < CPL; ++i) {
         const int t = c8[i];
-        if (t >= 0) uhat[spec_at(t, w, nitems)] = cplx<T>{ar[i], ai[i]};
+        if (t >= 0) g.uhat[spec_at(t, w, nitems)] = cplx<T>{ar[i], ai[i]};
     }
 }
 
@@ -822,8 +755,9 @@ static unsigned far_segments(const FarLevel<T>* lv, int nlev, int PPG, FarSegs<T
         const int ngb = (int)((lv[k].nparents + PPG - 1) / PPG);
         const int nchunks = (lv[k].S + F - 1) / F;
         segs.s[k] = FarSeg<T>{lv[k].fhat,      lv[k].khat,         lv[k].child8,       lv[k].src216,
-                              lv[k].uhat,      (int)lv[k].nparents, (int)lv[k].nitems, (int)lv[k].nsrc,
+                              lv[k].uhat,      lv[k].mask,          (int)lv[k].nparents, (int)lv[k].nitems, (int)lv[k].nsrc,
                               ngb,             (int)grid,           lv[k].S,
+                              lv[k].heavy_first,
                               lv[k].sym};
         grid += xcd_grid(nchunks, ngb);  // a multiple of the XCD count
     }
@@ -852,8 +786,8 @@ static hipError_t far_nw(const FarLevel<T>* lv, int nlev, hipStream_t s) {
 template <typename T, int CPL>
 static hipError_t far_cpl(const FarLevel<T>* lv, int nlev, int waves, hipStream_t s) {
     // at most 16 waves (1024 threads) per workgroup, and at most 8 in FP64, whose pipeline
-    // needs more than the 128 registers a lane gets in a 16-wave workgroup.  Larger groups
-    // share one kernel tile among more parents (more waves per CU for the same LDS).
+    // needs more registers.  Larger groups share one kernel tile among more parents (more waves
+    // per CU for the same LDS).
     constexpr int kMaxWaves = sizeof(T) == 8 ? 8 : 16;
     constexpr int kMaxGroups = kMaxWaves / (8 / CPL);
     const int g = waves < kMaxGroups ? waves : kMaxGroups;
@@ -868,36 +802,18 @@ static hipError_t far_cpl(const FarLevel<T>* lv, int nlev, int waves, hipStream_
     return far_nw<T, 1, CPL>(lv, nlev, s);
 }
 
-// Variant when the plan leaves it open, from measurements on MI355X:
-//  * FP32 with 16-bit list entries: all 8 children per lane, in 4 parent groups per
-//    workgroup, or 8 for levels of at least 256 parents (the 256^3 M2L 329 -> 269 us; the
-//    128^3 one, 64 parents, stays fastest with 4: 53 us);
-//  * FP64 with at least 64 parents: all children per lane in 4 groups (the 256^3 M2L
-//    610 -> 527 us; with the halved kernel tile also the 128^3 one, 64 parents: 103 -> 99
-//    us against 4 children per lane);
-//  * levels of at least 256 parents with 32-bit entries (65535 or more intervals) as
-//    with 16-bit ones (a 77^3-block cube of n = 6, p = 7: FP64 66 -> 62 ms per solve,
-//    FP32 42 -> 36 ms);
-//  * otherwise levels with at least 64 parents run 4 children per lane in 4 parent
-//    groups; smaller levels 2 children per lane (more waves for little work) in 1 (FP64)
-//    or 2 (FP32) groups.
-// A launch over several levels takes the variant of its largest level.  Every variant
-// computes the same bits.
+// Variant when the plan leaves it open, by the parents of the launch's largest level: from 32
+// on, all 8 children per lane and 64 parents per workgroup, which share one kernel tile (256^3
+// FP64, 512 parents: 308 us, with 32 parents 338, with 4 children per lane 359; 48 ragged layouts
+// FP32, 615 parents: 137, 152, 199; 128^3, 64 parents: FP64 50, 59, 54, FP32 33, 39, 49); below,
+// 2 children per lane and 8 parents (64 blocks of 8^3 FP64, 8 parents: 9.0 us against 12.4 with
+// all children; 38 blocks of 16^3 FP32: 10.4 against 12.4): more waves for little work.  Every
+// variant computes the same bits.
 template <typename T>
-void m2l_default(int64_t nparents, bool idx16, int& waves, int& cpl) {
-    if (sizeof(T) == 4 && (idx16 || nparents >= 256)) {
-        if (waves == 0) waves = nparents >= 256 ? 8 : 4;
-        if (cpl == 0) cpl = 8;
-        return;
-    }
-    if (sizeof(T) == 8 && nparents >= 64) {
-        if (waves == 0) waves = 4;
-        if (cpl == 0) cpl = 8;
-        return;
-    }
-    const bool big = nparents >= 64;
-    if (waves == 0) waves = big ? 4 : (sizeof(T) == 8 ? 1 : 2);
-    if (cpl == 0) cpl = big ? 4 : 2;
+void m2l_default(int64_t nparents, int& waves, int& cpl) {
+    const bool big = nparents >= 32;
+    if (cpl == 0) cpl = big ? 8 : 2;
+    if (waves == 0) waves = (big ? 64 : 8) / M2LShape<T>::PPW;
 }
 
 // Number of levels with parents (empty levels only at the end), or -1 where a level does not
@@ -908,38 +824,11 @@ static int far_check(const FarLevel<T>* lv, int nlev, int64_t& most) {
     most = 0;
     for (int i = 0; i < nlev; ++i) {
         if (lv[i].nparents <= 0) continue;
-        if (k != i || !chunk_fits_u32<T>(lv[i].nsrc + 1) || !sym_fits(lv[i].sym, lv[i].S)) return -1;
+        if (k != i || !lv[i].mask || !chunk_fits_u32<T>(lv[i].nsrc + 1) || !sym_fits(lv[i].sym, lv[i].S)) return -1;
         most = lv[i].nparents > most ? lv[i].nparents : most;
         ++k;
     }
     return k > kMaxFarSegs ? -1 : k;
-}
-
-// With the variant left open, a level whose workgroups in the largest level's variant would
-// exceed half that level's count (many frequency chunks, few parents: the 34-point levels of
-// the lattice scheme) gets a launch of its own with its own default variant; the others
-// (returned in keep) stay in one launch.
-template <typename T>
-static hipError_t far_split(const FarLevel<T>* lv, int k, int waves, int cpl, hipStream_t s, FarLevel<T>* keep,
-                            int& nk) {
-    constexpr int F = M2LShape<T>::F;
-    const int groups = std::min(waves, (sizeof(T) == 8 ? 8 : 16) / (8 / cpl));
-    const int64_t ppg = (int64_t)M2LShape<T>::PPW * groups;
-    auto wgs = [&](const FarLevel<T>& l) {
-        return (int64_t)xcd_grid((l.S + F - 1) / F, 1) * ((l.nparents + ppg - 1) / ppg);
-    };
-    int64_t wmax = 0;
-    for (int i = 0; i < k; ++i) wmax = std::max(wmax, wgs(lv[i]));
-    nk = 0;
-    for (int i = 0; i < k; ++i) {
-        if (wgs(lv[i]) == wmax || 2 * wgs(lv[i]) <= wmax) {
-            keep[nk++] = lv[i];
-        } else {
-            const hipError_t e = launch_prod_far_sib_levels<T>(&lv[i], 1, 0, 0, s);
-            if (e != hipSuccess) return e;
-        }
-    }
-    return hipSuccess;
 }
 
 template <typename T>
@@ -948,30 +837,13 @@ hipError_t launch_prod_far_sib_levels(const FarLevel<T>* lv, int nlev, int waves
     const int k = far_check<T>(lv, nlev, most);
     if (k < 0) return hipErrorInvalidValue;
     if (k == 0) return hipSuccess;
-    const bool open = waves == 0 && cpl == 0;
-    m2l_default<T>(most, far_idx16<T>(lv, k), waves, cpl);
-    if (open && k > 1) {
-        FarLevel<T> keep[kMaxFarSegs];
-        int nk = 0;
-        const hipError_t e = far_split<T>(lv, k, waves, cpl, s, keep, nk);
-        if (e != hipSuccess) return e;
-        if (nk < k) return launch_prod_far_sib_levels<T>(keep, nk, waves, cpl, s);
-    }
+    m2l_default<T>(most, waves, cpl);
     switch (cpl) {
         case 8: return far_cpl<T, 8>(lv, k, waves, s);
         case 4: return far_cpl<T, 4>(lv, k, waves, s);
         case 2: return far_cpl<T, 2>(lv, k, waves, s);
         default: return far_cpl<T, 1>(lv, k, waves, s);
     }
-}
-
-template <typename T>
-hipError_t launch_prod_far_sib(const cplx<T>* fhat, const cplx<T>* khat, const int32_t* child8,
-                               const int32_t* src216, cplx<T>* uhat, int64_t nparents, int64_t nitems, int64_t nsrc,
-                               int S, int waves, int cpl, hipStream_t s, const SpecSym& sym) {
-    if (nparents <= 0) return hipSuccess;
-    const FarLevel<T> one{fhat, khat, child8, src216, uhat, nparents, nitems, nsrc, S, sym};
-    return launch_prod_far_sib_levels<T>(&one, 1, waves, cpl, s);
 }
 
 template <typename T>
@@ -988,9 +860,6 @@ hipError_t launch_prod_far(const cplx<T>* fhat, const cplx<T>* khat, const int32
 
 #define LGF_INST(T)                                                                                              \
     template hipError_t launch_prod_near<T>(const NearLevel<T>&, int, hipStream_t);                         \
-    template hipError_t launch_prod_far_sib<T>(const cplx<T>*, const cplx<T>*, const int32_t*, const int32_t*,   \
-                                               cplx<T>*, int64_t, int64_t, int64_t, int, int, int, hipStream_t,  \
-                                               const SpecSym&);                                                  \
     template hipError_t launch_prod_far_sib_levels<T>(const FarLevel<T>*, int, int, int, hipStream_t);           \
     template hipError_t launch_prod_far<T>(const cplx<T>*, const cplx<T>*, const int32_t*, const int32_t*,       \
                                            const int32_t*, const int32_t*, cplx<T>*, int64_t, int64_t, int, int, \

@@ -62,3 +62,31 @@ def test_run_lengths(L, kind, prec):
         assert torch.equal(part, u)
     batch.close()
     plan.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("parents", [2, 7, 9, 31, 32, 33, 65, 130])
+def test_m2l_parent_counts(L, parents, prec):
+    """The M2L's workgroups hold 8 or 64 parents (fewer or more in pinned variants), sorted by
+    their number of neighbours: a line of parents, one to eight children each, whose count sits
+    at those edges.  Every variant sums each parent's own neighbours in one order: bitwise equal;
+    against the oracle with the bars of tolerances.py."""
+    n, p = 4, 4
+    rng = np.random.default_rng(parents)
+    print("case: M2L parents", parents, prec, flush=True)
+    b = [(2 * i + dx, dy, dz) for i in range(parents) for dx in (0, 1) for dy in (0, 1) for dz in (0, 1)
+         if (dx, dy, dz) == (0, 0, 0) or rng.random() < 0.4]
+    blocks = np.array(b, dtype=np.int32)
+    if prec == "f64":
+        f = rng.standard_normal((len(blocks), n, n, n))
+    else:
+        f, _ = W.zero_mean_gaussians(blocks, n, rng, max(2, len(blocks) // 8))
+    plan = L.Plan(blocks, n, p, 0, prec)
+    fd = torch.from_numpy(f).to("cuda:0", plan.dtype)
+    u = plan.solve(fd)
+    ref = flgf.FLGF(blocks, n, p, 0).solve(fd.cpu().numpy().astype(np.float64))
+    assert rel(u.cpu().numpy().astype(np.float64), ref) <= (fp64_tol(p) if prec == "f64" else FP32_BAR)
+    for fw, fc in ((1, 1), (16, 8), (4, 4), (2, 2), (8, 0)):
+        plan.set_tuning(far_waves=fw, far_children=fc)
+        assert torch.equal(plan.solve(fd), u), (fw, fc)
+    plan.close()
