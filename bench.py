@@ -800,7 +800,7 @@ def main():
                                "roofline": _roofline(m32["prof"], FP32_PEAK_TFLOPS, cfg["name"], "f32"),
                                "note": "FP32 transforms and products; FP64 kernel tables and spectrum "
                                        "generation, FP64 arithmetic in the level >= 1 inverse transforms "
-                                       "(float-float node values), FP64 final add"}, err)
+                                       "and FP64 node values through Interp, FP64 final add"}, err)
         result["fp32"]["solve_hbm"] = _solve_hbm(m32["prof"], result["fp32"]["ms_per_step"], copy_gbps,
                                                  cfg["name"], "f32")
         breakdown["fp32"] = _breakdown(m32["prof"])

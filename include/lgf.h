@@ -101,7 +101,7 @@ typedef struct {
  *               list holds every non-adjacent interval.
  *   prec      : LGF_F64, or LGF_F32 (FP32 forward transforms, products and level-0
  *               inverse; level >= 1 inverse transforms in FP64 arithmetic with
- *               float-float node values through Interp; FP64 kernel tables and spectrum
+ *               FP64 node values through Interp; FP64 kernel tables and spectrum
  *               generation, FP64 final add of far and near fields)
  *   hip_stream: stream for the set-up work (hipStream_t or NULL)
  *   out       : receives the plan on success

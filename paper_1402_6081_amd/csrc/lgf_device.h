@@ -76,62 +76,6 @@ __device__ __forceinline__ cplx<T> sym_coef(const cplx<T>* __restrict__ khat, ui
     return k;
 }
 
-// ---------------------------------------------------------------- float-float numbers
-// An unevaluated sum hi + lo of two floats (|lo| <= ulp(hi)/2), with error-free
-// transformations (Knuth TwoSum, FMA-based TwoProduct).  Used by the FP32 path to carry
-// the far-field level contributions with compensation through the interpolation down the
-// tree, where the Lebesgue constant of equispaced interpolation would otherwise amplify
-// FP32 rounding of the node values.
-// Every function here turns floating-point contraction off: HIP device code contracts
-// a * b + c into one FMA by default, and fusing the rounded product p = a.hi * b.hi into
-// the following sum p + e would break the error-free transformations (the error term is
-// computed from the rounded p), leaving products with FP32 accuracy only.
-struct alignas(8) ff32 {
-    float hi, lo;
-    ff32() = default;
-    __host__ __device__ constexpr ff32(float h, float l) : hi(h), lo(l) {}
-    __host__ __device__ ff32(int v) : hi((float)v), lo(0.f) {}
-    __host__ __device__ ff32(float v) : hi(v), lo(0.f) {}
-    __host__ __device__ ff32(double d) : hi((float)d), lo((float)(d - (double)(float)d)) {}
-};
-
-__device__ __forceinline__ ff32 ff_two_sum(float a, float b) {
-#pragma clang fp contract(off)
-    const float s = a + b;
-    const float bb = s - a;
-    const float e = (a - (s - bb)) + (b - bb);
-    return ff32(s, e);
-}
-__device__ __forceinline__ ff32 ff_fast_two_sum(float a, float b) {
-#pragma clang fp contract(off)
-    const float s = a + b;
-    return ff32(s, b - (s - a));
-}
-__device__ __forceinline__ ff32 operator+(ff32 a, ff32 b) {
-#pragma clang fp contract(off)
-    ff32 s = ff_two_sum(a.hi, b.hi);
-    s.lo += a.lo + b.lo;
-    return ff_fast_two_sum(s.hi, s.lo);
-}
-__device__ __forceinline__ ff32 operator-(ff32 a) { return ff32(-a.hi, -a.lo); }
-__device__ __forceinline__ ff32 operator-(ff32 a, ff32 b) { return a + (-b); }
-__device__ __forceinline__ ff32 operator*(ff32 a, ff32 b) {
-#pragma clang fp contract(off)
-    const float p = a.hi * b.hi;
-    float e = __builtin_fmaf(a.hi, b.hi, -p);
-    e = __builtin_fmaf(a.hi, b.lo, e);
-    e = __builtin_fmaf(a.lo, b.hi, e);
-    return ff_fast_two_sum(p, e);
-}
-__device__ __forceinline__ ff32& operator+=(ff32& a, ff32 b) {
-    a = a + b;
-    return a;
-}
-
-__device__ __forceinline__ double to_double(double v) { return v; }
-__device__ __forceinline__ double to_double(float v) { return (double)v; }
-__device__ __forceinline__ double to_double(ff32 v) { return (double)v.hi + (double)v.lo; }
-
 // ---------------------------------------------------------------- compile-time roots
 // cos / sin of 2*pi*k/M, reduced exactly to [0, pi/4] by integer octant arithmetic and
 // then summed as Taylor series (|error| < 1e-17 on that range).
@@ -215,16 +159,12 @@ __device__ __forceinline__ void cmul_const(T ar, T ai, double wr, double wi, T& 
         orr = -ai; oi = ar;
     } else if (wr == 0.0 && wi == -1.0) {
         orr = ai; oi = -ar;
-    } else if constexpr (std::is_floating_point<T>::value) {
+    } else {
         // fused explicitly, so the rounding does not depend on how the compiler unrolls or
         // schedules a kernel variant (every variant of a transform gives the same bits)
         const T r = (T)wr, i = (T)wi;
         orr = fma(ar, r, -(ai * i));
         oi = fma(ar, i, ai * r);
-    } else {
-        const T r = (T)wr, i = (T)wi;
-        orr = ar * r - ai * i;
-        oi = ar * i + ai * r;
     }
 }
 
@@ -269,13 +209,10 @@ constexpr int smallest_factor(int v) {
     return v;
 }
 
-// acc + a * c for a compile-time constant c, fused where T is a machine float
+// acc + a * c for a compile-time constant c, fused
 template <typename T>
 __device__ __forceinline__ T madd_const(T a, double c, T acc) {
-    if constexpr (std::is_floating_point<T>::value)
-        return fma(a, (T)c, acc);
-    else
-        return acc + a * T(c);
+    return fma(a, (T)c, acc);
 }
 
 // In-place DFT of odd prime length N in registers, by conjugate input pairs: with
@@ -478,15 +415,9 @@ __device__ __forceinline__ void stage_roots(double2* tw, int tid, int nthreads) 
 // forms give a product of 0 or a copy in each term)
 template <typename T>
 __device__ __forceinline__ void cmul_rt(T ar, T ai, double wr, double wi, T& orr, T& oi) {
-    if constexpr (std::is_floating_point<T>::value) {
-        const T r = (T)wr, i = (T)wi;
-        orr = fma(ar, r, -(ai * i));
-        oi = fma(ar, i, ai * r);
-    } else {
-        const T r = (T)wr, i = (T)wi;
-        orr = ar * r - ai * i;
-        oi = ar * i + ai * r;
-    }
+    const T r = (T)wr, i = (T)wi;
+    orr = fma(ar, r, -(ai * i));
+    oi = fma(ar, i, ai * r);
 }
 
 // Direct DFT handing each output to `put` as soon as it is formed, outputs in a runtime

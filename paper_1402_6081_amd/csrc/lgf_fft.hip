@@ -153,9 +153,10 @@ __global__ void __launch_bounds__(NT) k_pad_fft(const FwdSegs<T> segs, int64_t t
 
 // Inverse: spectrum elements of type Tin, arithmetic in A, real output of type Tout.
 // (FP64 path: all double.  FP32 path: float at level 0 and at level 1 of the lattice
-// scheme; at the other levels >= 1 the float spectra are inverted in double arithmetic and
-// written as float-float node values (each double rounded to a hi + lo float pair).  The
-// float-float arithmetic instantiation A = ff32 is kept for tiles up to 10 nodes.)
+// scheme; at the other levels >= 1 the float spectra are inverted in double arithmetic to
+// double node values: the Lebesgue constant of equispaced interpolation would amplify FP32
+// rounding of the node values above 1e-6, and gfx950 issues FP64 FMAs at the non-packed FP32
+// rate.)
 // One launch may invert several levels' spectra (segments of the grid with their own
 // input, output and item count; one workgroup per item).
 template <typename Tin, typename Tout>
@@ -473,7 +474,7 @@ static hipError_t launch_inv_segs(const InvSegs<Tin, Tout>& segs, int64_t nblock
     // FP64 16^3 tiles default to 512 threads: one workgroup fills a CU's LDS, and 8 waves
     // keep twice the column loads in flight (256^3: 331 -> 299 us; 128^3: 51 -> 47 us)
     if (nt == 0 && m == 16 && sizeof(A) == 8) nt = 512;
-    if constexpr ((m == 8 || m == 16) && !std::is_same<A, ff32>::value) {
+    if constexpr (m == 8 || m == 16) {
         if (nt == 512) return inv_mnt<Tin, A, Tout, m, 512>(segs, nblocks, out_map, opitch, s);
         if (nt == 128) return inv_mnt<Tin, A, Tout, m, 128>(segs, nblocks, out_map, opitch, s);
     }
@@ -530,20 +531,9 @@ hipError_t launch_ifft_trunc(int m, const cplx<Tin>* in, Tout* out, int64_t nbat
         case 8: return launch_inv_m<Tin, A, Tout, 8>(in, out, nbatch, out_map, opitch, s, nt);
         case 9: return launch_inv_m<Tin, A, Tout, 9>(in, out, nbatch, out_map, opitch, s);
         case 10: return launch_inv_m<Tin, A, Tout, 10>(in, out, nbatch, out_map, opitch, s);
-        // the large tiles (level 0 of n = 12 and 16, levels >= 1 of the 13-node scheme) are
-        // not inverted in float-float arithmetic
-        case 12:
-            if constexpr (!std::is_same<A, ff32>::value)
-                return launch_inv_m<Tin, A, Tout, 12>(in, out, nbatch, out_map, opitch, s);
-            return hipErrorInvalidValue;
-        case 13:
-            if constexpr (!std::is_same<A, ff32>::value)
-                return launch_inv_m<Tin, A, Tout, 13>(in, out, nbatch, out_map, opitch, s);
-            return hipErrorInvalidValue;
-        case 16:
-            if constexpr (!std::is_same<A, ff32>::value)
-                return launch_inv_m<Tin, A, Tout, 16>(in, out, nbatch, out_map, opitch, s, nt);
-            return hipErrorInvalidValue;
+        case 12: return launch_inv_m<Tin, A, Tout, 12>(in, out, nbatch, out_map, opitch, s);
+        case 13: return launch_inv_m<Tin, A, Tout, 13>(in, out, nbatch, out_map, opitch, s);
+        case 16: return launch_inv_m<Tin, A, Tout, 16>(in, out, nbatch, out_map, opitch, s, nt);
         default: return hipErrorInvalidValue;
     }
 }
@@ -611,8 +601,7 @@ hipError_t launch_ifft_trunc_levels(int m, const InvLevel<Tin, Tout>* lv, int nl
 
 template hipError_t launch_ifft_trunc_levels<double, double, double>(int, const InvLevel<double, double>*, int,
                                                                       hipStream_t);
-template hipError_t launch_ifft_trunc_levels<float, ff32, ff32>(int, const InvLevel<float, ff32>*, int, hipStream_t);
-template hipError_t launch_ifft_trunc_levels<float, double, ff32>(int, const InvLevel<float, ff32>*, int,
+template hipError_t launch_ifft_trunc_levels<float, double, double>(int, const InvLevel<float, double>*, int,
                                                                    hipStream_t);
 
 template hipError_t launch_pad_fft<double>(int, const double*, cplx<double>*, int64_t, hipStream_t, int, int64_t,
@@ -623,11 +612,9 @@ template hipError_t launch_ifft_trunc<double, double, double>(int, const cplx<do
                                                                hipStream_t, int, const int32_t*, void*, int);
 template hipError_t launch_ifft_trunc<float, float, float>(int, const cplx<float>*, float*, int64_t, hipStream_t,
                                                              int, const int32_t*, void*, int);
-template hipError_t launch_ifft_trunc<float, ff32, ff32>(int, const cplx<float>*, ff32*, int64_t, hipStream_t, int,
-                                                         const int32_t*, void*, int);
-template hipError_t launch_ifft_trunc<float, float, ff32>(int, const cplx<float>*, ff32*, int64_t, hipStream_t, int,
+template hipError_t launch_ifft_trunc<float, float, double>(int, const cplx<float>*, double*, int64_t, hipStream_t, int,
                                                           const int32_t*, void*, int);
-template hipError_t launch_ifft_trunc<float, double, ff32>(int, const cplx<float>*, ff32*, int64_t, hipStream_t, int,
+template hipError_t launch_ifft_trunc<float, double, double>(int, const cplx<float>*, double*, int64_t, hipStream_t, int,
                                                            const int32_t*, void*, int);
 
 }  // namespace lgfdev

@@ -167,11 +167,7 @@ struct InvLevel {
 template <typename Tin, typename A, typename Tout>
 hipError_t launch_ifft_trunc_levels(int m, const InvLevel<Tin, Tout>* lv, int nlev, hipStream_t s);
 
-// Far-field node values of the down pass: double on the FP64 path, float-float on the
-// FP32 path (8 bytes either way).
-template <typename T> struct FarAcc;
-template <> struct FarAcc<double> { using type = double; };
-template <> struct FarAcc<float> { using type = ff32; };
+// The far-field node values of the down pass (utilde) are double on both paths.
 
 // Source spectra (fhat) arrays hold nitems + 1 items per frequency chunk; the last is a zero
 // sentinel that inactive neighbours point to.  Field spectra (uhat) hold nitems items.
@@ -255,14 +251,13 @@ hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, 
 template <typename T>
 hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStream_t s);
 // Interp parent -> its children, accumulate: io[child8[J][c]] += (C_c^T x C_c^T x C_c^T) par[J]
-template <typename U>
-hipError_t launch_interp_down(const U* par, const int32_t* child8, const double* C01, U* io, int64_t nparent,
-                              int p, hipStream_t s);
+hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
+                              int64_t nparent, int p, hipStream_t s);
 // Final: u[b] = vnear[b] + (A^T x A^T x A^T) ut[q(b)], accumulated in FP64 (u may alias
 // vnear); q(b) = l1map[b] (the level-1 interval of evaluation block b), or b when l1map is
 // NULL; vnear[b] is taken as 0 (and not read) where near_flag[b] == 0 (NULL: every block)
-template <typename T, typename U>
-hipError_t launch_final(const T* vnear, const U* ut, const double* A, T* u, int64_t nb, int n, int p,
+template <typename T>
+hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p,
                         hipStream_t s, const int32_t* l1map = nullptr, const int32_t* near_flag = nullptr);
 
 // ------------------------------------------------------------------ kernel spectra

@@ -127,20 +127,19 @@ __global__ void __launch_bounds__(NT)
 }
 
 // ------------------------------------------------------------------ parent -> children
-// U is the down-pass value type (double or float-float).
-template <typename U, int P>
+template <int P>
 __global__ void __launch_bounds__(kDownThreads)
-    k_interp_down(const U* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
-                  U* __restrict__ io) {
+    k_interp_down(const double* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
+                  double* __restrict__ io) {
     constexpr int P3 = P * P * P;
-    __shared__ U X[P3], t1[2 * P3], t2[4 * P3];
-    __shared__ U Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
+    __shared__ double X[P3], t1[2 * P3], t2[4 * P3];
+    __shared__ double Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
     __shared__ int32_t ch[8];
     const int tid = threadIdx.x;
     const int64_t J = blockIdx.x;
     for (int i = tid; i < 2 * P * P; i += kDownThreads) {
         const int c = i / (P * P), r = i % (P * P), k = r / P, m = r % P;
-        Ct[i] = U(C01[c * P * P + m * P + k]);
+        Ct[i] = C01[c * P * P + m * P + k];
     }
     if (tid < 8) ch[tid] = child8[J * 8 + tid];
     for (int i = tid; i < P3; i += kDownThreads) X[i] = par[J * P3 + i];
@@ -148,9 +147,9 @@ __global__ void __launch_bounds__(kDownThreads)
     // x for both cx: t1[cx][a][b][x'] = sum_d Ct_cx[x'][d] X[a][b][d]
     for (int i = tid; i < 2 * P3; i += kDownThreads) {
         const int xo = i % P, ab = (i / P) % (P * P), cx = i / P3;
-        const U* m = Ct + cx * P * P + xo * P;
-        const U* row = X + ab * P;
-        U s = U(0);
+        const double* m = Ct + cx * P * P + xo * P;
+        const double* row = X + ab * P;
+        double s = 0.0;
 #pragma unroll
         for (int d = 0; d < P; ++d) s += m[d] * row[d];
         t1[i] = s;
@@ -159,9 +158,9 @@ __global__ void __launch_bounds__(kDownThreads)
     // y for both cy: t2[cy][cx][a][y'][x'] = sum_b Ct_cy[y'][b] t1[cx][a][b][x']
     for (int i = tid; i < 4 * P3; i += kDownThreads) {
         const int xo = i % P, yo = (i / P) % P, a = (i / (P * P)) % P, cx = (i / P3) & 1, cy = i / (2 * P3);
-        const U* m = Ct + cy * P * P + yo * P;
-        const U* src = t1 + cx * P3 + a * P * P + xo;
-        U s = U(0);
+        const double* m = Ct + cy * P * P + yo * P;
+        const double* src = t1 + cx * P3 + a * P * P + xo;
+        double s = 0.0;
 #pragma unroll
         for (int bb = 0; bb < P; ++bb) s += m[bb] * src[bb * P];
         t2[i] = s;
@@ -174,12 +173,12 @@ __global__ void __launch_bounds__(kDownThreads)
         if (q < 0) continue;
         const int yx = r % (P * P), zo = r / (P * P);
         const int cx = c & 1, cy = (c >> 1) & 1, cz = (c >> 2) & 1;
-        const U* m = Ct + cz * P * P + zo * P;
-        const U* src = t2 + (cy * 2 + cx) * P3 + yx;
-        U s = U(0);
+        const double* m = Ct + cz * P * P + zo * P;
+        const double* src = t2 + (cy * 2 + cx) * P3 + yx;
+        double s = 0.0;
 #pragma unroll
         for (int a = 0; a < P; ++a) s += m[a] * src[a * P * P];
-        U* dst = io + (int64_t)q * P3 + r;
+        double* dst = io + (int64_t)q * P3 + r;
         *dst = *dst + s;
     }
 }
@@ -251,13 +250,13 @@ __global__ void __launch_bounds__(kInterpThreads)
     out[g] = acc;
 }
 
-template <typename U, int P>
+template <int P>
 __global__ void __launch_bounds__(kDownThreads)
-    k_interp_down_one(const U* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
-                      U* __restrict__ io) {
+    k_interp_down_one(const double* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
+                      double* __restrict__ io) {
     constexpr int P3 = P * P * P;
-    __shared__ U X[P3], t1[P3], t2[P3];
-    __shared__ U Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
+    __shared__ double X[P3], t1[P3], t2[P3];
+    __shared__ double Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
     const int tid = threadIdx.x;
     const int64_t J = blockIdx.x >> 3;
     const int c = blockIdx.x & 7;
@@ -266,15 +265,15 @@ __global__ void __launch_bounds__(kDownThreads)
     const int cx = c & 1, cy = (c >> 1) & 1, cz = (c >> 2) & 1;
     for (int i = tid; i < 2 * P * P; i += kDownThreads) {
         const int cc = i / (P * P), r = i % (P * P), k = r / P, m = r % P;
-        Ct[i] = U(C01[cc * P * P + m * P + k]);
+        Ct[i] = C01[cc * P * P + m * P + k];
     }
     for (int i = tid; i < P3; i += kDownThreads) X[i] = par[J * P3 + i];
     __syncthreads();
     for (int i = tid; i < P3; i += kDownThreads) {  // x: t1[a][b][x']
         const int xo = i % P, ab = i / P;
-        const U* m = Ct + cx * P * P + xo * P;
-        const U* row = X + ab * P;
-        U sum = U(0);
+        const double* m = Ct + cx * P * P + xo * P;
+        const double* row = X + ab * P;
+        double sum = 0.0;
 #pragma unroll
         for (int d = 0; d < P; ++d) sum += m[d] * row[d];
         t1[i] = sum;
@@ -282,9 +281,9 @@ __global__ void __launch_bounds__(kDownThreads)
     __syncthreads();
     for (int i = tid; i < P3; i += kDownThreads) {  // y: t2[a][y'][x']
         const int xo = i % P, yo = (i / P) % P, a = i / (P * P);
-        const U* m = Ct + cy * P * P + yo * P;
-        const U* src = t1 + a * P * P + xo;
-        U sum = U(0);
+        const double* m = Ct + cy * P * P + yo * P;
+        const double* src = t1 + a * P * P + xo;
+        double sum = 0.0;
 #pragma unroll
         for (int bb = 0; bb < P; ++bb) sum += m[bb] * src[bb * P];
         t2[i] = sum;
@@ -292,11 +291,11 @@ __global__ void __launch_bounds__(kDownThreads)
     __syncthreads();
     for (int i = tid; i < P3; i += kDownThreads) {  // z, accumulated into the child
         const int yx = i % (P * P), zo = i / (P * P);
-        const U* m = Ct + cz * P * P + zo * P;
-        U sum = U(0);
+        const double* m = Ct + cz * P * P + zo * P;
+        double sum = 0.0;
 #pragma unroll
         for (int a = 0; a < P; ++a) sum += m[a] * t2[a * P * P + yx];
-        U* dst = io + (int64_t)q * P3 + i;
+        double* dst = io + (int64_t)q * P3 + i;
         *dst = *dst + sum;
     }
 }
@@ -315,9 +314,9 @@ __global__ void k_pad_copy(const T* __restrict__ f, T* __restrict__ out, int64_t
 }
 
 // ------------------------------------------------------------------ level 1 -> block, FP64 add-back
-template <typename T, typename U, int N, int P>
+template <typename T, int N, int P>
 __global__ void __launch_bounds__(kBlockThreads)
-    k_final(const T* vnear, const U* __restrict__ ut, const double* __restrict__ A, T* u,
+    k_final(const T* vnear, const double* __restrict__ ut, const double* __restrict__ A, T* u,
             const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
     constexpr int N3 = N * N * N, P3 = P * P * P, PR = P + 1;
     // rows read at several indices at once by a wave are padded to P + 1 values (LDS banks)
@@ -330,7 +329,7 @@ __global__ void __launch_bounds__(kBlockThreads)
         At[jj * PR + k] = A[k * N + jj];
     }
     const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
-    for (int i = tid; i < P3; i += kBlockThreads) X[(i / P) * PR + i % P] = to_double(ut[q * P3 + i]);
+    for (int i = tid; i < P3; i += kBlockThreads) X[(i / P) * PR + i % P] = ut[q * P3 + i];
     __syncthreads();
     for (int i = tid; i < P * P * N; i += kBlockThreads) {  // x: t1[a][c][x]
         const int x = i % N, ac = i / N;
@@ -407,13 +406,13 @@ struct RegBlockRun {
     };
 };
 
-template <typename T, typename U>
+template <typename T>
 struct FinalRun {
     template <int N, int P>
     struct K {
-        static hipError_t run(const T* vnear, const U* ut, const double* A, T* u, int64_t nb, const int32_t* l1map,
+        static hipError_t run(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, const int32_t* l1map,
                               const int32_t* near_flag, hipStream_t s) {
-            return lgf_launch(k_final<T, U, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, vnear, ut, A, u,
+            return lgf_launch(k_final<T, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, vnear, ut, A, u,
                               l1map, near_flag);
         }
     };
@@ -465,36 +464,35 @@ hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, 
     }
 }
 
-template <typename U, int P>
-static hipError_t interp_down_p(const U* par, const int32_t* child8, const double* C01, U* io, int64_t np,
+template <int P>
+static hipError_t interp_down_p(const double* par, const int32_t* child8, const double* C01, double* io, int64_t np,
                                 hipStream_t s) {
     // levels with few parents: one workgroup per (parent, child), eight times the
     // workgroups (the same sums in the same order, so the same bits as one per parent)
     if (np <= 256)
-        return lgf_launch(k_interp_down_one<U, P>, dim3((unsigned)(np * 8)), dim3(kDownThreads), 0, s, par, child8,
+        return lgf_launch(k_interp_down_one<P>, dim3((unsigned)(np * 8)), dim3(kDownThreads), 0, s, par, child8,
                           C01, io);
-    return lgf_launch(k_interp_down<U, P>, dim3((unsigned)np), dim3(kDownThreads), 0, s, par, child8, C01, io);
+    return lgf_launch(k_interp_down<P>, dim3((unsigned)np), dim3(kDownThreads), 0, s, par, child8, C01, io);
 }
 
-template <typename U>
-hipError_t launch_interp_down(const U* par, const int32_t* child8, const double* C01, U* io, int64_t nparent,
-                              int p, hipStream_t s) {
+hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
+                              int64_t nparent, int p, hipStream_t s) {
     if (nparent <= 0) return hipSuccess;
     switch (p) {
-        case 2: return interp_down_p<U, 2>(par, child8, C01, io, nparent, s);
-        case 3: return interp_down_p<U, 3>(par, child8, C01, io, nparent, s);
-        case 4: return interp_down_p<U, 4>(par, child8, C01, io, nparent, s);
-        case 5: return interp_down_p<U, 5>(par, child8, C01, io, nparent, s);
-        case 6: return interp_down_p<U, 6>(par, child8, C01, io, nparent, s);
-        case 7: return interp_down_p<U, 7>(par, child8, C01, io, nparent, s);
-        case 8: return interp_down_p<U, 8>(par, child8, C01, io, nparent, s);
-        case 9: return interp_down_p<U, 9>(par, child8, C01, io, nparent, s);
-        case 10: return interp_down_p<U, 10>(par, child8, C01, io, nparent, s);
+        case 2: return interp_down_p<2>(par, child8, C01, io, nparent, s);
+        case 3: return interp_down_p<3>(par, child8, C01, io, nparent, s);
+        case 4: return interp_down_p<4>(par, child8, C01, io, nparent, s);
+        case 5: return interp_down_p<5>(par, child8, C01, io, nparent, s);
+        case 6: return interp_down_p<6>(par, child8, C01, io, nparent, s);
+        case 7: return interp_down_p<7>(par, child8, C01, io, nparent, s);
+        case 8: return interp_down_p<8>(par, child8, C01, io, nparent, s);
+        case 9: return interp_down_p<9>(par, child8, C01, io, nparent, s);
+        case 10: return interp_down_p<10>(par, child8, C01, io, nparent, s);
         case 13:
-            return lgf_launch(k_interp_down_one<U, 13>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
+            return lgf_launch(k_interp_down_one<13>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
                               child8, C01, io);
         case 17:
-            return lgf_launch(k_interp_down_one<U, 17>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
+            return lgf_launch(k_interp_down_one<17>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
                               child8, C01, io);
         default: return hipErrorInvalidValue;
     }
@@ -507,11 +505,11 @@ hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStre
     return lgf_launch(k_pad_copy<T>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, f, out, nb, n, p);
 }
 
-template <typename T, typename U>
-hipError_t launch_final(const T* vnear, const U* ut, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
+template <typename T>
+hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
                         const int32_t* l1map, const int32_t* near_flag) {
     if (nb <= 0) return hipSuccess;
-    return dispatch_np<FinalRun<T, U>::template K>(n, p, vnear, ut, A, u, nb, l1map, near_flag, s);
+    return dispatch_np<FinalRun<T>::template K>(n, p, vnear, ut, A, u, nb, l1map, near_flag, s);
 }
 
 template hipError_t launch_reg_block<double>(const double*, const double*, double*, int64_t, int, int, hipStream_t);
@@ -522,13 +520,9 @@ template hipError_t launch_reg_up<double>(const double*, const int32_t*, const d
                                          hipStream_t, void*);
 template hipError_t launch_reg_up<float>(const float*, const int32_t*, const double*, float*, int64_t, int,
                                          hipStream_t, void*);
-template hipError_t launch_interp_down<double>(const double*, const int32_t*, const double*, double*, int64_t, int,
-                                               hipStream_t);
-template hipError_t launch_interp_down<ff32>(const ff32*, const int32_t*, const double*, ff32*, int64_t, int,
-                                             hipStream_t);
-template hipError_t launch_final<double, double>(const double*, const double*, const double*, double*, int64_t, int,
+template hipError_t launch_final<double>(const double*, const double*, const double*, double*, int64_t, int,
                                                  int, hipStream_t, const int32_t*, const int32_t*);
-template hipError_t launch_final<float, ff32>(const float*, const ff32*, const double*, float*, int64_t, int, int,
+template hipError_t launch_final<float>(const float*, const double*, const double*, float*, int64_t, int, int,
                                               hipStream_t, const int32_t*, const int32_t*);
 
 }  // namespace lgfdev

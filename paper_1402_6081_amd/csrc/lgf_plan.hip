@@ -240,7 +240,7 @@ inline double fft_flops(int M) {  // Table 1: 2 (8 N_b) log2(8 N_b) for a padded
 template <typename T>
 hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     using C = cplx<T>;
-    using U = typename FarAcc<T>::type;
+    using U = double;  // far-field node values
     const int n = pl->n, p = pl->p;
     const TuneConfig& tc = pl->tune;
     hipError_t e;
@@ -352,7 +352,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     // Interp from level l + 1 down to level l, accumulated (Step 3)
     auto interp = [&](int l, hipStream_t st) -> hipError_t {
         LGF_STEP(st,
-                 (launch_interp_down<U>((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_C01,
+                 (launch_interp_down((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_C01,
                                         (U*)pl->lv[l].d_util, pl->lv[l + 1].nint, p, st)),
                  "interp_l" + std::to_string(l + 1) + "_l" + std::to_string(l), (lvN(l + 1) + 2.0 * lvN(l)) * p3 * us,
                  lvN(l) * 2.0 * 3.0 * p3 * p);
@@ -517,7 +517,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     if (far) {
         if (overlap && (e = rec_stream_wait(s, pl->ev_join)) != hipSuccess) return e;
         LGF_STEP(s,
-                 (launch_final<T, U>(u, (const U*)pl->lv[1].d_util, pl->d_A, u, pl->neval, n, p, s, pl->d_eval_l1,
+                 (launch_final<T>(u, (const U*)pl->lv[1].d_util, pl->d_A, u, pl->neval, n, p, s, pl->d_eval_l1,
                                      pl->d_near_flag)),
                  "final_l1_l0", (ne + nt0) * n3 * es + ne * p3 * us, ne * 2.0 * (p3 * n + p * p * n * n + p * n3));
     }
@@ -610,7 +610,7 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
                 C01[c * p * p + mm * p + k] = (double)lagrange(p, mm, (long double)(c * (p - 1) + k) / 2.0L);
     // ---- device memory
     const int64_t esz = prec == LGF_F64 ? sizeof(double) : sizeof(float);
-    const int64_t usz = 8;  // far-field down-pass values: double or float-float
+    const int64_t usz = 8;  // far-field down-pass values: double
     const int64_t S0 = spec_padded(pl->spectra0->S);
     const int64_t S1 = spec_padded(2 * p * 2 * p * (p + 1));
     const int64_t p3 = (int64_t)p * p * p;
