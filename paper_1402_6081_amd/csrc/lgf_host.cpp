@@ -335,6 +335,11 @@ void order_groups(HostPlan& H) {
 void order_parents(HostPlan& H) {
     for (int l = 2; l <= H.L; ++l) {
         HostLevel& Lv = H.lv[l];
+        if (l <= H.Ltop) {
+            H.lv[l - 1].par.assign(H.lv[l - 1].nint, -1);
+            for (size_t k = 0; k < Lv.child8.size(); ++k)
+                if (Lv.child8[k] >= 0) H.lv[l - 1].par[Lv.child8[k]] = (int32_t)k;
+        }
         const int32_t sentinel = (int32_t)(l == 2 && H.lat1 ? H.nsrc : H.lv[l - 1].nint);
         const int64_t np = Lv.nint;
         std::vector<uint32_t> mask(np, 0);
@@ -392,6 +397,8 @@ lgf_status check_host(const HostPlan& H) {
              (int64_t)Lv.m2l_ord.size() == Lv.nint && (int64_t)Lv.m2l_mask.size() == Lv.nint &&
              (Lv.src216.empty() || (int64_t)Lv.src216.size() == 216 * Lv.nint);
     }
+    for (int l = 1; ok && l < H.Ltop; ++l)  // parents (8 J + c) and the par list of every level below the top
+        ok = (int64_t)H.lv[l].par.size() == H.lv[l].nint && within(H.lv[l].par, -1, 8 * H.lv[l + 1].nint - 1);
     for (int l = 1; ok && l <= H.L && l < (int)H.lv.size(); ++l) {
         const HostLevel& Lv = H.lv[l];
         const int64_t ns = l == 1 && H.lat1 ? H.nsrc : Lv.nint;
@@ -487,7 +494,7 @@ int64_t workspace_need(const HostPlan& H, lgf_precision prec) {
                    (int64_t)(H.eval_l1.size() + H.near_out.size() + H.near_flag.size()) * 4;
     for (int l = 1; l <= H.Ltop; ++l) {
         const HostLevel& h = H.lv[l];
-        need += h.nint * p3 * (esz + usz);
+        need += h.nint * p3 * ((needs_ftil(H, l) ? esz : 0) + (needs_util(H, l) ? usz : 0)) + (int64_t)h.par.size() * 4;
         if (h.pairs() > 0) {
             if (l == 1 && H.lat1)
                 need += h.nint * S0 * 2 * esz;  // products only: the sources are the level-0 spectra

@@ -73,6 +73,7 @@ struct HostLevel {
     std::vector<int32_t> m2l_ord;
     std::vector<uint32_t> m2l_mask;
     bool m2l_spread = false;
+    std::vector<int32_t> par;  // levels below the top: 8 J + c of child c of parent J (-1: no parent)
     int64_t sib_pairs = 0;        // interaction-list entries of targets served through parents
     // top level of a truncated tree: explicit lists over a target subset
     std::vector<int32_t> csr_tgt, csr_ptr{0}, csr_src;
@@ -119,7 +120,7 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
 // columns following each other; fills g0_runs and g0_flags.
 void order_groups(HostPlan& H);
 
-// Fills m2l_ord, m2l_mask and m2l_spread of the levels >= 2.
+// Fills par of the levels below the top, and m2l_ord, m2l_mask and m2l_spread of the levels >= 2.
 void order_parents(HostPlan& H);
 
 // Every list index within its array's range; LGF_ERR_LAYOUT otherwise.
@@ -128,6 +129,12 @@ lgf_status check_host(const HostPlan& H);
 // Union of independent layouts: every index is offset by the items of the earlier
 // layouts; sentinels map to the union's sentinel; lists never cross layouts.
 HostPlan concat(const std::vector<HostPlan>& parts);
+
+// Does level l <= Ltop keep its node values in HBM on the way up (read by Reg to the next level,
+// or by the lattice scheme's own transforms) / on the way down (read by Interp to the level below,
+// or by its final pass)?
+inline bool needs_ftil(const HostPlan& H, int l) { return H.lat1 || l < H.Ltop; }
+inline bool needs_util(const HostPlan& H, int l) { return H.lat1 || l >= 2; }
 
 // HBM intermediate of the two-phase transforms and of the 17-node Reg up.
 int64_t scratch_need(const HostPlan& H);

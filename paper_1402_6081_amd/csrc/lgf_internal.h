@@ -141,31 +141,15 @@ template <typename T>
 // complex values of 16 bytes (two_phase_scratch_bytes); unused otherwise
 hipError_t launch_pad_fft(int m, const T* in, cplx<T>* out, int64_t nbatch, hipStream_t s, int nt = 0,
                           int64_t nout = 0, void* scratch = nullptr);
-// out_map: output tile of each transformed item (NULL = the item's own index); opitch:
-// edge of the output tiles (0 = m; larger pads the m^3 results with zero planes, m = 16)
-template <typename Tin, typename A, typename Tout>
-hipError_t launch_ifft_trunc(int m, const cplx<Tin>* in, Tout* out, int64_t nbatch, hipStream_t s, int nt = 0,
-                             const int32_t* out_map = nullptr, void* scratch = nullptr, int opitch = 0);
-// Forward transforms of several levels in one launch (tiles of m <= 10; nout as above,
-// 0 = nbatch + 1; at most kMaxFarSegs levels, each with nbatch > 0).
+// Level-0 inverse.  out_map: output tile of each transformed item (NULL = the item's own index)
 template <typename T>
-struct FwdLevel {
-    const T* in;
-    cplx<T>* out;
-    int64_t nbatch, nout;
-};
+hipError_t launch_ifft0(int n, const cplx<T>* in, T* out, int64_t nbatch, hipStream_t s, int nt = 0,
+                        const int32_t* out_map = nullptr);
+// Inverse of a level of the lattice scheme to node values: m = n at level 1 (opitch = p: the n^3
+// results in tiles of p nodes, zeros beyond them), m = p above (scratch as for the forward).
 template <typename T>
-hipError_t launch_pad_fft_levels(int m, const FwdLevel<T>* lv, int nlev, hipStream_t s);
-// The same for several levels' spectra in one launch (tiles of m <= 10, outputs in item
-// order, at most kMaxFarSegs levels, each with nbatch > 0).
-template <typename Tin, typename Tout>
-struct InvLevel {
-    const cplx<Tin>* in;
-    Tout* out;
-    int64_t nbatch;
-};
-template <typename Tin, typename A, typename Tout>
-hipError_t launch_ifft_trunc_levels(int m, const InvLevel<Tin, Tout>* lv, int nlev, hipStream_t s);
+hipError_t launch_ifft_lattice(int m, const cplx<T>* in, double* out, int64_t nbatch, hipStream_t s, void* scratch,
+                               int opitch);
 
 // The far-field node values of the down pass (utilde) are double on both paths.
 
@@ -239,23 +223,43 @@ struct TuneConfig {
     int overlap = 0;       // far-field chain on a second stream: 1 = yes, 2 = no, 0 = default (yes)
 };
 
-// Reg block -> level-1 interval: out[b] = (A x A x A) f[b], A is p x n (row-major)
+// Reg block -> level-1 interval and its forward transform (p <= 10): ftil[b] = (A x A x A) f[b],
+// A is p x n (row-major), and its spectrum into item b of fhat (nout items); either output may
+// be NULL
 template <typename T>
-hipError_t launch_reg_block(const T* f, const double* A, T* out, int64_t nb, int n, int p, hipStream_t s);
-// Reg children -> parent: out[J] = sum_c (C_cz x C_cy x C_cx) in[child_c(J)]
+hipError_t launch_reg_fft(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
+                          hipStream_t s);
+// The same children -> parent: out[J] = sum_c (C_cz x C_cy x C_cx) in[child_c(J)]
 template <typename T>
-// scratch: p = 17 only, nparent * 8 * p^3 values of T (the children's partial sums)
+hipError_t launch_regup_fft(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat, int64_t np,
+                            int64_t nout, int p, hipStream_t s);
+// Inverse transform of a level's spectra (NULL: zeros) plus Interp from its parents (p <= 10):
+// out[i] = inverse of item i + (C_c^T x C_c^T x C_c^T) up[J], par[i] = 8 J + c (-1: no parent);
+// up = NULL: no parents
+template <typename T>
+hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+                             double* out, int64_t nint, int p, hipStream_t s);
+// The same at level 1, and on to the blocks: u[b] = vnear[b] + (A^T x A^T x A^T) ut[q(b)] with ut
+// the level-1 node values, accumulated in FP64 (u may alias vnear); q(b) = l1map[b] (the level-1
+// interval of evaluation block b), or b when l1map is NULL; vnear[b] is taken as 0 (and not
+// read) where near_flag[b] == 0 (NULL: every block).  uhat holds nint items.
+template <typename T>
+hipError_t launch_final_far(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up, const int32_t* par,
+                            const double* C01, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
+                            const int32_t* l1map, const int32_t* near_flag);
+
+// The lattice scheme (p = 13 and 17), whose node tiles do not fit those kernels:
+// Reg children -> parent; scratch: nparent * 8 * p^3 values of T (the children's partial sums)
+template <typename T>
 hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, T* out, int64_t nparent, int p,
-                         hipStream_t s, void* scratch = nullptr);
-// Level-1 node values of the lattice scheme: out[b] (p^3) = f[b] (n^3) padded with zeros
+                         hipStream_t s, void* scratch);
+// Level-1 node values: out[b] (p^3) = f[b] (n^3) padded with zeros
 template <typename T>
 hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStream_t s);
 // Interp parent -> its children, accumulate: io[child8[J][c]] += (C_c^T x C_c^T x C_c^T) par[J]
 hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
                               int64_t nparent, int p, hipStream_t s);
-// Final: u[b] = vnear[b] + (A^T x A^T x A^T) ut[q(b)], accumulated in FP64 (u may alias
-// vnear); q(b) = l1map[b] (the level-1 interval of evaluation block b), or b when l1map is
-// NULL; vnear[b] is taken as 0 (and not read) where near_flag[b] == 0 (NULL: every block)
+// Final pass as above from node values ut
 template <typename T>
 hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p,
                         hipStream_t s, const int32_t* l1map = nullptr, const int32_t* near_flag = nullptr);

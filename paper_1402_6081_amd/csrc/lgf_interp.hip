@@ -5,35 +5,46 @@
 //                                                                 C_c[m][k] = phi_m((c(p-1)+k)/2)
 //   parent -> children (add)    utilde_{2J+c} += (C_c^T x C_c^T x C_c^T) utilde_J
 //   level-1 interval -> block   u = vnear + (A^T x A^T x A^T) utilde    (FP64 add-back)
-// Each 3D product is three 1D passes through LDS.  Parent-level kernels handle all eight
-// children of one parent per workgroup; the down pass shares the x and y passes of the
-// children that have equal x (and y) child bits.
+// Each 3D product is three 1D passes through LDS.  For p <= 10 a workgroup that has an interval's
+// node values in LDS also transforms them: Reg goes on to the level's forward transform, the
+// level's inverse transform to Interp from the parent, and at level 1 on to the block, so the node
+// values of level 1 are not written to HBM on the way down, and each step is one launch less.
+// The passes are latency-bound (a few barriers over little data).
 #include <type_traits>
 
 #include "lgf_internal.h"
+#include "lgf_tile.h"
 
 namespace lgfdev {
 
 constexpr int kInterpThreads = 256;
-// Reg up runs one workgroup per parent over eight children: more waves per workgroup
-// hide the latency of its few, long workgroups
+// Reg up works on eight children per workgroup: more waves hide the latency of its few, long
+// workgroups
 constexpr int kRegUpThreads = 1024;
-// the per-block transfers (Reg 0->1, the final pass)
+// block -> level 1
 constexpr int kBlockThreads = 512;
-// Interp down (one workgroup per parent, or per (parent, child))
+// Interp down of the lattice scheme (one workgroup per (parent, child))
 constexpr int kDownThreads = 512;
+// inverse transform, Interp and the final pass
+constexpr int kInvThreads = 256;
+
+constexpr int imax(int a, int b) { return a > b ? a : b; }
 
 // ------------------------------------------------------------------ block -> level 1
 // One workgroup per block: the block is staged in LDS with coalesced loads, then the
-// three passes run from LDS with compile-time extents.  Rows that a wave reads at several
-// indices at once (the block's x rows, the matrix rows) are padded to N + 1 values, so
-// the reads fall into different LDS banks.
+// three passes run from LDS with compile-time extents, and the forward transform of the node
+// values.  Rows that a wave reads at several indices at once (the block's x rows, the matrix
+// rows) are padded to N + 1 values, so the reads fall into different LDS banks.
 template <typename T, int N, int P>
 __global__ void __launch_bounds__(kBlockThreads)
-    k_reg_block(const T* __restrict__ f, const double* __restrict__ A, T* __restrict__ out) {
+    k_reg_fft(const T* __restrict__ f, const double* __restrict__ A, T* __restrict__ ftil,
+              cplx<T>* __restrict__ fhat, int64_t nout) {
     constexpr int N3 = N * N * N, P3 = P * P * P, NR = N + 1;
-    __shared__ T X[N * N * NR], t1[N * N * P], t2[N * P * P];
-    __shared__ T Am[P * NR];
+    constexpr int kX = N * N * NR, kT1 = N * N * P, kT2 = N * P * P;
+    constexpr int kFront = (imax(kX + kT1, 2 * tile_values<P>()) + 1) / 2 * 2;  // X and t1, then the transform
+    __shared__ alignas(16) T lds[kFront + kT2 + P * NR];
+    T *X = lds, *t1 = lds + kX, *t2 = lds + kFront, *Am = t2 + kT2;
+    cplx<T>* buf = reinterpret_cast<cplx<T>*>(lds);
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     for (int i = tid; i < P * N; i += kBlockThreads) Am[(i / N) * NR + i % N] = (T)A[i];
@@ -60,26 +71,31 @@ __global__ void __launch_bounds__(kBlockThreads)
         t2[i] = acc;
     }
     __syncthreads();
-    T* o = out + b * P3;
-    for (int i = tid; i < P3; i += kBlockThreads) {  // z: out[a][c][d]
+    for (int i = tid; i < P3; i += kBlockThreads) {  // z: node values [a][c][d]
         const int cd = i % (P * P), a = i / (P * P);
         const T* m = Am + a * NR;
         T acc = T(0);
 #pragma unroll
         for (int z = 0; z < N; ++z) acc += m[z] * t2[z * (P * P) + cd];
-        o[i] = acc;
+        if (ftil) ftil[b * P3 + i] = acc;
+        staged<T, P>(buf, a, cd / P, cd % P) = acc;
     }
+    if (!fhat) return;
+    __syncthreads();
+    tile_forward<T, P, kBlockThreads>(buf, tid, fhat, (size_t)b, nout);
 }
 
 // ------------------------------------------------------------------ children -> parent
-template <typename T, int P, int NT = kRegUpThreads>
-__global__ void __launch_bounds__(NT)
-    k_reg_up(const T* __restrict__ in, const int32_t* __restrict__ child8, const double* __restrict__ C01,
-             T* __restrict__ out) {
-    constexpr int P3 = P * P * P;
-    __shared__ T X[8 * P3], t1[8 * P3];
+template <typename T, int P>
+__global__ void __launch_bounds__(kRegUpThreads)
+    k_regup_fft(const T* __restrict__ in, const int32_t* __restrict__ child8, const double* __restrict__ C01,
+                T* __restrict__ ftil, cplx<T>* __restrict__ fhat, int64_t nout) {
+    constexpr int P3 = P * P * P, NT = kRegUpThreads;
+    static_assert(8 * P3 >= 2 * tile_values<P>(), "the transform's tile fits in t1");
+    __shared__ alignas(16) T X[8 * P3], t1[8 * P3];
     __shared__ T Cm[2 * P * P];
     __shared__ int32_t ch[8];
+    cplx<T>* buf = reinterpret_cast<cplx<T>*>(t1);
     const int tid = threadIdx.x;
     const int64_t J = blockIdx.x;
     for (int i = tid; i < 2 * P * P; i += NT) Cm[i] = (T)C01[i];
@@ -112,7 +128,7 @@ __global__ void __launch_bounds__(NT)
         X[i] = s;
     }
     __syncthreads();
-    // z and the sum over children: out[a][b][d] = sum_c sum_z C_cz[a][z] X[c][z][b][d]
+    // z and the sum over children: node values [a][b][d] = sum_c sum_z C_cz[a][z] X[c][z][b][d]
     for (int i = tid; i < P3; i += NT) {
         const int bd = i % (P * P), a = i / (P * P);
         T s = T(0);
@@ -122,72 +138,93 @@ __global__ void __launch_bounds__(NT)
 #pragma unroll
             for (int z = 0; z < P; ++z) s += m[z] * X[c * P3 + z * P * P + bd];
         }
-        out[J * P3 + i] = s;
+        if (ftil) ftil[J * P3 + i] = s;
+        staged<T, P>(buf, a, bd / P, bd % P) = s;
     }
+    if (!fhat) return;
+    __syncthreads();
+    tile_forward<T, P, NT>(buf, tid, fhat, (size_t)J, nout);
 }
 
-// ------------------------------------------------------------------ parent -> children
-template <int P>
-__global__ void __launch_bounds__(kDownThreads)
-    k_interp_down(const double* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
-                  double* __restrict__ io) {
+// ------------------------------------------------------------------ inverse and parent -> child
+// The node values of interval q (rows of P values, VP apart) into V: the inverse transform of its
+// field spectrum (uhat NULL: zeros) plus Interp from its parent (par[q] = 8 J + c, -1: none;
+// up NULL: no level above).  R: 2 tile_values<P>() doubles, Xp: P^3, Ct: 2 P^2, used on the way.
+template <typename T, int P, int VP, int NT>
+__device__ __forceinline__ void node_values(const cplx<T>* __restrict__ uhat, int64_t nint,
+                                            const double* __restrict__ up, const int32_t* __restrict__ par,
+                                            const double* __restrict__ C01, int64_t q, double* R, double* Xp,
+                                            double* Ct, double* V, int tid) {
+    constexpr int P3 = P * P * P, P2 = P * P;
+    static_assert(tile_values<P>() >= P3, "the two passes' values fit in R");
+    const int pc = up ? par[q] : -1;  // uniform
+    if (pc >= 0) {
+        for (int i = tid; i < P3; i += NT) Xp[i] = up[(int64_t)(pc >> 3) * P3 + i];
+        for (int i = tid; i < 2 * P2; i += NT) {  // Ct_c[k][m] = C_c[m][k]
+            const int cc = i / P2, r = i % P2, k = r / P, m = r % P;
+            Ct[i] = C01[cc * P2 + m * P + k];
+        }
+    }
+    if (uhat) {
+        cplx<double>* buf = reinterpret_cast<cplx<double>*>(R);
+        tile_inverse<T, double, P, NT>(uhat, (size_t)q, nint, buf, tid);
+        __syncthreads();
+        for (int i = tid; i < P3; i += NT) V[(i / P) * VP + i % P] = staged<double, P>(buf, i / P2, i / P % P, i % P);
+    } else {
+        for (int i = tid; i < P3; i += NT) V[(i / P) * VP + i % P] = 0.0;
+    }
+    __syncthreads();
+    if (pc < 0) return;
+    const int cx = pc & 1, cy = (pc >> 1) & 1, cz = (pc >> 2) & 1;
+    double *t1 = R, *t2 = R + P3;
+    for (int i = tid; i < P3; i += NT) {  // x: t1[a][b][x']
+        const int xo = i % P, ab = i / P;
+        const double* m = Ct + cx * P2 + xo * P;
+        const double* row = Xp + ab * P;
+        double sum = 0.0;
+#pragma unroll
+        for (int d = 0; d < P; ++d) sum += m[d] * row[d];
+        t1[i] = sum;
+    }
+    __syncthreads();
+    for (int i = tid; i < P3; i += NT) {  // y: t2[a][y'][x']
+        const int xo = i % P, yo = (i / P) % P, a = i / P2;
+        const double* m = Ct + cy * P2 + yo * P;
+        const double* src = t1 + a * P2 + xo;
+        double sum = 0.0;
+#pragma unroll
+        for (int bb = 0; bb < P; ++bb) sum += m[bb] * src[bb * P];
+        t2[i] = sum;
+    }
+    __syncthreads();
+    for (int i = tid; i < P3; i += NT) {  // z, added to the interval's own values
+        const int yx = i % P2, zo = i / P2;
+        const double* m = Ct + cz * P2 + zo * P;
+        double sum = 0.0;
+#pragma unroll
+        for (int a = 0; a < P; ++a) sum += m[a] * t2[a * P2 + yx];
+        double* v = V + (i / P) * VP + i % P;
+        *v = *v + sum;
+    }
+    __syncthreads();
+}
+
+template <typename T, int P>
+__global__ void __launch_bounds__(kInvThreads)
+    k_inv_interp(const cplx<T>* __restrict__ uhat, const double* __restrict__ up, const int32_t* __restrict__ par,
+                 const double* __restrict__ C01, double* __restrict__ out) {
     constexpr int P3 = P * P * P;
-    __shared__ double X[P3], t1[2 * P3], t2[4 * P3];
-    __shared__ double Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
-    __shared__ int32_t ch[8];
-    const int tid = threadIdx.x;
-    const int64_t J = blockIdx.x;
-    for (int i = tid; i < 2 * P * P; i += kDownThreads) {
-        const int c = i / (P * P), r = i % (P * P), k = r / P, m = r % P;
-        Ct[i] = C01[c * P * P + m * P + k];
-    }
-    if (tid < 8) ch[tid] = child8[J * 8 + tid];
-    for (int i = tid; i < P3; i += kDownThreads) X[i] = par[J * P3 + i];
-    __syncthreads();
-    // x for both cx: t1[cx][a][b][x'] = sum_d Ct_cx[x'][d] X[a][b][d]
-    for (int i = tid; i < 2 * P3; i += kDownThreads) {
-        const int xo = i % P, ab = (i / P) % (P * P), cx = i / P3;
-        const double* m = Ct + cx * P * P + xo * P;
-        const double* row = X + ab * P;
-        double s = 0.0;
-#pragma unroll
-        for (int d = 0; d < P; ++d) s += m[d] * row[d];
-        t1[i] = s;
-    }
-    __syncthreads();
-    // y for both cy: t2[cy][cx][a][y'][x'] = sum_b Ct_cy[y'][b] t1[cx][a][b][x']
-    for (int i = tid; i < 4 * P3; i += kDownThreads) {
-        const int xo = i % P, yo = (i / P) % P, a = (i / (P * P)) % P, cx = (i / P3) & 1, cy = i / (2 * P3);
-        const double* m = Ct + cy * P * P + yo * P;
-        const double* src = t1 + cx * P3 + a * P * P + xo;
-        double s = 0.0;
-#pragma unroll
-        for (int bb = 0; bb < P; ++bb) s += m[bb] * src[bb * P];
-        t2[i] = s;
-    }
-    __syncthreads();
-    // z per child, accumulate into the child's node values
-    for (int i = tid; i < 8 * P3; i += kDownThreads) {
-        const int r = i % P3, c = i / P3;
-        const int q = ch[c];
-        if (q < 0) continue;
-        const int yx = r % (P * P), zo = r / (P * P);
-        const int cx = c & 1, cy = (c >> 1) & 1, cz = (c >> 2) & 1;
-        const double* m = Ct + cz * P * P + zo * P;
-        const double* src = t2 + (cy * 2 + cx) * P3 + yx;
-        double s = 0.0;
-#pragma unroll
-        for (int a = 0; a < P; ++a) s += m[a] * src[a * P * P];
-        double* dst = io + (int64_t)q * P3 + r;
-        *dst = *dst + s;
-    }
+    __shared__ alignas(16) double R[2 * tile_values<P>()];
+    __shared__ double Xp[P3], Ct[2 * P * P], V[P3];
+    const int64_t q = blockIdx.x;
+    node_values<T, P, P, kInvThreads>(uhat, gridDim.x, up, par, C01, q, R, Xp, Ct, V, threadIdx.x);
+    for (int i = threadIdx.x; i < P3; i += kInvThreads) out[q * P3 + i] = V[i];
 }
 
 // ------------------------------------------------------------------ one (parent, child) per workgroup
-// (every P = 17 level, and the Interp of levels with few parents at any P)
-// The kernels above hold 8 children, or a parent's 2 + 4 partial passes, in LDS (629 /
-// 275 KB at P = 17).  Here one workgroup handles one (parent, child) pair, which also
-// gives levels with few parents eight times the workgroups:
+// (the lattice scheme, P = 13 and 17)
+// The kernels above hold 8 children, or a tile and its transform, in LDS (629 KB at P = 17).
+// Here one workgroup handles one (parent, child) pair:
 //   Reg up:      k_reg_up_part writes each child's contribution to `part` (scratch), then
 //                k_reg_up_sum adds them in child order c = 0..7 (as one workgroup would);
 //   Interp down: each child accumulates its own values (no two workgroups write one child).
@@ -314,24 +351,14 @@ __global__ void k_pad_copy(const T* __restrict__ f, T* __restrict__ out, int64_t
 }
 
 // ------------------------------------------------------------------ level 1 -> block, FP64 add-back
-template <typename T, int N, int P>
-__global__ void __launch_bounds__(kBlockThreads)
-    k_final(const T* vnear, const double* __restrict__ ut, const double* __restrict__ A, T* u,
-            const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
-    constexpr int N3 = N * N * N, P3 = P * P * P, PR = P + 1;
-    // rows read at several indices at once by a wave are padded to P + 1 values (LDS banks)
-    __shared__ double X[P * P * PR], t1[P * P * N], t2[P * N * N];
-    __shared__ double At[N * PR];  // At[j][k] = A[k][j]
-    const int tid = threadIdx.x;
-    const int64_t b = blockIdx.x;
-    for (int i = tid; i < N * P; i += kBlockThreads) {
-        const int jj = i / P, k = i % P;
-        At[jj * PR + k] = A[k * N + jj];
-    }
-    const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
-    for (int i = tid; i < P3; i += kBlockThreads) X[(i / P) * PR + i % P] = ut[q * P3 + i];
-    __syncthreads();
-    for (int i = tid; i < P * P * N; i += kBlockThreads) {  // x: t1[a][c][x]
+// u[b] from the level-1 node values X (rows of P values, P + 1 apart: rows that a wave reads at
+// several indices at once fall into different LDS banks).  At: N (P + 1) values, the rows of A^T;
+// t1: P^2 N, t2: P N^2.  At and X are visible to the workgroup.
+template <typename T, int N, int P, int NT>
+__device__ __forceinline__ void final_passes(const double* X, const double* At, double* t1, double* t2,
+                                             const T* vnear, T* u, int64_t b, bool has_near, int tid) {
+    constexpr int N3 = N * N * N, PR = P + 1;
+    for (int i = tid; i < P * P * N; i += NT) {  // x: t1[a][c][x]
         const int x = i % N, ac = i / N;
         const double* m = At + x * PR;
         const double* row = X + ac * PR;
@@ -341,7 +368,7 @@ __global__ void __launch_bounds__(kBlockThreads)
         t1[i] = acc;
     }
     __syncthreads();
-    for (int i = tid; i < P * N * N; i += kBlockThreads) {  // y: t2[a][y][x]
+    for (int i = tid; i < P * N * N; i += NT) {  // y: t2[a][y][x]
         const int x = i % N, y = (i / N) % N, a = i / (N * N);
         const double* m = At + y * PR;
         const double* col = t1 + a * P * N + x;
@@ -352,86 +379,176 @@ __global__ void __launch_bounds__(kBlockThreads)
     }
     __syncthreads();
     const T* v = vnear + b * N3;
-    const bool has_near = !near_flag || near_flag[b];  // no near field: v is not read
     T* o = u + b * N3;
-    for (int i = tid; i < N3; i += kBlockThreads) {  // z: u[z][y][x]
+    for (int i = tid; i < N3; i += NT) {  // z: u[z][y][x]
         const int yx = i % (N * N), z = i / (N * N);
         const double* m = At + z * PR;
         double acc = 0.0;
 #pragma unroll
         for (int a = 0; a < P; ++a) acc += m[a] * t2[a * N * N + yx];
-        o[i] = (T)((has_near ? (double)v[i] : 0.0) + acc);
+        o[i] = (T)((has_near ? (double)v[i] : 0.0) + acc);  // no near field: v is not read
     }
+}
+
+// At[j][k] = A[k][j], rows P + 1 apart
+template <int N, int P, int NT>
+__device__ __forceinline__ void load_at(const double* __restrict__ A, double* At, int tid) {
+    for (int i = tid; i < N * P; i += NT) At[(i / P) * (P + 1) + i % P] = A[(i % P) * N + i / P];
+}
+
+// The level-1 inverse transform, Interp from level 2 and the interpolation to the block in one
+// workgroup per evaluation block (p <= 10).
+template <typename T, int N, int P>
+__global__ void __launch_bounds__(kInvThreads)
+    k_final_far(const T* vnear, const cplx<T>* __restrict__ uhat, int64_t nint, const double* __restrict__ up,
+                const int32_t* __restrict__ par, const double* __restrict__ C01, const double* __restrict__ A, T* u,
+                const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
+    constexpr int P3 = P * P * P, kT1 = P * P * N;
+    __shared__ alignas(16) double R[imax(2 * tile_values<P>(), kT1 + P * N * N)];
+    __shared__ double Xp[P3], Ct[2 * P * P], V[P * P * (P + 1)], At[N * (P + 1)];
+    const int tid = threadIdx.x;
+    const int64_t b = blockIdx.x;
+    const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
+    load_at<N, P, kInvThreads>(A, At, tid);
+    node_values<T, P, P + 1, kInvThreads>(uhat, nint, up, par, C01, q, R, Xp, Ct, V, tid);
+    final_passes<T, N, P, kInvThreads>(V, At, R, R + kT1, vnear, u, b, !near_flag || near_flag[b], tid);
+}
+
+// From node values in HBM (the lattice scheme).
+template <typename T, int N, int P>
+__global__ void __launch_bounds__(kBlockThreads)
+    k_final(const T* vnear, const double* __restrict__ ut, const double* __restrict__ A, T* u,
+            const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
+    constexpr int P3 = P * P * P, PR = P + 1;
+    __shared__ double X[P * P * PR], t1[P * P * N], t2[P * N * N];
+    __shared__ double At[N * PR];
+    const int tid = threadIdx.x;
+    const int64_t b = blockIdx.x;
+    load_at<N, P, kBlockThreads>(A, At, tid);
+    const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
+    for (int i = tid; i < P3; i += kBlockThreads) X[(i / P) * PR + i % P] = ut[q * P3 + i];
+    __syncthreads();
+    final_passes<T, N, P, kBlockThreads>(X, At, t1, t2, vnear, u, b, !near_flag || near_flag[b], tid);
 }
 
 // ------------------------------------------------------------------ launchers
-// (n, p) -> compile-time kernel: n in {4, 6, 8, 12, 16}, p in [2, 10], and (12, 13), (16, 17)
-template <template <int, int> class K, typename... Args>
-static hipError_t dispatch_np(int n, int p, Args... args) {
-#define LGF_NP(NN)                                          \
-    switch (p) {                                            \
-        case 2: return K<NN, 2>::run(args...);              \
-        case 3: return K<NN, 3>::run(args...);              \
-        case 4: return K<NN, 4>::run(args...);              \
-        case 5: return K<NN, 5>::run(args...);              \
-        case 6: return K<NN, 6>::run(args...);              \
-        case 7: return K<NN, 7>::run(args...);              \
-        case 8: return K<NN, 8>::run(args...);              \
-        case 9: return K<NN, 9>::run(args...);              \
-        case 10: return K<NN, 10>::run(args...);            \
-        default: return hipErrorInvalidValue;               \
-    }
-    switch (n) {
-        case 4: LGF_NP(4)
-        case 6: LGF_NP(6)
-        case 8: LGF_NP(8)
-        case 12:
-            if (p == 13) return K<12, 13>::run(args...);  // the lattice scheme n_I = n + 1
-            LGF_NP(12)
-        case 16:
-            if (p == 17) return K<16, 17>::run(args...);
-            LGF_NP(16)
+// p <= 10 -> compile-time kernel
+template <template <int> class K, typename... Args>
+static hipError_t dispatch_p(int p, Args... args) {
+    switch (p) {
+        case 2: return K<2>::run(args...);
+        case 3: return K<3>::run(args...);
+        case 4: return K<4>::run(args...);
+        case 5: return K<5>::run(args...);
+        case 6: return K<6>::run(args...);
+        case 7: return K<7>::run(args...);
+        case 8: return K<8>::run(args...);
+        case 9: return K<9>::run(args...);
+        case 10: return K<10>::run(args...);
         default: return hipErrorInvalidValue;
     }
-#undef LGF_NP
+}
+
+// n in {4, 6, 8, 12, 16} too
+template <template <int> class K, typename... Args>
+static hipError_t dispatch_np(int n, int p, Args... args) {
+    switch (n) {
+        case 4: return dispatch_p<K<4>::template At>(p, args...);
+        case 6: return dispatch_p<K<6>::template At>(p, args...);
+        case 8: return dispatch_p<K<8>::template At>(p, args...);
+        case 12: return dispatch_p<K<12>::template At>(p, args...);
+        case 16: return dispatch_p<K<16>::template At>(p, args...);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename T>
-struct RegBlockRun {
-    template <int N, int P>
+struct RegFft {
+    template <int N>
     struct K {
-        static hipError_t run(const T* f, const double* A, T* out, int64_t nb, hipStream_t s) {
-            return lgf_launch(k_reg_block<T, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, f, A, out);
+        template <int P>
+        struct At {
+            static hipError_t run(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout,
+                                  hipStream_t s) {
+                return lgf_launch(k_reg_fft<T, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, f, A, ftil, fhat,
+                                  nout);
+            }
+        };
+    };
+};
+
+template <typename T>
+struct RegupFft {
+    template <int P>
+    struct K {
+        static hipError_t run(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat,
+                              int64_t np, int64_t nout, hipStream_t s) {
+            return lgf_launch(k_regup_fft<T, P>, dim3((unsigned)np), dim3(kRegUpThreads), 0, s, in, child8, C01, ftil,
+                              fhat, nout);
         }
     };
 };
 
 template <typename T>
-struct FinalRun {
-    template <int N, int P>
+struct InvInterp {
+    template <int P>
     struct K {
-        static hipError_t run(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, const int32_t* l1map,
-                              const int32_t* near_flag, hipStream_t s) {
-            return lgf_launch(k_final<T, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, vnear, ut, A, u,
-                              l1map, near_flag);
+        static hipError_t run(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+                              double* out, int64_t nint, hipStream_t s) {
+            return lgf_launch(k_inv_interp<T, P>, dim3((unsigned)nint), dim3(kInvThreads), 0, s, uhat, up, par, C01,
+                              out);
         }
     };
 };
 
 template <typename T>
-hipError_t launch_reg_block(const T* f, const double* A, T* out, int64_t nb, int n, int p, hipStream_t s) {
+struct FinalFar {
+    template <int N>
+    struct K {
+        template <int P>
+        struct At {
+            static hipError_t run(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up,
+                                  const int32_t* par, const double* C01, const double* A, T* u, int64_t nb,
+                                  hipStream_t s, const int32_t* l1map, const int32_t* near_flag) {
+                return lgf_launch(k_final_far<T, N, P>, dim3((unsigned)nb), dim3(kInvThreads), 0, s, vnear, uhat,
+                                  nint, up, par, C01, A, u, l1map, near_flag);
+            }
+        };
+    };
+};
+
+template <typename T>
+hipError_t launch_reg_fft(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
+                          hipStream_t s) {
     if (nb <= 0) return hipSuccess;
-    return dispatch_np<RegBlockRun<T>::template K>(n, p, f, A, out, nb, s);
+    return dispatch_np<RegFft<T>::template K>(n, p, f, A, ftil, fhat, nb, nout, s);
 }
 
-template <typename T, int P>
-static hipError_t reg_up_p(const T* in, const int32_t* child8, const double* C01, T* out, int64_t np, hipStream_t s) {
-    return lgf_launch(k_reg_up<T, P>, dim3((unsigned)np), dim3(kRegUpThreads), 0, s, in, child8, C01, out);
+template <typename T>
+hipError_t launch_regup_fft(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat, int64_t np,
+                            int64_t nout, int p, hipStream_t s) {
+    if (np <= 0) return hipSuccess;
+    return dispatch_p<RegupFft<T>::template K>(p, in, child8, C01, ftil, fhat, np, nout, s);
 }
 
-// Tiles of more than n_max nodes: one workgroup per (parent, child) writes each child's
-// contribution to scratch, a second kernel adds them in child order (eight children of so
-// many nodes do not fit one workgroup's LDS).
+template <typename T>
+hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+                             double* out, int64_t nint, int p, hipStream_t s) {
+    if (nint <= 0) return hipSuccess;
+    return dispatch_p<InvInterp<T>::template K>(p, uhat, up, par, C01, out, nint, s);
+}
+
+template <typename T>
+hipError_t launch_final_far(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up, const int32_t* par,
+                            const double* C01, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
+                            const int32_t* l1map, const int32_t* near_flag) {
+    if (nb <= 0) return hipSuccess;
+    return dispatch_np<FinalFar<T>::template K>(n, p, vnear, uhat, nint, up, par, C01, A, u, nb, s, l1map, near_flag);
+}
+
+// One workgroup per (parent, child) writes each child's contribution to scratch, a second
+// kernel adds them in child order (eight children of 13^3 or 17^3 nodes do not fit one
+// workgroup's LDS).
 template <typename T, int P>
 static hipError_t reg_up_parts(const T* in, const int32_t* child8, const double* C01, T* out, int64_t np,
                                hipStream_t s, void* scratch) {
@@ -449,51 +566,19 @@ hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, 
                          hipStream_t s, void* scratch) {
     if (np <= 0) return hipSuccess;
     switch (p) {
-        case 2: return reg_up_p<T, 2>(in, child8, C01, out, np, s);
-        case 3: return reg_up_p<T, 3>(in, child8, C01, out, np, s);
-        case 4: return reg_up_p<T, 4>(in, child8, C01, out, np, s);
-        case 5: return reg_up_p<T, 5>(in, child8, C01, out, np, s);
-        case 6: return reg_up_p<T, 6>(in, child8, C01, out, np, s);
-        case 7: return reg_up_p<T, 7>(in, child8, C01, out, np, s);
-        case 8: return reg_up_p<T, 8>(in, child8, C01, out, np, s);
-        case 9: return reg_up_p<T, 9>(in, child8, C01, out, np, s);
-        case 10: return reg_up_p<T, 10>(in, child8, C01, out, np, s);
         case 13: return reg_up_parts<T, 13>(in, child8, C01, out, np, s, scratch);
         case 17: return reg_up_parts<T, 17>(in, child8, C01, out, np, s, scratch);
         default: return hipErrorInvalidValue;
     }
 }
 
-template <int P>
-static hipError_t interp_down_p(const double* par, const int32_t* child8, const double* C01, double* io, int64_t np,
-                                hipStream_t s) {
-    // levels with few parents: one workgroup per (parent, child), eight times the
-    // workgroups (the same sums in the same order, so the same bits as one per parent)
-    if (np <= 256)
-        return lgf_launch(k_interp_down_one<P>, dim3((unsigned)(np * 8)), dim3(kDownThreads), 0, s, par, child8,
-                          C01, io);
-    return lgf_launch(k_interp_down<P>, dim3((unsigned)np), dim3(kDownThreads), 0, s, par, child8, C01, io);
-}
-
 hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
                               int64_t nparent, int p, hipStream_t s) {
     if (nparent <= 0) return hipSuccess;
+    const dim3 grid((unsigned)(nparent * 8)), block(kDownThreads);
     switch (p) {
-        case 2: return interp_down_p<2>(par, child8, C01, io, nparent, s);
-        case 3: return interp_down_p<3>(par, child8, C01, io, nparent, s);
-        case 4: return interp_down_p<4>(par, child8, C01, io, nparent, s);
-        case 5: return interp_down_p<5>(par, child8, C01, io, nparent, s);
-        case 6: return interp_down_p<6>(par, child8, C01, io, nparent, s);
-        case 7: return interp_down_p<7>(par, child8, C01, io, nparent, s);
-        case 8: return interp_down_p<8>(par, child8, C01, io, nparent, s);
-        case 9: return interp_down_p<9>(par, child8, C01, io, nparent, s);
-        case 10: return interp_down_p<10>(par, child8, C01, io, nparent, s);
-        case 13:
-            return lgf_launch(k_interp_down_one<13>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
-                              child8, C01, io);
-        case 17:
-            return lgf_launch(k_interp_down_one<17>, dim3((unsigned)(nparent * 8)), dim3(kDownThreads), 0, s, par,
-                              child8, C01, io);
+        case 13: return lgf_launch(k_interp_down_one<13>, grid, block, 0, s, par, child8, C01, io);
+        case 17: return lgf_launch(k_interp_down_one<17>, grid, block, 0, s, par, child8, C01, io);
         default: return hipErrorInvalidValue;
     }
 }
@@ -506,23 +591,32 @@ hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStre
 }
 
 template <typename T>
-hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
-                        const int32_t* l1map, const int32_t* near_flag) {
+hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p,
+                        hipStream_t s, const int32_t* l1map, const int32_t* near_flag) {
     if (nb <= 0) return hipSuccess;
-    return dispatch_np<FinalRun<T>::template K>(n, p, vnear, ut, A, u, nb, l1map, near_flag, s);
+    const dim3 grid((unsigned)nb), block(kBlockThreads);
+    if (n == 12 && p == 13) return lgf_launch(k_final<T, 12, 13>, grid, block, 0, s, vnear, ut, A, u, l1map, near_flag);
+    if (n == 16 && p == 17) return lgf_launch(k_final<T, 16, 17>, grid, block, 0, s, vnear, ut, A, u, l1map, near_flag);
+    return hipErrorInvalidValue;
 }
 
-template hipError_t launch_reg_block<double>(const double*, const double*, double*, int64_t, int, int, hipStream_t);
-template hipError_t launch_pad_copy<double>(const double*, double*, int64_t, int, int, hipStream_t);
-template hipError_t launch_pad_copy<float>(const float*, float*, int64_t, int, int, hipStream_t);
-template hipError_t launch_reg_block<float>(const float*, const double*, float*, int64_t, int, int, hipStream_t);
-template hipError_t launch_reg_up<double>(const double*, const int32_t*, const double*, double*, int64_t, int,
-                                         hipStream_t, void*);
-template hipError_t launch_reg_up<float>(const float*, const int32_t*, const double*, float*, int64_t, int,
-                                         hipStream_t, void*);
-template hipError_t launch_final<double>(const double*, const double*, const double*, double*, int64_t, int,
-                                                 int, hipStream_t, const int32_t*, const int32_t*);
-template hipError_t launch_final<float>(const float*, const double*, const double*, float*, int64_t, int, int,
-                                              hipStream_t, const int32_t*, const int32_t*);
+#define LGF_INST(T)                                                                                                 \
+    template hipError_t launch_reg_fft<T>(const T*, const double*, T*, cplx<T>*, int64_t, int64_t, int, int,        \
+                                          hipStream_t);                                                             \
+    template hipError_t launch_regup_fft<T>(const T*, const int32_t*, const double*, T*, cplx<T>*, int64_t, int64_t, \
+                                            int, hipStream_t);                                                      \
+    template hipError_t launch_inv_interp<T>(const cplx<T>*, const double*, const int32_t*, const double*, double*, \
+                                             int64_t, int, hipStream_t);                                            \
+    template hipError_t launch_final_far<T>(const T*, const cplx<T>*, int64_t, const double*, const int32_t*,       \
+                                            const double*, const double*, T*, int64_t, int, int, hipStream_t,       \
+                                            const int32_t*, const int32_t*);                                        \
+    template hipError_t launch_reg_up<T>(const T*, const int32_t*, const double*, T*, int64_t, int, hipStream_t,    \
+                                         void*);                                                                    \
+    template hipError_t launch_pad_copy<T>(const T*, T*, int64_t, int, int, hipStream_t);                           \
+    template hipError_t launch_final<T>(const T*, const double*, const double*, T*, int64_t, int, int, hipStream_t, \
+                                        const int32_t*, const int32_t*);
+LGF_INST(double)
+LGF_INST(float)
+#undef LGF_INST
 
 }  // namespace lgfdev

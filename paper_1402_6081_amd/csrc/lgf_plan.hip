@@ -89,9 +89,8 @@ struct DevBuf {
 struct LevelPlan {
     int64_t nint = 0, nsrc_int = 0;
     int64_t sib_pairs = 0, csr_entries = 0, ncsr = 0;
-    bool zero_uhat = false;
     std::shared_ptr<SpectraEntry> spectra, spectra_csr;  // radius 3 / radius of the CSR offsets
-    int32_t* d_child8 = nullptr;
+    int32_t *d_child8 = nullptr, *d_par = nullptr;
     // these intervals as parents of the M2L below: children, candidate sources and neighbours
     // holding a source, by decreasing number of neighbours
     int32_t *d_m2l_child8 = nullptr, *d_m2l_src216 = nullptr;
@@ -274,44 +273,40 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     const bool split = overlap && ov == 1;
     hipStream_t s2 = overlap ? pl->far_stream : s;
     hipStream_t s3 = split ? pl->far_stream2 : s2;
-    // the M2L of level l over its parents' lists (level 1 of the lattice scheme reads the blocks'
-    // own spectra)
+    // the source spectra of level l and their number (level 1 of the lattice scheme reads the
+    // blocks' own spectra)
+    auto far_sources = [&](int l) { return (const C*)(l == 1 && pl->lat1 ? pl->d_fhat0 : pl->lv[l].d_fhat); };
+    auto far_nsrc = [&](int l) { return l == 1 && pl->lat1 ? pl->nsrc : pl->lv[l].nint; };
+    // the M2L of level l (below the top, with sib_pairs) over its parents' lists
     auto far_level = [&](int l) -> FarLevel<T> {
         const LevelPlan &L = pl->lv[l], &Pp = pl->lv[l + 1];
-        const bool reuse0 = l == 1 && pl->lat1;
-        return FarLevel<T>{reuse0 ? (const C*)pl->d_fhat0 : (const C*)L.d_fhat,
+        return FarLevel<T>{far_sources(l),
                            (const C*)L.spectra->dev,
                            Pp.d_m2l_child8,
                            Pp.d_m2l_src216,
                            (C*)L.d_uhat,
                            Pp.nint,
                            L.nint,
-                           reuse0 ? pl->nsrc : L.nint,
+                           far_nsrc(l),
                            L.spectra->S,
                            L.spectra->sym,
                            Pp.d_m2l_mask,
                            Pp.m2l_spread};
     };
-    // forward work of level l: PadFFT and the M2L products (Steps 1-2)
-    auto level_up = [&](int l, hipStream_t st, bool sib = true, bool fwd = true) -> hipError_t {
+    // Interp of the lattice scheme from level l + 1 down to level l, accumulated
+    auto interp = [&](int l, hipStream_t st) -> hipError_t {
+        LGF_STEP(st,
+                 (launch_interp_down((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_C01,
+                                     (U*)pl->lv[l].d_util, pl->lv[l + 1].nint, p, st)),
+                 "interp_l" + std::to_string(l + 1) + "_l" + std::to_string(l), (lvN(l + 1) + 2.0 * lvN(l)) * p3 * us,
+                 lvN(l) * 2.0 * 3.0 * p3 * p);
+        return hipSuccess;
+    };
+    // M2L products of level l (Step 2); sib = false: the top-level lists only
+    auto level_prod = [&](int l, hipStream_t st, bool sib = true) -> hipError_t {
         LevelPlan& L = pl->lv[l];
         if (L.pairs() == 0) return hipSuccess;
         const double S1 = Sl(l);
-        // level 1 of the lattice scheme: the intervals' nodes are the blocks' grid points and
-        // the last node plane of Reg is zero, so its spectra are the level-0 block spectra
-        const bool reuse0 = l == 1 && pl->lat1;
-        const C* fhat = reuse0 ? (const C*)pl->d_fhat0 : (const C*)L.d_fhat;
-        const int64_t nsrc_items = reuse0 ? pl->nsrc : L.nint;
-        if (!reuse0 && fwd) {
-            // level 1: the sources come first and are the only intervals the lists read
-            const int64_t nfwd = l == 1 ? pl->nsrc : L.nint;
-            LGF_STEP(st,
-                     (launch_pad_fft<T>(p, (const T*)L.d_ftil, (C*)L.d_fhat, nfwd, st, 0, L.nint + 1, pl->d_scratch)),
-                     lname("fft_fwd_l", l), (double)nfwd * (p3 * es + S1 * cs), (double)nfwd * fft_flops(2 * p));
-        }
-        if (L.zero_uhat)
-            LGF_STEP(st, zero_fill(L.d_uhat, L.nint * Slp(l) * 2 * (int64_t)sizeof(T), st), lname("zero_uhat_l", l),
-                     lvN(l) * S1 * cs, 0.0);
         if (sib && L.sib_pairs > 0) {
             const FarLevel<T> one = far_level(l);
             LGF_STEP(st, (launch_prod_far_sib_levels<T>(&one, 1, tc.far_waves, tc.far_children, st)),
@@ -320,42 +315,80 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
         }
         if (L.csr_entries > 0)
             LGF_STEP(st,
-                     (launch_prod_far<T>(fhat, (const C*)L.spectra_csr->dev, L.d_csr_ptr, L.d_csr_src, L.d_csr_off,
+                     (launch_prod_far<T>(far_sources(l), (const C*)L.spectra_csr->dev, L.d_csr_ptr, L.d_csr_src, L.d_csr_off,
                                          L.d_csr_tgt, (C*)L.d_uhat, L.ncsr, L.nint, L.spectra_csr->noff,
-                                         L.spectra_csr->S, st, nsrc_items, L.spectra_csr->sym)),
+                                         L.spectra_csr->S, st, far_nsrc(l), L.spectra_csr->sym)),
                      lname("prod_top_l", l),
                      ((double)L.nsrc_int + lvN(l) + khat_rows(*L.spectra_csr, L.spectra_csr->noff)) * S1 * cs,
                      (double)L.csr_entries * S1 * 8.0);
         return hipSuccess;
     };
-    // inverse of level l (IFFT + Trunc, or zero when the level has no list entries)
-    auto level_down = [&](int l, hipStream_t st) -> hipError_t {
+    // Reg to level l and its forward transform (Step 1).  Level 1: the sources come first and are
+    // the only intervals the lists read.
+    auto level_up = [&](int l, hipStream_t st) -> hipError_t {
         LevelPlan& L = pl->lv[l];
-        if (L.pairs() == 0) {
-            LGF_STEP(st, zero_fill(L.d_util, L.nint * (int64_t)p * p * p * sizeof(U), st), lname("zero_l", l),
-                     lvN(l) * p3 * us, 0.0);
-        } else if (l == 1 && pl->lat1) {
-            // n^3 results into tiles of p = n + 1 nodes (the last node plane is not used by
-            // the final pass); plain precision: these values are not interpolated further
-            LGF_STEP(st,
-                     (launch_ifft_trunc<T, T, U>(n, (const C*)L.d_uhat, (U*)L.d_util, L.nint, st, 0, nullptr, nullptr,
-                                                 p)),
-                     lname("fft_inv_l", l), lvN(l) * (Sl(l) * cs + p3 * us), lvN(l) * fft_flops(2 * n));
-        } else {
-            LGF_STEP(st,
-                     (launch_ifft_trunc<T, double, U>(p, (const C*)L.d_uhat, (U*)L.d_util, L.nint, st, 0, nullptr,
-                                                      pl->d_scratch)),
-                     lname("fft_inv_l", l), lvN(l) * (Sl(l) * cs + p3 * us), lvN(l) * fft_flops(2 * p));
+        const bool lists = L.pairs() > 0;
+        const double nup = l == 1 ? ns : lvN(l);
+        const double rbytes = l == 1 ? ns * (n3 + p3) * es : (lvN(l - 1) + lvN(l)) * p3 * es;
+        const double rflops = l == 1 ? ns * 2.0 * (p * n3 + p * p * n * n + p3 * n) : lvN(l - 1) * 6.0 * p3 * p;
+        const std::string rname = "reg_l" + std::to_string(l - 1) + "_l" + std::to_string(l);
+        if (!pl->lat1) {
+            const double fb = lists ? nup * Sl(l) * cs : 0.0, ff = lists ? nup * fft_flops(2 * p) : 0.0;
+            if (l == 1)
+                LGF_STEP(st,
+                         (launch_reg_fft<T>(f, pl->d_A, (T*)L.d_ftil, (C*)L.d_fhat, pl->nsrc, L.nint + 1, n, p, st)),
+                         rname, rbytes + fb, rflops + ff);
+            else
+                LGF_STEP(st,
+                         (launch_regup_fft<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, pl->d_C01, (T*)L.d_ftil,
+                                              (C*)L.d_fhat, L.nint, L.nint + 1, p, st)),
+                         rname, rbytes + fb, rflops + ff);
+            return hipSuccess;
         }
+        // the lattice scheme: the level-1 nodes are the blocks' grid points (a padded copy, and
+        // the level-0 block spectra serve as its spectra)
+        if (l == 1) {
+            LGF_STEP(st, (launch_pad_copy<T>(f, (T*)L.d_ftil, pl->nsrc, n, p, st)), rname, rbytes, 0.0);
+            return hipSuccess;
+        }
+        LGF_STEP(st,
+                 (launch_reg_up<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, pl->d_C01, (T*)L.d_ftil, L.nint, p, st,
+                                   pl->d_scratch)),
+                 rname, rbytes, rflops);
+        if (lists)
+            LGF_STEP(st,
+                     (launch_pad_fft<T>(p, (const T*)L.d_ftil, (C*)L.d_fhat, L.nint, st, 0, L.nint + 1,
+                                        pl->d_scratch)),
+                     lname("fft_fwd_l", l), lvN(l) * (p3 * es + Sl(l) * cs), lvN(l) * fft_flops(2 * p));
         return hipSuccess;
     };
-    // Interp from level l + 1 down to level l, accumulated (Step 3)
-    auto interp = [&](int l, hipStream_t st) -> hipError_t {
-        LGF_STEP(st,
-                 (launch_interp_down((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_C01,
-                                        (U*)pl->lv[l].d_util, pl->lv[l + 1].nint, p, st)),
-                 "interp_l" + std::to_string(l + 1) + "_l" + std::to_string(l), (lvN(l + 1) + 2.0 * lvN(l)) * p3 * us,
-                 lvN(l) * 2.0 * 3.0 * p3 * p);
+    // inverse of level l (IFFT + Trunc, or zeros when the level has no list entries) plus Interp
+    // from the level above (Step 3); at level 1 only for the lattice scheme (the final pass does
+    // it otherwise)
+    auto level_down = [&](int l, hipStream_t st) -> hipError_t {
+        LevelPlan& L = pl->lv[l];
+        const bool lists = L.pairs() > 0, above = l < pl->Ltop;
+        const double ibytes = above ? (lvN(l + 1) + 2.0 * lvN(l)) * p3 * us : 0.0;
+        const double iflops = above ? lvN(l) * 6.0 * p3 * p : 0.0;
+        if (!pl->lat1) {
+            LGF_STEP(st,
+                     (launch_inv_interp<T>(lists ? (const C*)L.d_uhat : nullptr,
+                                           above ? (const U*)pl->lv[l + 1].d_util : nullptr, L.d_par, pl->d_C01,
+                                           (U*)L.d_util, L.nint, p, st)),
+                     lname("inv_interp_l", l), lvN(l) * ((lists ? Sl(l) * cs : 0.0) + p3 * us) + (above ? lvN(l + 1) * p3 * us : 0.0),
+                     (lists ? lvN(l) * fft_flops(2 * p) : 0.0) + iflops);
+            return hipSuccess;
+        }
+        if (!lists)
+            LGF_STEP(st, zero_fill(L.d_util, L.nint * (int64_t)p * p * p * sizeof(U), st), lname("zero_l", l),
+                     lvN(l) * p3 * us, 0.0);
+        else
+            LGF_STEP(st,
+                     (launch_ifft_lattice<T>(tile(l), (const C*)L.d_uhat, (U*)L.d_util, L.nint, st, pl->d_scratch,
+                                             l == 1 ? p : 0)),
+                     lname("fft_inv_l", l), lvN(l) * (Sl(l) * cs + p3 * us), lvN(l) * fft_flops(2 * tile(l)));
+        if (above && !(l == 1 && split))  // (three branches: level 1 waits for the coarse levels first)
+            return interp(l, st);
         return hipSuccess;
     };
     const NearLevel<T> near0{(const C*)pl->d_fhat0, (const C*)pl->spectra0->dev, pl->d_g0_tgt8, pl->d_g0_src64,
@@ -379,53 +412,14 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             if ((e = rec_event_record(pl->ev_fork, s)) != hipSuccess) return e;
             if ((e = rec_stream_wait(s2, pl->ev_fork)) != hipSuccess) return e;
         }
-        if (pl->lat1)  // identity on the grid points: a padded copy
-            LGF_STEP(s2, (launch_pad_copy<T>(f, (T*)pl->lv[1].d_ftil, pl->nsrc, n, p, s2)), "reg_l0_l1",
-                     ns * (n3 + p3) * es, 0.0);
-        else
-            LGF_STEP(s2, (launch_reg_block<T>(f, pl->d_A, (T*)pl->lv[1].d_ftil, pl->nsrc, n, p, s2)), "reg_l0_l1",
-                     ns * (n3 + p3) * es, ns * 2.0 * (p * n3 + p * p * n * n + p3 * n));
         const bool coarse = pl->Ltop >= 2;
-        // with one far stream, the coarse levels' M2L joins level 1's in one launch after all
-        // the levels' transforms (their small kernels would otherwise run nearly alone before
-        // the near field's large ones start).  The transforms go out as one launch too, except
-        // in the lattice scheme, whose level 1 and two-phase levels keep their own launches.
-        const bool merge = !split && coarse;
-        if (merge) {
-            for (int l = 1; l < pl->Ltop; ++l)
-                LGF_STEP(s2,
-                         (launch_reg_up<T>((const T*)pl->lv[l].d_ftil, pl->lv[l + 1].d_child8, pl->d_C01,
-                                           (T*)pl->lv[l + 1].d_ftil, pl->lv[l + 1].nint, p, s2, pl->d_scratch)),
-                         "reg_l" + std::to_string(l) + "_l" + std::to_string(l + 1),
-                         (lvN(l) + lvN(l + 1)) * p3 * es, lvN(l) * 2.0 * 3.0 * p3 * p);
-            // every level's forward transform in one launch, then the zero fills and top-level
-            // lists level by level
-            std::vector<FwdLevel<T>> fw;
-            if (pl->lat1)
-                for (int l = pl->Ltop; l >= 1; --l)
-                    if ((e = level_up(l, s2, false, true)) != hipSuccess) return e;
-            double fbytes = 0.0, fflops = 0.0;
-            int flo = 0, fhi = 0;
-            for (int l = pl->Ltop; l >= 1 && !pl->lat1; --l) {
-                LevelPlan& L = pl->lv[l];
-                if (L.pairs() == 0) continue;
-                const int64_t nfwd = l == 1 ? pl->nsrc : L.nint;  // level 1: the source intervals
-                if (nfwd <= 0) continue;
-                fw.push_back(FwdLevel<T>{(const T*)L.d_ftil, (C*)L.d_fhat, nfwd, L.nint + 1});
-                fbytes += (double)nfwd * (p3 * es + Sl(l) * cs);
-                fflops += (double)nfwd * fft_flops(2 * p);
-                flo = l;
-                if (!fhi) fhi = l;
-            }
-            for (size_t k0 = 0; k0 < fw.size(); k0 += kMaxFarSegs) {
-                const int nk = (int)std::min<size_t>(kMaxFarSegs, fw.size() - k0);
-                const std::string nm = fw.size() == 1 ? lname("fft_fwd_l", flo)
-                                                      : "fft_fwd_l" + std::to_string(flo) + "-" + std::to_string(fhi);
-                LGF_STEP(s2, (launch_pad_fft_levels<T>(p, fw.data() + k0, nk, s2)), nm, k0 == 0 ? fbytes : 0.0,
-                         k0 == 0 ? fflops : 0.0);
-            }
-            for (int l = pl->Ltop; l >= 1 && !pl->lat1; --l)
-                if ((e = level_up(l, s2, false, false)) != hipSuccess) return e;
+        if ((e = level_up(1, s2)) != hipSuccess) return e;
+        if (!split) {
+            // one far stream: the M2L of all the levels in one launch after their transforms (the
+            // coarse levels' small kernels would otherwise run nearly alone), then the top-level
+            // lists and the way down
+            for (int l = 2; l <= pl->Ltop; ++l)
+                if ((e = level_up(l, s2)) != hipSuccess) return e;
             std::vector<FarLevel<T>> fl;
             double bytes = 0.0, flops = 0.0;
             int lo = 0, hi = 0;
@@ -446,61 +440,28 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
                          (launch_prod_far_sib_levels<T>(fl.data() + k0, nk, tc.far_waves, tc.far_children, s2)),
                          nm, k0 == 0 ? bytes : 0.0, k0 == 0 ? flops : 0.0);
             }
-            // every level's inverse in one launch too (levels without list entries are zeroed),
-            // then Interp from the top down
-            std::vector<InvLevel<T, U>> il;
-            double ibytes = 0.0, iflops = 0.0;
-            int ilo = 0, ihi = 0;
-            for (int l = pl->Ltop; l >= 1; --l) {
-                LevelPlan& L = pl->lv[l];
-                if (L.pairs() == 0 || pl->lat1) {
-                    if ((e = level_down(l, s2)) != hipSuccess) return e;
-                    continue;
-                }
-                il.push_back(InvLevel<T, U>{(const C*)L.d_uhat, (U*)L.d_util, L.nint});
-                ibytes += lvN(l) * (Sl(l) * cs + p3 * us);
-                iflops += lvN(l) * fft_flops(2 * p);
-                ilo = l;
-                if (!ihi) ihi = l;
-            }
-            for (size_t k0 = 0; k0 < il.size(); k0 += kMaxFarSegs) {
-                const int nk = (int)std::min<size_t>(kMaxFarSegs, il.size() - k0);
-                const std::string nm = il.size() == 1 ? lname("fft_inv_l", ilo)
-                                                      : "fft_inv_l" + std::to_string(ilo) + "-" + std::to_string(ihi);
-                LGF_STEP(s2, (launch_ifft_trunc_levels<T, double, U>(p, il.data() + k0, nk, s2)), nm,
-                         k0 == 0 ? ibytes : 0.0, k0 == 0 ? iflops : 0.0);
-            }
-            for (int l = pl->Ltop - 1; l >= 1; --l)
-                if ((e = interp(l, s2)) != hipSuccess) return e;
-        }
-        if (!merge && coarse) {
-            // levels >= 2 on s3: Reg up, their M2L, and the down pass to level 2
-            if (split) {
+            for (int l = pl->Ltop; l >= 1; --l)
+                if ((e = level_prod(l, s2, false)) != hipSuccess) return e;
+            for (int l = pl->Ltop; l >= (pl->lat1 ? 1 : 2); --l)
+                if ((e = level_down(l, s2)) != hipSuccess) return e;
+        } else {
+            if (coarse) {
+                // levels >= 2 on s3: Reg up, their M2L, and the down pass to level 2
                 if ((e = rec_event_record(pl->ev_fork2, s2)) != hipSuccess) return e;
                 if ((e = rec_stream_wait(s3, pl->ev_fork2)) != hipSuccess) return e;
+                for (int l = 2; l <= pl->Ltop; ++l)
+                    if ((e = level_up(l, s3)) != hipSuccess) return e;
+                for (int l = 2; l <= pl->Ltop; ++l)
+                    if ((e = level_prod(l, s3)) != hipSuccess) return e;
+                for (int l = pl->Ltop; l >= 2; --l)
+                    if ((e = level_down(l, s3)) != hipSuccess) return e;
+                if ((e = rec_event_record(pl->ev_join2, s3)) != hipSuccess) return e;
             }
-            for (int l = 1; l < pl->Ltop; ++l)
-                LGF_STEP(s3,
-                         (launch_reg_up<T>((const T*)pl->lv[l].d_ftil, pl->lv[l + 1].d_child8, pl->d_C01,
-                                           (T*)pl->lv[l + 1].d_ftil, pl->lv[l + 1].nint, p, s3, pl->d_scratch)),
-                         "reg_l" + std::to_string(l) + "_l" + std::to_string(l + 1),
-                         (lvN(l) + lvN(l + 1)) * p3 * es, lvN(l) * 2.0 * 3.0 * p3 * p);
-            for (int l = 2; l <= pl->Ltop; ++l)
-                if ((e = level_up(l, s3)) != hipSuccess) return e;
-            for (int l = pl->Ltop; l >= 2; --l) {
-                if ((e = level_down(l, s3)) != hipSuccess) return e;
-                if (l < pl->Ltop && (e = interp(l, s3)) != hipSuccess) return e;
-            }
-            if (split && (e = rec_event_record(pl->ev_join2, s3)) != hipSuccess) return e;
-        }
-        // level 1 on s2
-        if (!merge) {
-            if ((e = level_up(1, s2)) != hipSuccess) return e;
-            if ((e = level_down(1, s2)) != hipSuccess) return e;
-        }
-        if (!merge && coarse) {
-            if (split && (e = rec_stream_wait(s2, pl->ev_join2)) != hipSuccess) return e;
-            if ((e = interp(1, s2)) != hipSuccess) return e;
+            // level 1 on s2
+            if ((e = level_prod(1, s2)) != hipSuccess) return e;
+            if (pl->lat1 && (e = level_down(1, s2)) != hipSuccess) return e;
+            if (coarse && (e = rec_stream_wait(s2, pl->ev_join2)) != hipSuccess) return e;
+            if (coarse && pl->lat1 && (e = interp(1, s2)) != hipSuccess) return e;
         }
         if (overlap && (e = rec_event_record(pl->ev_join, s2)) != hipSuccess) return e;
     }
@@ -509,17 +470,30 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     {
         LGF_STEP(s, launch_prod_near<T>(near0, tc.near_waves, s),
                  "prod_l0", (ns + nt0 + khat_rows(*pl->spectra0, 27)) * S0 * cs, (double)pl->near_pairs * S0 * 8.0);
-        LGF_STEP(s,
-                 (launch_ifft_trunc<T, T, T>(n, (const C*)pl->d_uhat0, u, pl->ntgt0, s, tc.fft0_threads,
-                                             pl->d_near_out)),
+        LGF_STEP(s, (launch_ifft0<T>(n, (const C*)pl->d_uhat0, u, pl->ntgt0, s, tc.fft0_threads, pl->d_near_out)),
                  "fft_inv_l0", nt0 * (S0 * cs + n3 * es), nt0 * fft_flops(2 * n));
     }
     if (far) {
         if (overlap && (e = rec_stream_wait(s, pl->ev_join)) != hipSuccess) return e;
-        LGF_STEP(s,
-                 (launch_final<T>(u, (const U*)pl->lv[1].d_util, pl->d_A, u, pl->neval, n, p, s, pl->d_eval_l1,
-                                     pl->d_near_flag)),
-                 "final_l1_l0", (ne + nt0) * n3 * es + ne * p3 * us, ne * 2.0 * (p3 * n + p * p * n * n + p * n3));
+        LevelPlan& L = pl->lv[1];
+        const double fbytes = (ne + nt0) * n3 * es;
+        const double fflops = ne * 2.0 * (p3 * n + p * p * n * n + p * n3);
+        if (pl->lat1) {
+            LGF_STEP(s,
+                     (launch_final<T>(u, (const U*)L.d_util, pl->d_A, u, pl->neval, n, p, s, pl->d_eval_l1,
+                                      pl->d_near_flag)),
+                     "final_l1_l0", fbytes + ne * p3 * us, fflops);
+        } else {
+            // the level-1 inverse and Interp from level 2 on the way
+            const bool lists = L.pairs() > 0, above = pl->Ltop >= 2;
+            LGF_STEP(s,
+                     (launch_final_far<T>(u, lists ? (const C*)L.d_uhat : nullptr, L.nint,
+                                          above ? (const U*)pl->lv[2].d_util : nullptr, L.d_par, pl->d_C01, pl->d_A,
+                                          u, pl->neval, n, p, s, pl->d_eval_l1, pl->d_near_flag)),
+                     "final_l1_l0",
+                     fbytes + (lists ? ne * Sl(1) * cs : 0.0) + (above ? lvN(2) * p3 * us : 0.0),
+                     fflops + (lists ? ne * fft_flops(2 * p) : 0.0) + (above ? ne * 6.0 * p3 * p : 0.0));
+        }
     }
     mark.solve_end(s);
 #undef LGF_STEP
@@ -568,7 +542,6 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
         pl->lv[l].sib_pairs = H.lv[l].sib_pairs;
         pl->lv[l].csr_entries = (int64_t)H.lv[l].csr_src.size();
         pl->lv[l].ncsr = (int64_t)H.lv[l].csr_tgt.size();
-        pl->lv[l].zero_uhat = H.lv[l].zero_uhat;
     }
     // ---- kernel spectra (shared cache): radius 1 at level 0, 3 for the sibling kernel,
     //      the CSR offsets' own radius for a truncated top level
@@ -632,7 +605,9 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     for (int l = 1; ok && l <= pl->Ltop; ++l) {
         LevelPlan& Lv = pl->lv[l];
         const HostLevel& h = H.lv[l];
-        ok = dev_alloc(pl, &Lv.d_ftil, Lv.nint * p3 * esz) && dev_alloc(pl, &Lv.d_util, Lv.nint * p3 * usz);
+        ok = (!needs_ftil(H, l) || dev_alloc(pl, &Lv.d_ftil, Lv.nint * p3 * esz)) &&
+             (!needs_util(H, l) || dev_alloc(pl, &Lv.d_util, Lv.nint * p3 * usz)) &&
+             dev_alloc(pl, &Lv.d_par, (int64_t)h.par.size() * 4);
         if (ok && h.pairs() > 0 && l == 1 && H.lat1)
             ok = dev_alloc(pl, &Lv.d_uhat, Lv.nint * S0 * 2 * esz);  // sources: the level-0 spectra
         else if (ok && h.pairs() > 0)
@@ -665,7 +640,8 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     if (e == hipSuccess) e = upload(pl->d_near_flag, H.near_flag, s);
     for (int l = 1; e == hipSuccess && l <= pl->Ltop; ++l) {
         LevelPlan& Lv = pl->lv[l];
-        if (Lv.d_csr_tgt) {
+        e = upload(Lv.d_par, H.lv[l].par, s);
+        if (e == hipSuccess && Lv.d_csr_tgt) {
             e = upload(Lv.d_csr_tgt, H.lv[l].csr_tgt, s);
             if (e == hipSuccess) e = upload(Lv.d_csr_ptr, H.lv[l].csr_ptr, s);
             if (e == hipSuccess) e = upload(Lv.d_csr_src, H.lv[l].csr_src, s);
@@ -686,10 +662,15 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     if (e == hipSuccess) e = zero_fill(pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz, s);
     // level-1 fields of the union intervals that are not sources stay zero (Reg writes the
     // first nsrc only)
-    if (e == hipSuccess && pl->Ltop >= 1 && nb > H.nsrc)
+    if (e == hipSuccess && pl->Ltop >= 1 && pl->lv[1].d_ftil && nb > H.nsrc)
         e = zero_fill((char*)pl->lv[1].d_ftil + H.nsrc * p3 * esz, (nb - H.nsrc) * p3 * esz, s);
     for (int l = 1; e == hipSuccess && l <= pl->Ltop; ++l)
         if (pl->lv[l].d_fhat) e = zero_fill(pl->lv[l].d_fhat, (pl->lv[l].nint + 1) * S1 * 2 * esz, s);
+    // fields that neither list kind serves (a union's layouts without top-level entries) stay
+    // zero: no Prod writes them
+    for (int l = 1; e == hipSuccess && l <= pl->Ltop; ++l)
+        if (H.lv[l].zero_uhat && pl->lv[l].d_uhat)
+            e = zero_fill(pl->lv[l].d_uhat, pl->lv[l].nint * (l == 1 && H.lat1 ? S0 : S1) * 2 * esz, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(LGF_ERR_DEVICE, std::string("plan upload failed: ") + hipGetErrorString(e));
     return LGF_OK;
