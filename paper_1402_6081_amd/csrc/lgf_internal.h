@@ -223,21 +223,24 @@ struct TuneConfig {
     int overlap = 0;       // far-field chain on a second stream: 1 = yes, 2 = no, 0 = default (yes)
 };
 
+// The 1D matrices: A p x n and its transpose At n x p (blocks and level 1), C01 the two p x p
+// matrices C_0, C_1 (children and parent) and Ct their transposes, all row-major; Reg uses them
+// in the path's precision, the way down in double.
 // Reg block -> level-1 interval and its forward transform (p <= 10): ftil[b] = (A x A x A) f[b],
-// A is p x n (row-major), and its spectrum into item b of fhat (nout items); either output may
+// and its spectrum into item b of fhat (nout items); either output may
 // be NULL
 template <typename T>
-hipError_t launch_reg_fft(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
+hipError_t launch_reg_fft(const T* f, const T* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
                           hipStream_t s);
 // The same children -> parent: out[J] = sum_c (C_cz x C_cy x C_cx) in[child_c(J)]
 template <typename T>
-hipError_t launch_regup_fft(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat, int64_t np,
+hipError_t launch_regup_fft(const T* in, const int32_t* child8, const T* C01, T* ftil, cplx<T>* fhat, int64_t np,
                             int64_t nout, int p, hipStream_t s);
 // Inverse transform of a level's spectra (NULL: zeros) plus Interp from its parents (p <= 10):
 // out[i] = inverse of item i + (C_c^T x C_c^T x C_c^T) up[J], par[i] = 8 J + c (-1: no parent);
 // up = NULL: no parents
 template <typename T>
-hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* Ct,
                              double* out, int64_t nint, int p, hipStream_t s);
 // The same at level 1, and on to the blocks: u[b] = vnear[b] + (A^T x A^T x A^T) ut[q(b)] with ut
 // the level-1 node values, accumulated in FP64 (u may alias vnear); q(b) = l1map[b] (the level-1
@@ -245,23 +248,23 @@ hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_
 // read) where near_flag[b] == 0 (NULL: every block).  uhat holds nint items.
 template <typename T>
 hipError_t launch_final_far(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up, const int32_t* par,
-                            const double* C01, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
+                            const double* Ct, const double* At, T* u, int64_t nb, int n, int p, hipStream_t s,
                             const int32_t* l1map, const int32_t* near_flag);
 
 // The lattice scheme (p = 13 and 17), whose node tiles do not fit those kernels:
 // Reg children -> parent; scratch: nparent * 8 * p^3 values of T (the children's partial sums)
 template <typename T>
-hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, T* out, int64_t nparent, int p,
+hipError_t launch_reg_up(const T* in, const int32_t* child8, const T* C01, T* out, int64_t nparent, int p,
                          hipStream_t s, void* scratch);
 // Level-1 node values: out[b] (p^3) = f[b] (n^3) padded with zeros
 template <typename T>
 hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStream_t s);
 // Interp parent -> its children, accumulate: io[child8[J][c]] += (C_c^T x C_c^T x C_c^T) par[J]
-hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
+hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* Ct, double* io,
                               int64_t nparent, int p, hipStream_t s);
 // Final pass as above from node values ut
 template <typename T>
-hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p,
+hipError_t launch_final(const T* vnear, const double* ut, const double* At, T* u, int64_t nb, int n, int p,
                         hipStream_t s, const int32_t* l1map = nullptr, const int32_t* near_flag = nullptr);
 
 // ------------------------------------------------------------------ kernel spectra

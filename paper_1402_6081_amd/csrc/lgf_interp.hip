@@ -9,7 +9,16 @@
 // node values in LDS also transforms them: Reg goes on to the level's forward transform, the
 // level's inverse transform to Interp from the parent, and at level 1 on to the block, so the node
 // values of level 1 are not written to HBM on the way down, and each step is one launch less.
-// The passes are latency-bound (a few barriers over little data).
+//
+// A pass is a small matrix applied along one axis (contract below): a lane holds one column of
+// inputs in registers and forms several outputs with the matrix values in scalar registers, so
+// that a multiply-add needs no LDS read of its own (one thread per output, reading a value and a
+// matrix entry from LDS for each multiply-add, made the passes LDS-bound).  On a 256^3 cube of
+// 16^3 blocks, p = 8, from one output per thread to this, FP64 and FP32: Reg to level 1 with its
+// transform 85 to 55 us (its 0.30 GB take 53 at a copy's rate) and 45 to 31, Reg up 25 to 17 and
+// 14 to 11, the final pass with its transform and Interp 106 to 77 (0.42 GB: 74) and 85 to 66
+// (node values and their passes stay in double there); at p = 17, FP64, 128^3: Reg up 63 to 36,
+// Interp down 50 to 31, the final pass 30 to 22.
 #include <type_traits>
 
 #include "lgf_internal.h"
@@ -17,128 +26,149 @@
 
 namespace lgfdev {
 
-constexpr int kInterpThreads = 256;
 // Reg up works on eight children per workgroup: more waves hide the latency of its few, long
 // workgroups
 constexpr int kRegUpThreads = 1024;
 // block -> level 1
-constexpr int kBlockThreads = 512;
-// Interp down of the lattice scheme (one workgroup per (parent, child))
-constexpr int kDownThreads = 512;
+constexpr int kBlockThreads = 256;
+// the lattice scheme's Reg up, Interp down and final pass: two waves per 64 of the 17^2 columns
+constexpr int kLatThreads = 640;
+constexpr int kSumThreads = 256;
 // inverse transform, Interp and the final pass
 constexpr int kInvThreads = 256;
 
 constexpr int imax(int a, int b) { return a > b ? a : b; }
 
+// Matrices of the plan, read at wave-uniform indices through scalar loads (constant address
+// space: they do not change during a launch).
+template <typename T>
+using Uniform = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ Uniform<T> uniform_ptr(const T* p) {
+    return (Uniform<T>)(uintptr_t)p;
+}
+
+// One pass of W waves over C columns: put(col, o, sum_k mat[o * IN + k] * load(col, k), base(col, o))
+// for o < OUT, the sum in increasing k.  A wave takes 64 columns, one per lane, and all their
+// outputs, or, with fewer groups of columns than waves, a share of the outputs; base, what the
+// outputs are added to, is read for all of them before the first is written.  mat is row-major
+// [OUT][IN] and wave-uniform.
+template <int IN, int OUT, int C, int W, typename T, typename Load, typename Base, typename Put>
+__device__ __forceinline__ void contract_onto(int wave, int lane, Uniform<T> mat, Load load, Base base, Put put) {
+    constexpr int G = (C + 63) / 64, CH = W >= 2 * G ? (OUT + W / G - 1) / (W / G) : OUT;
+    constexpr int SPLIT = (OUT + CH - 1) / CH;  // shares of CH outputs, the last one with the rest
+    static_assert(SPLIT * CH >= OUT && (SPLIT - 1) * CH < OUT && (SPLIT == 1 || G * SPLIT <= W), "shares");
+    for (int task = wave; task < G * SPLIT; task += W) {
+        const int col = task % G * 64 + lane, o0 = task / G * CH;
+        const bool on = C % 64 == 0 || col < C;
+        using B = std::remove_reference_t<decltype(base(0, 0))>;
+        B b[CH];
+        T v[IN];
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            b[i] = on && (SPLIT * CH == OUT || o0 + i < OUT) ? base(col, o0 + i) : B(0);
+#pragma unroll
+        for (int k = 0; k < IN; ++k) v[k] = on ? load(col, k) : T(0);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int o = o0 + i;
+            if (SPLIT * CH != OUT && o >= OUT) break;
+            T acc = T(0);
+#pragma unroll
+            for (int k = 0; k < IN; ++k) acc += mat[o * IN + k] * v[k];
+            if (on) put(col, o, acc, b[i]);
+        }
+    }
+}
+template <int IN, int OUT, int C, int W, typename T, typename Load, typename Put>
+__device__ __forceinline__ void contract(int wave, int lane, Uniform<T> mat, Load load, Put put) {
+    contract_onto<IN, OUT, C, W, T>(
+        wave, lane, mat, load, [](int, int) { return 0; }, [&](int col, int o, T v, int) { put(col, o, v); });
+}
+
 // ------------------------------------------------------------------ block -> level 1
-// One workgroup per block: the block is staged in LDS with coalesced loads, then the
-// three passes run from LDS with compile-time extents, and the forward transform of the node
-// values.  Rows that a wave reads at several indices at once (the block's x rows, the matrix
-// rows) are padded to N + 1 values, so the reads fall into different LDS banks.
+// One workgroup per block.  A: [P][N].
 template <typename T, int N, int P>
 __global__ void __launch_bounds__(kBlockThreads)
-    k_reg_fft(const T* __restrict__ f, const double* __restrict__ A, T* __restrict__ ftil,
-              cplx<T>* __restrict__ fhat, int64_t nout) {
-    constexpr int N3 = N * N * N, P3 = P * P * P, NR = N + 1;
-    constexpr int kX = N * N * NR, kT1 = N * N * P, kT2 = N * P * P;
-    constexpr int kFront = (imax(kX + kT1, 2 * tile_values<P>()) + 1) / 2 * 2;  // X and t1, then the transform
-    __shared__ alignas(16) T lds[kFront + kT2 + P * NR];
-    T *X = lds, *t1 = lds + kX, *t2 = lds + kFront, *Am = t2 + kT2;
+    k_reg_fft(const T* __restrict__ f, const T* __restrict__ A, T* __restrict__ ftil, cplx<T>* __restrict__ fhat,
+              int64_t nout) {
+    constexpr int N3 = N * N * N, P3 = P * P * P, W = kBlockThreads / 64;
+    // t1[d][z][y] and t2[z][c][d], rows padded so that the lanes' columns fall into different banks
+    constexpr int kZ = N + 1, kD = N * kZ + 1, kS = P * P + 4;
+    constexpr int kFront = (imax(P * kD, 2 * tile_values<P>()) + 1) / 2 * 2;  // t1, then the transform
+    __shared__ alignas(16) T lds[kFront + N * kS];
+    T *t1 = lds, *t2 = lds + kFront;
     cplx<T>* buf = reinterpret_cast<cplx<T>*>(lds);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t b = blockIdx.x;
-    for (int i = tid; i < P * N; i += kBlockThreads) Am[(i / N) * NR + i % N] = (T)A[i];
+    const Uniform<T> m = uniform_ptr(A);
     const T* src = f + b * N3;
-    for (int i = tid; i < N3; i += kBlockThreads) X[(i / N) * NR + i % N] = src[i];
+    contract<N, P, N * N, W, T>(
+        wave, lane, m, [&](int zy, int x) { return src[zy * N + x]; },
+        [&](int zy, int d, T v) { t1[d * kD + zy / N * kZ + zy % N] = v; });
     __syncthreads();
-    for (int i = tid; i < N * N * P; i += kBlockThreads) {  // x: t1[z][y][d]
-        const int d = i % P, zy = i / P;
-        const T* row = X + zy * NR;
-        const T* m = Am + d * NR;
-        T acc = T(0);
-#pragma unroll
-        for (int x = 0; x < N; ++x) acc += m[x] * row[x];
-        t1[i] = acc;
-    }
+    contract<N, P, N * P, W, T>(
+        wave, lane, m, [&](int zd, int y) { return t1[zd % P * kD + zd / P * kZ + y]; },
+        [&](int zd, int c, T v) { t2[zd / P * kS + c * P + zd % P] = v; });
     __syncthreads();
-    for (int i = tid; i < N * P * P; i += kBlockThreads) {  // y: t2[z][c][d]
-        const int d = i % P, c = (i / P) % P, z = i / (P * P);
-        const T* m = Am + c * NR;
-        const T* col = t1 + z * N * P + d;
-        T acc = T(0);
-#pragma unroll
-        for (int y = 0; y < N; ++y) acc += m[y] * col[y * P];
-        t2[i] = acc;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += kBlockThreads) {  // z: node values [a][c][d]
-        const int cd = i % (P * P), a = i / (P * P);
-        const T* m = Am + a * NR;
-        T acc = T(0);
-#pragma unroll
-        for (int z = 0; z < N; ++z) acc += m[z] * t2[z * (P * P) + cd];
-        if (ftil) ftil[b * P3 + i] = acc;
-        staged<T, P>(buf, a, cd / P, cd % P) = acc;
-    }
+    contract<N, P, P * P, W, T>(
+        wave, lane, m, [&](int cd, int z) { return t2[z * kS + cd]; },
+        [&](int cd, int a, T v) {
+            if (ftil) ftil[b * P3 + a * (P * P) + cd] = v;
+            staged<T, P>(buf, a, cd / P, cd % P) = v;
+        });
     if (!fhat) return;
     __syncthreads();
     tile_forward<T, P, kBlockThreads>(buf, tid, fhat, (size_t)b, nout);
 }
 
 // ------------------------------------------------------------------ children -> parent
+// C01: [2][P][P].
 template <typename T, int P>
 __global__ void __launch_bounds__(kRegUpThreads)
-    k_regup_fft(const T* __restrict__ in, const int32_t* __restrict__ child8, const double* __restrict__ C01,
+    k_regup_fft(const T* __restrict__ in, const int32_t* __restrict__ child8, const T* __restrict__ C01,
                 T* __restrict__ ftil, cplx<T>* __restrict__ fhat, int64_t nout) {
-    constexpr int P3 = P * P * P, NT = kRegUpThreads;
-    static_assert(8 * P3 >= 2 * tile_values<P>(), "the transform's tile fits in t1");
-    __shared__ alignas(16) T X[8 * P3], t1[8 * P3];
-    __shared__ T Cm[2 * P * P];
-    __shared__ int32_t ch[8];
+    constexpr int P2 = P * P, P3 = P2 * P, NT = kRegUpThreads, W = NT / 64;
+    constexpr int kD = P2 + 1, kC1 = P * kD;   // t1[c][d][z y]
+    constexpr int kZ2 = P2 + 4, kC2 = P * kZ2;  // t2[c][z][b d]
+    __shared__ alignas(16) T t1[imax(8 * kC1, 2 * tile_values<P>())], t2[8 * kC2];
     cplx<T>* buf = reinterpret_cast<cplx<T>*>(t1);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t J = blockIdx.x;
-    for (int i = tid; i < 2 * P * P; i += NT) Cm[i] = (T)C01[i];
-    if (tid < 8) ch[tid] = child8[J * 8 + tid];
-    __syncthreads();
-    for (int i = tid; i < 8 * P3; i += NT) {
-        const int c = i / P3, r = i - c * P3;
-        const int q = ch[c];
-        X[i] = q >= 0 ? in[(int64_t)q * P3 + r] : T(0);
+    const Uniform<T> m = uniform_ptr(C01);
+    const Uniform<int32_t> ch = uniform_ptr(child8 + J * 8);
+    // two waves per child
+    constexpr int WC = W / 8;
+    const int c = wave / WC, wc = wave % WC, q = ch[c];
+    if (q >= 0) {  // x: t1[d][z y] = sum_x C_cx[d][x] in[z y][x]
+        const T* src = in + (int64_t)q * P3;
+        T* d1 = t1 + c * kC1;
+        contract<P, P, P2, WC, T>(
+            wc, lane, m + (c & 1) * P2, [&](int zy, int x) { return src[zy * P + x]; },
+            [&](int zy, int d, T v) { d1[d * kD + zy] = v; });
     }
     __syncthreads();
-    // x: t1[c][z][y][d] = sum_x C_cx[d][x] X[c][z][y][x]
-    for (int i = tid; i < 8 * P3; i += NT) {
-        const int d = i % P, rest = i / P, c = i / P3;
-        const T* m = Cm + (c & 1) * P * P + d * P;
-        const T* row = X + rest * P;
-        T s = T(0);
-#pragma unroll
-        for (int x = 0; x < P; ++x) s += m[x] * row[x];
-        t1[i] = s;
+    if (q >= 0) {  // y: t2[z][b d] = sum_y C_cy[b][y] t1[d][z y]
+        const T* s1 = t1 + c * kC1;
+        T* d2 = t2 + c * kC2;
+        contract<P, P, P2, WC, T>(
+            wc, lane, m + ((c >> 1) & 1) * P2, [&](int zd, int y) { return s1[zd % P * kD + zd / P * P + y]; },
+            [&](int zd, int b, T v) { d2[zd / P * kZ2 + b * P + zd % P] = v; });
     }
     __syncthreads();
-    // y: X[c][z][b][d] = sum_y C_cy[b][y] t1[c][z][y][d]
-    for (int i = tid; i < 8 * P3; i += NT) {
-        const int d = i % P, bb = (i / P) % P, cz = i / (P * P), c = i / P3;
-        const T* m = Cm + ((c >> 1) & 1) * P * P + bb * P;
+    // z and the sum over children: node values [a][b d] = sum_c sum_z C_cz[a][z] t2[c][z][b d]
+    constexpr int G = (P2 + 63) / 64;
+    for (int task = wave; task < G * P; task += W) {
+        const int bd = task % G * 64 + lane, a = task / G;
+        if (P2 % 64 != 0 && bd >= P2) continue;
         T s = T(0);
+        for (int cc = 0; cc < 8; ++cc) {
+            if (ch[cc] < 0) continue;
+            const Uniform<T> row = m + ((cc >> 2) & 1) * P2 + a * P;
 #pragma unroll
-        for (int y = 0; y < P; ++y) s += m[y] * t1[(cz * P + y) * P + d];
-        X[i] = s;
-    }
-    __syncthreads();
-    // z and the sum over children: node values [a][b][d] = sum_c sum_z C_cz[a][z] X[c][z][b][d]
-    for (int i = tid; i < P3; i += NT) {
-        const int bd = i % (P * P), a = i / (P * P);
-        T s = T(0);
-        for (int c = 0; c < 8; ++c) {
-            if (ch[c] < 0) continue;
-            const T* m = Cm + ((c >> 2) & 1) * P * P + a * P;
-#pragma unroll
-            for (int z = 0; z < P; ++z) s += m[z] * X[c * P3 + z * P * P + bd];
+            for (int z = 0; z < P; ++z) s += row[z] * t2[cc * kC2 + z * kZ2 + bd];
         }
-        if (ftil) ftil[J * P3 + i] = s;
+        if (ftil) ftil[J * P3 + a * P2 + bd] = s;
         staged<T, P>(buf, a, bd / P, bd % P) = s;
     }
     if (!fhat) return;
@@ -147,24 +177,37 @@ __global__ void __launch_bounds__(kRegUpThreads)
 }
 
 // ------------------------------------------------------------------ inverse and parent -> child
+// Interp of a parent's node values (in HBM) to its child c: at(yx, z) += its value for every node
+// z, y x of the child (yx = y P + x).  Ct: [2][P][P], Ct_c[k][m] = C_c[m][k]; R: interp_values<P>() doubles.
+template <int P>
+constexpr int interp_values() { return P * (P * P + 1) + P * (P * P + 4); }
+template <int P, int W, typename At>
+__device__ __forceinline__ void interp_child(const double* __restrict__ src, int c, Uniform<double> Ct, double* R,
+                                             int wave, int lane, At at) {
+    constexpr int P2 = P * P, kX = P2 + 1, kA = P2 + 4;
+    double *t1 = R, *t2 = R + P * kX;  // t1[x'][a b], t2[a][y' x']
+    contract<P, P, P2, W, double>(
+        wave, lane, Ct + (c & 1) * P2, [&](int ab, int d) { return src[ab * P + d]; },
+        [&](int ab, int x, double v) { t1[x * kX + ab] = v; });
+    __syncthreads();
+    contract<P, P, P2, W, double>(
+        wave, lane, Ct + ((c >> 1) & 1) * P2, [&](int ax, int bb) { return t1[ax % P * kX + ax / P * P + bb]; },
+        [&](int ax, int y, double v) { t2[ax / P * kA + y * P + ax % P] = v; });
+    __syncthreads();
+    contract_onto<P, P, P2, W, double>(
+        wave, lane, Ct + ((c >> 2) & 1) * P2, [&](int yx, int a) { return t2[a * kA + yx]; }, at,
+        [&](int yx, int z, double v, double before) { at(yx, z) = before + v; });
+}
+
 // The node values of interval q (rows of P values, VP apart) into V: the inverse transform of its
 // field spectrum (uhat NULL: zeros) plus Interp from its parent (par[q] = 8 J + c, -1: none;
-// up NULL: no level above).  R: 2 tile_values<P>() doubles, Xp: P^3, Ct: 2 P^2, used on the way.
+// up NULL: no level above).  R: max(2 tile_values, interp_values) doubles.
 template <typename T, int P, int VP, int NT>
 __device__ __forceinline__ void node_values(const cplx<T>* __restrict__ uhat, int64_t nint,
                                             const double* __restrict__ up, const int32_t* __restrict__ par,
-                                            const double* __restrict__ C01, int64_t q, double* R, double* Xp,
-                                            double* Ct, double* V, int tid) {
+                                            Uniform<double> Ct, int64_t q, double* R, double* V, int tid) {
     constexpr int P3 = P * P * P, P2 = P * P;
-    static_assert(tile_values<P>() >= P3, "the two passes' values fit in R");
-    const int pc = up ? par[q] : -1;  // uniform
-    if (pc >= 0) {
-        for (int i = tid; i < P3; i += NT) Xp[i] = up[(int64_t)(pc >> 3) * P3 + i];
-        for (int i = tid; i < 2 * P2; i += NT) {  // Ct_c[k][m] = C_c[m][k]
-            const int cc = i / P2, r = i % P2, k = r / P, m = r % P;
-            Ct[i] = C01[cc * P2 + m * P + k];
-        }
-    }
+    const int pc = up ? uniform_ptr(par)[q] : -1;  // uniform
     if (uhat) {
         cplx<double>* buf = reinterpret_cast<cplx<double>*>(R);
         tile_inverse<T, double, P, NT>(uhat, (size_t)q, nint, buf, tid);
@@ -175,49 +218,21 @@ __device__ __forceinline__ void node_values(const cplx<T>* __restrict__ uhat, in
     }
     __syncthreads();
     if (pc < 0) return;
-    const int cx = pc & 1, cy = (pc >> 1) & 1, cz = (pc >> 2) & 1;
-    double *t1 = R, *t2 = R + P3;
-    for (int i = tid; i < P3; i += NT) {  // x: t1[a][b][x']
-        const int xo = i % P, ab = i / P;
-        const double* m = Ct + cx * P2 + xo * P;
-        const double* row = Xp + ab * P;
-        double sum = 0.0;
-#pragma unroll
-        for (int d = 0; d < P; ++d) sum += m[d] * row[d];
-        t1[i] = sum;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += NT) {  // y: t2[a][y'][x']
-        const int xo = i % P, yo = (i / P) % P, a = i / P2;
-        const double* m = Ct + cy * P2 + yo * P;
-        const double* src = t1 + a * P2 + xo;
-        double sum = 0.0;
-#pragma unroll
-        for (int bb = 0; bb < P; ++bb) sum += m[bb] * src[bb * P];
-        t2[i] = sum;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += NT) {  // z, added to the interval's own values
-        const int yx = i % P2, zo = i / P2;
-        const double* m = Ct + cz * P2 + zo * P;
-        double sum = 0.0;
-#pragma unroll
-        for (int a = 0; a < P; ++a) sum += m[a] * t2[a * P2 + yx];
-        double* v = V + (i / P) * VP + i % P;
-        *v = *v + sum;
-    }
+    interp_child<P, NT / 64>(up + (int64_t)(pc >> 3) * P3, pc & 7, Ct, R, __builtin_amdgcn_readfirstlane(tid >> 6),
+                             tid & 63,
+                             [&](int yx, int z) -> double& { return V[(z * P + yx / P) * VP + yx % P]; });
     __syncthreads();
 }
 
 template <typename T, int P>
 __global__ void __launch_bounds__(kInvThreads)
     k_inv_interp(const cplx<T>* __restrict__ uhat, const double* __restrict__ up, const int32_t* __restrict__ par,
-                 const double* __restrict__ C01, double* __restrict__ out) {
+                 const double* __restrict__ Ct, double* __restrict__ out) {
     constexpr int P3 = P * P * P;
-    __shared__ alignas(16) double R[2 * tile_values<P>()];
-    __shared__ double Xp[P3], Ct[2 * P * P], V[P3];
+    __shared__ alignas(16) double R[imax(2 * tile_values<P>(), interp_values<P>())];
+    __shared__ double V[P3];
     const int64_t q = blockIdx.x;
-    node_values<T, P, P, kInvThreads>(uhat, gridDim.x, up, par, C01, q, R, Xp, Ct, V, threadIdx.x);
+    node_values<T, P, P, kInvThreads>(uhat, gridDim.x, up, par, uniform_ptr(Ct), q, R, V, threadIdx.x);
     for (int i = threadIdx.x; i < P3; i += kInvThreads) out[q * P3 + i] = V[i];
 }
 
@@ -229,55 +244,37 @@ __global__ void __launch_bounds__(kInvThreads)
 //                k_reg_up_sum adds them in child order c = 0..7 (as one workgroup would);
 //   Interp down: each child accumulates its own values (no two workgroups write one child).
 template <typename T, int P>
-__global__ void __launch_bounds__(kInterpThreads)
-    k_reg_up_part(const T* __restrict__ in, const int32_t* __restrict__ child8, const double* __restrict__ C01,
+__global__ void __launch_bounds__(kLatThreads)
+    k_reg_up_part(const T* __restrict__ in, const int32_t* __restrict__ child8, const T* __restrict__ C01,
                   T* __restrict__ part) {
-    constexpr int P3 = P * P * P;
-    __shared__ T X[P3], t1[P3];
-    __shared__ T Cm[2 * P * P];
-    const int tid = threadIdx.x;
+    constexpr int P2 = P * P, P3 = P2 * P, W = kLatThreads / 64, kD = P2 + 1, kZ = P2 + 4;
+    __shared__ T t1[P * kD], t2[P * kZ];  // t1[d][z y], t2[z][b d]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t J = blockIdx.x >> 3;
     const int c = blockIdx.x & 7;
     const int q = child8[J * 8 + c];  // uniform
     if (q < 0) return;
-    for (int i = tid; i < 2 * P * P; i += kInterpThreads) Cm[i] = (T)C01[i];
-    for (int i = tid; i < P3; i += kInterpThreads) X[i] = in[(int64_t)q * P3 + i];
+    const Uniform<T> m = uniform_ptr(C01);
+    const T* src = in + (int64_t)q * P3;
+    contract<P, P, P2, W, T>(
+        wave, lane, m + (c & 1) * P2, [&](int zy, int x) { return src[zy * P + x]; },
+        [&](int zy, int d, T v) { t1[d * kD + zy] = v; });
     __syncthreads();
-    for (int i = tid; i < P3; i += kInterpThreads) {  // x: t1[z][y][d]
-        const int d = i % P, rest = i / P;
-        const T* m = Cm + (c & 1) * P * P + d * P;
-        const T* row = X + rest * P;
-        T sum = T(0);
-#pragma unroll
-        for (int x = 0; x < P; ++x) sum += m[x] * row[x];
-        t1[i] = sum;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += kInterpThreads) {  // y: X[z][b][d]
-        const int d = i % P, bb = (i / P) % P, z = i / (P * P);
-        const T* m = Cm + ((c >> 1) & 1) * P * P + bb * P;
-        T sum = T(0);
-#pragma unroll
-        for (int y = 0; y < P; ++y) sum += m[y] * t1[(z * P + y) * P + d];
-        X[i] = sum;
-    }
+    contract<P, P, P2, W, T>(
+        wave, lane, m + ((c >> 1) & 1) * P2, [&](int zd, int y) { return t1[zd % P * kD + zd / P * P + y]; },
+        [&](int zd, int b, T v) { t2[zd / P * kZ + b * P + zd % P] = v; });
     __syncthreads();
     T* o = part + (J * 8 + c) * P3;
-    for (int i = tid; i < P3; i += kInterpThreads) {  // z
-        const int bd = i % (P * P), a = i / (P * P);
-        const T* m = Cm + ((c >> 2) & 1) * P * P + a * P;
-        T sum = T(0);
-#pragma unroll
-        for (int z = 0; z < P; ++z) sum += m[z] * X[z * P * P + bd];
-        o[i] = sum;
-    }
+    contract<P, P, P2, W, T>(
+        wave, lane, m + ((c >> 2) & 1) * P2, [&](int bd, int z) { return t2[z * kZ + bd]; },
+        [&](int bd, int a, T v) { o[a * P2 + bd] = v; });
 }
 
 template <typename T, int P>
-__global__ void __launch_bounds__(kInterpThreads)
+__global__ void __launch_bounds__(kSumThreads)
     k_reg_up_sum(const T* __restrict__ part, const int32_t* __restrict__ child8, T* __restrict__ out, int64_t np) {
     constexpr int P3 = P * P * P;
-    const int64_t g = (int64_t)blockIdx.x * kInterpThreads + threadIdx.x;
+    const int64_t g = (int64_t)blockIdx.x * kSumThreads + threadIdx.x;
     if (g >= np * P3) return;
     const int64_t J = g / P3;
     const int i = (int)(g - J * P3);
@@ -288,53 +285,19 @@ __global__ void __launch_bounds__(kInterpThreads)
 }
 
 template <int P>
-__global__ void __launch_bounds__(kDownThreads)
-    k_interp_down_one(const double* __restrict__ par, const int32_t* __restrict__ child8, const double* __restrict__ C01,
-                      double* __restrict__ io) {
-    constexpr int P3 = P * P * P;
-    __shared__ double X[P3], t1[P3], t2[P3];
-    __shared__ double Ct[2 * P * P];  // Ct_c[k][m] = C_c[m][k]
-    const int tid = threadIdx.x;
+__global__ void __launch_bounds__(kLatThreads)
+    k_interp_down_one(const double* __restrict__ par, const int32_t* __restrict__ child8,
+                      const double* __restrict__ Ct, double* __restrict__ io) {
+    constexpr int P2 = P * P, P3 = P2 * P;
+    __shared__ double R[interp_values<P>()];
     const int64_t J = blockIdx.x >> 3;
     const int c = blockIdx.x & 7;
     const int q = child8[J * 8 + c];  // uniform
     if (q < 0) return;
-    const int cx = c & 1, cy = (c >> 1) & 1, cz = (c >> 2) & 1;
-    for (int i = tid; i < 2 * P * P; i += kDownThreads) {
-        const int cc = i / (P * P), r = i % (P * P), k = r / P, m = r % P;
-        Ct[i] = C01[cc * P * P + m * P + k];
-    }
-    for (int i = tid; i < P3; i += kDownThreads) X[i] = par[J * P3 + i];
-    __syncthreads();
-    for (int i = tid; i < P3; i += kDownThreads) {  // x: t1[a][b][x']
-        const int xo = i % P, ab = i / P;
-        const double* m = Ct + cx * P * P + xo * P;
-        const double* row = X + ab * P;
-        double sum = 0.0;
-#pragma unroll
-        for (int d = 0; d < P; ++d) sum += m[d] * row[d];
-        t1[i] = sum;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += kDownThreads) {  // y: t2[a][y'][x']
-        const int xo = i % P, yo = (i / P) % P, a = i / (P * P);
-        const double* m = Ct + cy * P * P + yo * P;
-        const double* src = t1 + a * P * P + xo;
-        double sum = 0.0;
-#pragma unroll
-        for (int bb = 0; bb < P; ++bb) sum += m[bb] * src[bb * P];
-        t2[i] = sum;
-    }
-    __syncthreads();
-    for (int i = tid; i < P3; i += kDownThreads) {  // z, accumulated into the child
-        const int yx = i % (P * P), zo = i / (P * P);
-        const double* m = Ct + cz * P * P + zo * P;
-        double sum = 0.0;
-#pragma unroll
-        for (int a = 0; a < P; ++a) sum += m[a] * t2[a * P * P + yx];
-        double* dst = io + (int64_t)q * P3 + i;
-        *dst = *dst + sum;
-    }
+    double* dst = io + (int64_t)q * P3;
+    interp_child<P, kLatThreads / 64>(par + J * P3, c, uniform_ptr(Ct), R,
+                                      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63,
+                                      [&](int yx, int z) -> double& { return dst[z * P2 + yx]; });
 }
 
 // Level-1 node values of the lattice scheme (p = n + 1 nodes on the grid points, Reg the
@@ -351,49 +314,29 @@ __global__ void k_pad_copy(const T* __restrict__ f, T* __restrict__ out, int64_t
 }
 
 // ------------------------------------------------------------------ level 1 -> block, FP64 add-back
-// u[b] from the level-1 node values X (rows of P values, P + 1 apart: rows that a wave reads at
-// several indices at once fall into different LDS banks).  At: N (P + 1) values, the rows of A^T;
-// t1: P^2 N, t2: P N^2.  At and X are visible to the workgroup.
-template <typename T, int N, int P, int NT>
-__device__ __forceinline__ void final_passes(const double* X, const double* At, double* t1, double* t2,
-                                             const T* vnear, T* u, int64_t b, bool has_near, int tid) {
-    constexpr int N3 = N * N * N, PR = P + 1;
-    for (int i = tid; i < P * P * N; i += NT) {  // x: t1[a][c][x]
-        const int x = i % N, ac = i / N;
-        const double* m = At + x * PR;
-        const double* row = X + ac * PR;
-        double acc = 0.0;
-#pragma unroll
-        for (int d = 0; d < P; ++d) acc += m[d] * row[d];
-        t1[i] = acc;
-    }
+// u[b] from the level-1 node values V (LDS, rows of P values, P + 1 apart; visible to the
+// workgroup).  At: [N][P], the rows of A^T; R: final_values<N, P>() doubles.
+template <int N, int P>
+constexpr int final_values() { return P * P * (N + 1) + P * (N * N + 8); }
+template <typename T, int N, int P, int W>
+__device__ __forceinline__ void final_passes(const double* V, Uniform<double> At, double* R, const T* vnear, T* u,
+                                             int64_t b, bool has_near, int wave, int lane) {
+    constexpr int N2 = N * N, kX = N + 1, kA = N2 + 8;
+    double *t1 = R, *t2 = R + P * P * kX;  // t1[a c][x], t2[a][y x]
+    contract<P, N, P * P, W, double>(
+        wave, lane, At, [&](int ac, int d) { return V[ac * (P + 1) + d]; },
+        [&](int ac, int x, double v) { t1[ac * kX + x] = v; });
     __syncthreads();
-    for (int i = tid; i < P * N * N; i += NT) {  // y: t2[a][y][x]
-        const int x = i % N, y = (i / N) % N, a = i / (N * N);
-        const double* m = At + y * PR;
-        const double* col = t1 + a * P * N + x;
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < P; ++c) acc += m[c] * col[c * N];
-        t2[i] = acc;
-    }
+    contract<P, N, P * N, W, double>(
+        wave, lane, At, [&](int ax, int c) { return t1[(ax / N * P + c) * kX + ax % N]; },
+        [&](int ax, int y, double v) { t2[ax / N * kA + y * N + ax % N] = v; });
     __syncthreads();
-    const T* v = vnear + b * N3;
-    T* o = u + b * N3;
-    for (int i = tid; i < N3; i += NT) {  // z: u[z][y][x]
-        const int yx = i % (N * N), z = i / (N * N);
-        const double* m = At + z * PR;
-        double acc = 0.0;
-#pragma unroll
-        for (int a = 0; a < P; ++a) acc += m[a] * t2[a * N * N + yx];
-        o[i] = (T)((has_near ? (double)v[i] : 0.0) + acc);  // no near field: v is not read
-    }
-}
-
-// At[j][k] = A[k][j], rows P + 1 apart
-template <int N, int P, int NT>
-__device__ __forceinline__ void load_at(const double* __restrict__ A, double* At, int tid) {
-    for (int i = tid; i < N * P; i += NT) At[(i / P) * (P + 1) + i % P] = A[(i % P) * N + i / P];
+    const T* v = vnear + b * (N2 * N);
+    T* o = u + b * (N2 * N);
+    contract_onto<P, N, N2, W, double>(
+        wave, lane, At, [&](int yx, int a) { return t2[a * kA + yx]; },
+        [&](int yx, int z) { return has_near ? v[z * N2 + yx] : T(0); },  // no near field: v is not read
+        [&](int yx, int z, double acc, T near) { o[z * N2 + yx] = (T)((double)near + acc); });
 }
 
 // The level-1 inverse transform, Interp from level 2 and the interpolation to the block in one
@@ -401,34 +344,33 @@ __device__ __forceinline__ void load_at(const double* __restrict__ A, double* At
 template <typename T, int N, int P>
 __global__ void __launch_bounds__(kInvThreads)
     k_final_far(const T* vnear, const cplx<T>* __restrict__ uhat, int64_t nint, const double* __restrict__ up,
-                const int32_t* __restrict__ par, const double* __restrict__ C01, const double* __restrict__ A, T* u,
+                const int32_t* __restrict__ par, const double* __restrict__ Ct, const double* __restrict__ At, T* u,
                 const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
-    constexpr int P3 = P * P * P, kT1 = P * P * N;
-    __shared__ alignas(16) double R[imax(2 * tile_values<P>(), kT1 + P * N * N)];
-    __shared__ double Xp[P3], Ct[2 * P * P], V[P * P * (P + 1)], At[N * (P + 1)];
+    __shared__ alignas(16)
+        double R[imax(imax(2 * tile_values<P>(), interp_values<P>()), final_values<N, P>())];
+    __shared__ double V[P * P * (P + 1)];
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
-    const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
-    load_at<N, P, kInvThreads>(A, At, tid);
-    node_values<T, P, P + 1, kInvThreads>(uhat, nint, up, par, C01, q, R, Xp, Ct, V, tid);
-    final_passes<T, N, P, kInvThreads>(V, At, R, R + kT1, vnear, u, b, !near_flag || near_flag[b], tid);
+    const int64_t q = l1map ? (int64_t)uniform_ptr(l1map)[b] : b;  // level-1 interval of this block
+    node_values<T, P, P + 1, kInvThreads>(uhat, nint, up, par, uniform_ptr(Ct), q, R, V, tid);
+    final_passes<T, N, P, kInvThreads / 64>(V, uniform_ptr(At), R, vnear, u, b, !near_flag || near_flag[b],
+                                            __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
 }
 
 // From node values in HBM (the lattice scheme).
 template <typename T, int N, int P>
-__global__ void __launch_bounds__(kBlockThreads)
-    k_final(const T* vnear, const double* __restrict__ ut, const double* __restrict__ A, T* u,
+__global__ void __launch_bounds__(kLatThreads)
+    k_final(const T* vnear, const double* __restrict__ ut, const double* __restrict__ At, T* u,
             const int32_t* __restrict__ l1map, const int32_t* __restrict__ near_flag) {
     constexpr int P3 = P * P * P, PR = P + 1;
-    __shared__ double X[P * P * PR], t1[P * P * N], t2[P * N * N];
-    __shared__ double At[N * PR];
+    __shared__ double V[P * P * PR], R[final_values<N, P>()];
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
-    load_at<N, P, kBlockThreads>(A, At, tid);
-    const int64_t q = l1map ? (int64_t)l1map[b] : b;  // level-1 interval of this block
-    for (int i = tid; i < P3; i += kBlockThreads) X[(i / P) * PR + i % P] = ut[q * P3 + i];
+    const int64_t q = l1map ? (int64_t)uniform_ptr(l1map)[b] : b;  // level-1 interval of this block
+    for (int i = tid; i < P3; i += kLatThreads) V[(i / P) * PR + i % P] = ut[q * P3 + i];
     __syncthreads();
-    final_passes<T, N, P, kBlockThreads>(X, At, t1, t2, vnear, u, b, !near_flag || near_flag[b], tid);
+    final_passes<T, N, P, kLatThreads / 64>(V, uniform_ptr(At), R, vnear, u, b, !near_flag || near_flag[b],
+                                            __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -468,7 +410,7 @@ struct RegFft {
     struct K {
         template <int P>
         struct At {
-            static hipError_t run(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout,
+            static hipError_t run(const T* f, const T* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout,
                                   hipStream_t s) {
                 return lgf_launch(k_reg_fft<T, N, P>, dim3((unsigned)nb), dim3(kBlockThreads), 0, s, f, A, ftil, fhat,
                                   nout);
@@ -481,7 +423,7 @@ template <typename T>
 struct RegupFft {
     template <int P>
     struct K {
-        static hipError_t run(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat,
+        static hipError_t run(const T* in, const int32_t* child8, const T* C01, T* ftil, cplx<T>* fhat,
                               int64_t np, int64_t nout, hipStream_t s) {
             return lgf_launch(k_regup_fft<T, P>, dim3((unsigned)np), dim3(kRegUpThreads), 0, s, in, child8, C01, ftil,
                               fhat, nout);
@@ -493,9 +435,9 @@ template <typename T>
 struct InvInterp {
     template <int P>
     struct K {
-        static hipError_t run(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+        static hipError_t run(const cplx<T>* uhat, const double* up, const int32_t* par, const double* Ct,
                               double* out, int64_t nint, hipStream_t s) {
-            return lgf_launch(k_inv_interp<T, P>, dim3((unsigned)nint), dim3(kInvThreads), 0, s, uhat, up, par, C01,
+            return lgf_launch(k_inv_interp<T, P>, dim3((unsigned)nint), dim3(kInvThreads), 0, s, uhat, up, par, Ct,
                               out);
         }
     };
@@ -508,61 +450,61 @@ struct FinalFar {
         template <int P>
         struct At {
             static hipError_t run(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up,
-                                  const int32_t* par, const double* C01, const double* A, T* u, int64_t nb,
+                                  const int32_t* par, const double* Ct, const double* At, T* u, int64_t nb,
                                   hipStream_t s, const int32_t* l1map, const int32_t* near_flag) {
                 return lgf_launch(k_final_far<T, N, P>, dim3((unsigned)nb), dim3(kInvThreads), 0, s, vnear, uhat,
-                                  nint, up, par, C01, A, u, l1map, near_flag);
+                                  nint, up, par, Ct, At, u, l1map, near_flag);
             }
         };
     };
 };
 
 template <typename T>
-hipError_t launch_reg_fft(const T* f, const double* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
+hipError_t launch_reg_fft(const T* f, const T* A, T* ftil, cplx<T>* fhat, int64_t nb, int64_t nout, int n, int p,
                           hipStream_t s) {
     if (nb <= 0) return hipSuccess;
     return dispatch_np<RegFft<T>::template K>(n, p, f, A, ftil, fhat, nb, nout, s);
 }
 
 template <typename T>
-hipError_t launch_regup_fft(const T* in, const int32_t* child8, const double* C01, T* ftil, cplx<T>* fhat, int64_t np,
+hipError_t launch_regup_fft(const T* in, const int32_t* child8, const T* C01, T* ftil, cplx<T>* fhat, int64_t np,
                             int64_t nout, int p, hipStream_t s) {
     if (np <= 0) return hipSuccess;
     return dispatch_p<RegupFft<T>::template K>(p, in, child8, C01, ftil, fhat, np, nout, s);
 }
 
 template <typename T>
-hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* C01,
+hipError_t launch_inv_interp(const cplx<T>* uhat, const double* up, const int32_t* par, const double* Ct,
                              double* out, int64_t nint, int p, hipStream_t s) {
     if (nint <= 0) return hipSuccess;
-    return dispatch_p<InvInterp<T>::template K>(p, uhat, up, par, C01, out, nint, s);
+    return dispatch_p<InvInterp<T>::template K>(p, uhat, up, par, Ct, out, nint, s);
 }
 
 template <typename T>
 hipError_t launch_final_far(const T* vnear, const cplx<T>* uhat, int64_t nint, const double* up, const int32_t* par,
-                            const double* C01, const double* A, T* u, int64_t nb, int n, int p, hipStream_t s,
+                            const double* Ct, const double* At, T* u, int64_t nb, int n, int p, hipStream_t s,
                             const int32_t* l1map, const int32_t* near_flag) {
     if (nb <= 0) return hipSuccess;
-    return dispatch_np<FinalFar<T>::template K>(n, p, vnear, uhat, nint, up, par, C01, A, u, nb, s, l1map, near_flag);
+    return dispatch_np<FinalFar<T>::template K>(n, p, vnear, uhat, nint, up, par, Ct, At, u, nb, s, l1map, near_flag);
 }
 
 // One workgroup per (parent, child) writes each child's contribution to scratch, a second
 // kernel adds them in child order (eight children of 13^3 or 17^3 nodes do not fit one
 // workgroup's LDS).
 template <typename T, int P>
-static hipError_t reg_up_parts(const T* in, const int32_t* child8, const double* C01, T* out, int64_t np,
+static hipError_t reg_up_parts(const T* in, const int32_t* child8, const T* C01, T* out, int64_t np,
                                hipStream_t s, void* scratch) {
     constexpr int P3 = P * P * P;
     if (!scratch) return hipErrorInvalidValue;
-    const hipError_t e = lgf_launch(k_reg_up_part<T, P>, dim3((unsigned)(np * 8)), dim3(kInterpThreads), 0, s, in,
+    const hipError_t e = lgf_launch(k_reg_up_part<T, P>, dim3((unsigned)(np * 8)), dim3(kLatThreads), 0, s, in,
                                     child8, C01, (T*)scratch);
     if (e != hipSuccess) return e;
-    return lgf_launch(k_reg_up_sum<T, P>, dim3((unsigned)((np * P3 + kInterpThreads - 1) / kInterpThreads)),
-                      dim3(kInterpThreads), 0, s, (const T*)scratch, child8, out, np);
+    return lgf_launch(k_reg_up_sum<T, P>, dim3((unsigned)((np * P3 + kSumThreads - 1) / kSumThreads)),
+                      dim3(kSumThreads), 0, s, (const T*)scratch, child8, out, np);
 }
 
 template <typename T>
-hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, T* out, int64_t np, int p,
+hipError_t launch_reg_up(const T* in, const int32_t* child8, const T* C01, T* out, int64_t np, int p,
                          hipStream_t s, void* scratch) {
     if (np <= 0) return hipSuccess;
     switch (p) {
@@ -572,13 +514,13 @@ hipError_t launch_reg_up(const T* in, const int32_t* child8, const double* C01, 
     }
 }
 
-hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* C01, double* io,
+hipError_t launch_interp_down(const double* par, const int32_t* child8, const double* Ct, double* io,
                               int64_t nparent, int p, hipStream_t s) {
     if (nparent <= 0) return hipSuccess;
-    const dim3 grid((unsigned)(nparent * 8)), block(kDownThreads);
+    const dim3 grid((unsigned)(nparent * 8)), block(kLatThreads);
     switch (p) {
-        case 13: return lgf_launch(k_interp_down_one<13>, grid, block, 0, s, par, child8, C01, io);
-        case 17: return lgf_launch(k_interp_down_one<17>, grid, block, 0, s, par, child8, C01, io);
+        case 13: return lgf_launch(k_interp_down_one<13>, grid, block, 0, s, par, child8, Ct, io);
+        case 17: return lgf_launch(k_interp_down_one<17>, grid, block, 0, s, par, child8, Ct, io);
         default: return hipErrorInvalidValue;
     }
 }
@@ -591,26 +533,26 @@ hipError_t launch_pad_copy(const T* f, T* out, int64_t nb, int n, int p, hipStre
 }
 
 template <typename T>
-hipError_t launch_final(const T* vnear, const double* ut, const double* A, T* u, int64_t nb, int n, int p,
+hipError_t launch_final(const T* vnear, const double* ut, const double* At, T* u, int64_t nb, int n, int p,
                         hipStream_t s, const int32_t* l1map, const int32_t* near_flag) {
     if (nb <= 0) return hipSuccess;
-    const dim3 grid((unsigned)nb), block(kBlockThreads);
-    if (n == 12 && p == 13) return lgf_launch(k_final<T, 12, 13>, grid, block, 0, s, vnear, ut, A, u, l1map, near_flag);
-    if (n == 16 && p == 17) return lgf_launch(k_final<T, 16, 17>, grid, block, 0, s, vnear, ut, A, u, l1map, near_flag);
+    const dim3 grid((unsigned)nb), block(kLatThreads);
+    if (n == 12 && p == 13) return lgf_launch(k_final<T, 12, 13>, grid, block, 0, s, vnear, ut, At, u, l1map, near_flag);
+    if (n == 16 && p == 17) return lgf_launch(k_final<T, 16, 17>, grid, block, 0, s, vnear, ut, At, u, l1map, near_flag);
     return hipErrorInvalidValue;
 }
 
 #define LGF_INST(T)                                                                                                 \
-    template hipError_t launch_reg_fft<T>(const T*, const double*, T*, cplx<T>*, int64_t, int64_t, int, int,        \
+    template hipError_t launch_reg_fft<T>(const T*, const T*, T*, cplx<T>*, int64_t, int64_t, int, int,        \
                                           hipStream_t);                                                             \
-    template hipError_t launch_regup_fft<T>(const T*, const int32_t*, const double*, T*, cplx<T>*, int64_t, int64_t, \
+    template hipError_t launch_regup_fft<T>(const T*, const int32_t*, const T*, T*, cplx<T>*, int64_t, int64_t, \
                                             int, hipStream_t);                                                      \
     template hipError_t launch_inv_interp<T>(const cplx<T>*, const double*, const int32_t*, const double*, double*, \
                                              int64_t, int, hipStream_t);                                            \
     template hipError_t launch_final_far<T>(const T*, const cplx<T>*, int64_t, const double*, const int32_t*,       \
                                             const double*, const double*, T*, int64_t, int, int, hipStream_t,       \
                                             const int32_t*, const int32_t*);                                        \
-    template hipError_t launch_reg_up<T>(const T*, const int32_t*, const double*, T*, int64_t, int, hipStream_t,    \
+    template hipError_t launch_reg_up<T>(const T*, const int32_t*, const T*, T*, int64_t, int, hipStream_t,    \
                                          void*);                                                                    \
     template hipError_t launch_pad_copy<T>(const T*, T*, int64_t, int, int, hipStream_t);                           \
     template hipError_t launch_final<T>(const T*, const double*, const double*, T*, int64_t, int, int, hipStream_t, \

@@ -117,7 +117,8 @@ struct lgf_plan_s {
     std::vector<LevelPlan> lv;  // index 0 unused, 1..L
     std::shared_ptr<SpectraEntry> spectra0;
     int32_t *d_g0_tgt8 = nullptr, *d_g0_src64 = nullptr, *d_g0_runs = nullptr, *d_g0_flags = nullptr;
-    double *d_A = nullptr, *d_C01 = nullptr;
+    void *d_A = nullptr, *d_C01 = nullptr;    // Reg matrices, plan precision
+    double *d_At = nullptr, *d_Ct = nullptr;  // Interp matrices
     void *d_fhat0 = nullptr, *d_uhat0 = nullptr;
     std::vector<DevBuf> allocs;
     int64_t ws_bytes = 0;
@@ -296,7 +297,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     // Interp of the lattice scheme from level l + 1 down to level l, accumulated
     auto interp = [&](int l, hipStream_t st) -> hipError_t {
         LGF_STEP(st,
-                 (launch_interp_down((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_C01,
+                 (launch_interp_down((const U*)pl->lv[l + 1].d_util, pl->lv[l + 1].d_child8, pl->d_Ct,
                                      (U*)pl->lv[l].d_util, pl->lv[l + 1].nint, p, st)),
                  "interp_l" + std::to_string(l + 1) + "_l" + std::to_string(l), (lvN(l + 1) + 2.0 * lvN(l)) * p3 * us,
                  lvN(l) * 2.0 * 3.0 * p3 * p);
@@ -336,12 +337,13 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             const double fb = lists ? nup * Sl(l) * cs : 0.0, ff = lists ? nup * fft_flops(2 * p) : 0.0;
             if (l == 1)
                 LGF_STEP(st,
-                         (launch_reg_fft<T>(f, pl->d_A, (T*)L.d_ftil, (C*)L.d_fhat, pl->nsrc, L.nint + 1, n, p, st)),
+                         (launch_reg_fft<T>(f, (const T*)pl->d_A, (T*)L.d_ftil, (C*)L.d_fhat, pl->nsrc, L.nint + 1, n, p,
+                                            st)),
                          rname, rbytes + fb, rflops + ff);
             else
                 LGF_STEP(st,
-                         (launch_regup_fft<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, pl->d_C01, (T*)L.d_ftil,
-                                              (C*)L.d_fhat, L.nint, L.nint + 1, p, st)),
+                         (launch_regup_fft<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, (const T*)pl->d_C01,
+                                              (T*)L.d_ftil, (C*)L.d_fhat, L.nint, L.nint + 1, p, st)),
                          rname, rbytes + fb, rflops + ff);
             return hipSuccess;
         }
@@ -352,7 +354,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             return hipSuccess;
         }
         LGF_STEP(st,
-                 (launch_reg_up<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, pl->d_C01, (T*)L.d_ftil, L.nint, p, st,
+                 (launch_reg_up<T>((const T*)pl->lv[l - 1].d_ftil, L.d_child8, (const T*)pl->d_C01, (T*)L.d_ftil, L.nint, p, st,
                                    pl->d_scratch)),
                  rname, rbytes, rflops);
         if (lists)
@@ -373,7 +375,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
         if (!pl->lat1) {
             LGF_STEP(st,
                      (launch_inv_interp<T>(lists ? (const C*)L.d_uhat : nullptr,
-                                           above ? (const U*)pl->lv[l + 1].d_util : nullptr, L.d_par, pl->d_C01,
+                                           above ? (const U*)pl->lv[l + 1].d_util : nullptr, L.d_par, pl->d_Ct,
                                            (U*)L.d_util, L.nint, p, st)),
                      lname("inv_interp_l", l), lvN(l) * ((lists ? Sl(l) * cs : 0.0) + p3 * us) + (above ? lvN(l + 1) * p3 * us : 0.0),
                      (lists ? lvN(l) * fft_flops(2 * p) : 0.0) + iflops);
@@ -480,7 +482,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
         const double fflops = ne * 2.0 * (p3 * n + p * p * n * n + p * n3);
         if (pl->lat1) {
             LGF_STEP(s,
-                     (launch_final<T>(u, (const U*)L.d_util, pl->d_A, u, pl->neval, n, p, s, pl->d_eval_l1,
+                     (launch_final<T>(u, (const U*)L.d_util, pl->d_At, u, pl->neval, n, p, s, pl->d_eval_l1,
                                       pl->d_near_flag)),
                      "final_l1_l0", fbytes + ne * p3 * us, fflops);
         } else {
@@ -488,7 +490,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
             const bool lists = L.pairs() > 0, above = pl->Ltop >= 2;
             LGF_STEP(s,
                      (launch_final_far<T>(u, lists ? (const C*)L.d_uhat : nullptr, L.nint,
-                                          above ? (const U*)pl->lv[2].d_util : nullptr, L.d_par, pl->d_C01, pl->d_A,
+                                          above ? (const U*)pl->lv[2].d_util : nullptr, L.d_par, pl->d_Ct, pl->d_At,
                                           u, pl->neval, n, p, s, pl->d_eval_l1, pl->d_near_flag)),
                      "final_l1_l0",
                      fbytes + (lists ? ne * Sl(1) * cs : 0.0) + (above ? lvN(2) * p3 * us : 0.0),
@@ -581,6 +583,12 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
         for (int mm = 0; mm < p; ++mm)
             for (int k = 0; k < p; ++k)
                 C01[c * p * p + mm * p + k] = (double)lagrange(p, mm, (long double)(c * (p - 1) + k) / 2.0L);
+    std::vector<double> At(p * n), Ct(2 * p * p);
+    for (int k = 0; k < p; ++k)
+        for (int j = 0; j < n; ++j) At[j * p + k] = A[k * n + j];
+    for (int c = 0; c < 2; ++c)
+        for (int mm = 0; mm < p; ++mm)
+            for (int k = 0; k < p; ++k) Ct[c * p * p + k * p + mm] = C01[c * p * p + mm * p + k];
     // ---- device memory
     const int64_t esz = prec == LGF_F64 ? sizeof(double) : sizeof(float);
     const int64_t usz = 8;  // far-field down-pass values: double
@@ -596,7 +604,8 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
               dev_alloc(pl, &pl->d_g0_src64, H.ngroups0 * 64 * 4) &&
               dev_alloc(pl, &pl->d_g0_runs, (int64_t)H.g0_runs.size() * 4) &&
               dev_alloc(pl, &pl->d_g0_flags, H.ngroups0 * 4) && dev_alloc(pl, &pl->d_A, p * n * 8) &&
-              dev_alloc(pl, &pl->d_C01, 2 * p * p * 8) &&
+              dev_alloc(pl, &pl->d_C01, 2 * p * p * 8) && dev_alloc(pl, &pl->d_At, p * n * 8) &&
+              dev_alloc(pl, &pl->d_Ct, 2 * p * p * 8) &&
               dev_alloc(pl, &pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz) &&
               dev_alloc(pl, &pl->d_uhat0, H.ntgt0 * S0 * 2 * esz) &&
               dev_alloc(pl, &pl->d_eval_l1, (int64_t)H.eval_l1.size() * 4) &&
@@ -633,8 +642,11 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     if (e == hipSuccess) e = upload(pl->d_g0_src64, H.g0_src64, s);
     if (e == hipSuccess) e = upload(pl->d_g0_runs, H.g0_runs, s);
     if (e == hipSuccess) e = upload(pl->d_g0_flags, H.g0_flags, s);
-    if (e == hipSuccess) e = upload(pl->d_A, A, s);
-    if (e == hipSuccess) e = upload(pl->d_C01, C01, s);
+    const std::vector<float> A32(A.begin(), A.end()), C32(C01.begin(), C01.end());
+    if (e == hipSuccess) e = prec == LGF_F64 ? upload(pl->d_A, A, s) : upload(pl->d_A, A32, s);
+    if (e == hipSuccess) e = prec == LGF_F64 ? upload(pl->d_C01, C01, s) : upload(pl->d_C01, C32, s);
+    if (e == hipSuccess) e = upload(pl->d_At, At, s);
+    if (e == hipSuccess) e = upload(pl->d_Ct, Ct, s);
     if (e == hipSuccess) e = upload(pl->d_eval_l1, H.eval_l1, s);
     if (e == hipSuccess) e = upload(pl->d_near_out, H.near_out, s);
     if (e == hipSuccess) e = upload(pl->d_near_flag, H.near_flag, s);
