@@ -270,24 +270,24 @@ static hipError_t launch_fwd_m(const T* in, cplx<T>* out, int64_t nbatch, int64_
 }
 
 template <typename Tin, typename A, typename Tout, int m, int NT>
-static hipError_t inv_mnt(const cplx<Tin>* in, Tout* out, int64_t nbatch, const int32_t* out_map, int opitch,
-                          hipStream_t s) {
-    return lgf_launch(k_ifft_trunc<Tin, A, Tout, m, NT>, dim3((unsigned)nbatch), dim3(NT), 0, s, in, out, nbatch,
+static hipError_t inv_mnt(const cplx<Tin>* in, Tout* out, int64_t nbatch, int64_t nin, const int32_t* out_map,
+                          int opitch, hipStream_t s) {
+    return lgf_launch(k_ifft_trunc<Tin, A, Tout, m, NT>, dim3((unsigned)nbatch), dim3(NT), 0, s, in, out, nin,
                       out_map, opitch);
 }
 
 template <typename Tin, typename A, typename Tout, int m>
-static hipError_t launch_inv_m(const cplx<Tin>* in, Tout* out, int64_t nbatch, const int32_t* out_map, int opitch,
-                               hipStream_t s, int nt = 0) {
+static hipError_t launch_inv_m(const cplx<Tin>* in, Tout* out, int64_t nbatch, int64_t nin, const int32_t* out_map,
+                               int opitch, hipStream_t s, int nt = 0) {
     if (opitch <= 0) opitch = m;
     // FP64 16^3 tiles default to 512 threads: one workgroup fills a CU's LDS, and 8 waves
     // keep twice the column loads in flight (256^3: 331 -> 299 us; 128^3: 51 -> 47 us)
     if (nt == 0 && m == 16 && sizeof(A) == 8) nt = 512;
     if constexpr (m == 8 || m == 16) {
-        if (nt == 512) return inv_mnt<Tin, A, Tout, m, 512>(in, out, nbatch, out_map, opitch, s);
-        if (nt == 128) return inv_mnt<Tin, A, Tout, m, 128>(in, out, nbatch, out_map, opitch, s);
+        if (nt == 512) return inv_mnt<Tin, A, Tout, m, 512>(in, out, nbatch, nin, out_map, opitch, s);
+        if (nt == 128) return inv_mnt<Tin, A, Tout, m, 128>(in, out, nbatch, nin, out_map, opitch, s);
     }
-    return inv_mnt<Tin, A, Tout, m, 256>(in, out, nbatch, out_map, opitch, s);
+    return inv_mnt<Tin, A, Tout, m, 256>(in, out, nbatch, nin, out_map, opitch, s);
 }
 
 template <typename T>
@@ -308,15 +308,15 @@ hipError_t launch_pad_fft(int m, const T* in, cplx<T>* out, int64_t nbatch, hipS
 }
 
 template <typename T>
-hipError_t launch_ifft0(int n, const cplx<T>* in, T* out, int64_t nbatch, hipStream_t s, int nt,
+hipError_t launch_ifft0(int n, const cplx<T>* in, T* out, int64_t nbatch, int64_t nin, hipStream_t s, int nt,
                         const int32_t* out_map) {
     if (nbatch <= 0) return hipSuccess;
     switch (n) {
-        case 4: return launch_inv_m<T, T, T, 4>(in, out, nbatch, out_map, 0, s);
-        case 6: return launch_inv_m<T, T, T, 6>(in, out, nbatch, out_map, 0, s);
-        case 8: return launch_inv_m<T, T, T, 8>(in, out, nbatch, out_map, 0, s, nt);
-        case 12: return launch_inv_m<T, T, T, 12>(in, out, nbatch, out_map, 0, s);
-        case 16: return launch_inv_m<T, T, T, 16>(in, out, nbatch, out_map, 0, s, nt);
+        case 4: return launch_inv_m<T, T, T, 4>(in, out, nbatch, nin, out_map, 0, s);
+        case 6: return launch_inv_m<T, T, T, 6>(in, out, nbatch, nin, out_map, 0, s);
+        case 8: return launch_inv_m<T, T, T, 8>(in, out, nbatch, nin, out_map, 0, s, nt);
+        case 12: return launch_inv_m<T, T, T, 12>(in, out, nbatch, nin, out_map, 0, s);
+        case 16: return launch_inv_m<T, T, T, 16>(in, out, nbatch, nin, out_map, 0, s, nt);
         default: return hipErrorInvalidValue;
     }
 }
@@ -329,9 +329,9 @@ hipError_t launch_ifft_lattice(int m, const cplx<T>* in, double* out, int64_t nb
     switch (m) {
         // level 1: the blocks' spectra, in the path's own precision (these values are not
         // interpolated further)
-        case 12: return launch_inv_m<T, T, double, 12>(in, out, nbatch, nullptr, opitch, s);
-        case 16: return launch_inv_m<T, T, double, 16>(in, out, nbatch, nullptr, opitch, s);
-        case 13: return launch_inv_m<T, double, double, 13>(in, out, nbatch, nullptr, opitch, s);
+        case 12: return launch_inv_m<T, T, double, 12>(in, out, nbatch, nbatch, nullptr, opitch, s);
+        case 16: return launch_inv_m<T, T, double, 16>(in, out, nbatch, nbatch, nullptr, opitch, s);
+        case 13: return launch_inv_m<T, double, double, 13>(in, out, nbatch, nbatch, nullptr, opitch, s);
         case 17: return inv_two_phase<T, double, double, 17>(in, out, nbatch, nullptr, scratch, s);
         default: return hipErrorInvalidValue;
     }
@@ -339,7 +339,7 @@ hipError_t launch_ifft_lattice(int m, const cplx<T>* in, double* out, int64_t nb
 
 #define LGF_INST(T)                                                                                                  \
     template hipError_t launch_pad_fft<T>(int, const T*, cplx<T>*, int64_t, hipStream_t, int, int64_t, void*);       \
-    template hipError_t launch_ifft0<T>(int, const cplx<T>*, T*, int64_t, hipStream_t, int, const int32_t*);         \
+    template hipError_t launch_ifft0<T>(int, const cplx<T>*, T*, int64_t, int64_t, hipStream_t, int, const int32_t*);\
     template hipError_t launch_ifft_lattice<T>(int, const cplx<T>*, double*, int64_t, hipStream_t, void*, int);
 LGF_INST(double)
 LGF_INST(float)

@@ -490,7 +490,8 @@ int64_t workspace_need(const HostPlan& H, lgf_precision prec) {
     const int64_t S1 = spec_padded(2 * p * 2 * p * (p + 1));
     const int64_t p3 = (int64_t)p * p * p;
     const int topc = std::min(H.Ltop + 1, H.L);
-    int64_t need = (H.ngroups0 * 73 + (int64_t)H.g0_runs.size()) * 4 + 2 * (p * n + 2 * p * p) * 8 + (H.nsrc + 1 + H.ntgt0) * S0 * 2 * esz +
+    int64_t need = (H.ngroups0 * 73 + (int64_t)H.g0_runs.size()) * 4 + 2 * (p * n + 2 * p * p) * 8 +
+                   (H.nsrc + 1 + field_items(H.ntgt0)) * S0 * 2 * esz +
                    (int64_t)(H.eval_l1.size() + H.near_out.size() + H.near_flag.size()) * 4;
     for (int l = 1; l <= H.Ltop; ++l) {
         const HostLevel& h = H.lv[l];

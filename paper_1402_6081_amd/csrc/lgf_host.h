@@ -30,6 +30,14 @@ constexpr int kNmax = 10;  // most nodes one interpolation stencil uses (the pap
 constexpr int kSpecChunk = 64;
 constexpr int spec_padded(int S) { return (S + kSpecChunk - 1) / kSpecChunk * kSpecChunk; }
 
+// Items per chunk of the level-0 field spectra of n targets.  The inverse transform reads one item
+// from every chunk at once; with a multiple of 1024 items the chunks lie a multiple of 1 MB (FP32:
+// 512 KB) apart and those reads meet in the same DRAM banks, so one item is added (256^3 in 16^3
+// blocks, 4096 -> 4097 items: FP64 288 -> 267 us, FP32 144 -> 136; up to 256 items more make no
+// further difference, and 512 -> 513 items at 128^3 none at all).  The source spectra have a
+// sentinel item beside theirs.
+constexpr int64_t field_items(int64_t n) { return n % 1024 == 0 ? n + 1 : n; }
+
 // Tiles of 17 nodes take the two-phase transforms, whose HBM intermediate holds
 // nbatch * m * 2m * (m + 1) complex values of 16 bytes.
 inline bool two_phase_tile(int m) { return m == 17; }

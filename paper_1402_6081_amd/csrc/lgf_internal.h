@@ -143,7 +143,7 @@ hipError_t launch_pad_fft(int m, const T* in, cplx<T>* out, int64_t nbatch, hipS
                           int64_t nout = 0, void* scratch = nullptr);
 // Level-0 inverse.  out_map: output tile of each transformed item (NULL = the item's own index)
 template <typename T>
-hipError_t launch_ifft0(int n, const cplx<T>* in, T* out, int64_t nbatch, hipStream_t s, int nt = 0,
+hipError_t launch_ifft0(int n, const cplx<T>* in, T* out, int64_t nbatch, int64_t nin, hipStream_t s, int nt = 0,
                         const int32_t* out_map = nullptr);
 // Inverse of a level of the lattice scheme to node values: m = n at level 1 (opitch = p: the n^3
 // results in tiles of p nodes, zeros beyond them), m = p above (scratch as for the forward).
@@ -154,10 +154,11 @@ hipError_t launch_ifft_lattice(int m, const cplx<T>* in, double* out, int64_t nb
 // The far-field node values of the down pass (utilde) are double on both paths.
 
 // Source spectra (fhat) arrays hold nitems + 1 items per frequency chunk; the last is a zero
-// sentinel that inactive neighbours point to.  Field spectra (uhat) hold nitems items.
+// sentinel that inactive neighbours point to.  Field spectra (uhat) hold nitems items
+// (field_items at level 0).
 // Level 0 over groups of 2x2x2 target blocks (tgt8) with their 4^3 source neighbourhood (src64).
 // Sources and targets are numbered separately: fhat holds nsrc + 1 items (sentinel nsrc),
-// uhat ntgt items.
+// uhat ntgt items per chunk (field_items of the targets).
 // Groups stacked in z are numbered consecutively; a run (first group, count) is such a stack,
 // which one wave marches through.  flags: per group, bit 2 sz + h = half h of source slab sz
 // holds a source, bit 8 + cz = target slab cz holds a target.

@@ -395,7 +395,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     };
     const NearLevel<T> near0{(const C*)pl->d_fhat0, (const C*)pl->spectra0->dev, pl->d_g0_tgt8, pl->d_g0_src64,
                              pl->d_g0_runs,         pl->d_g0_flags,              (C*)pl->d_uhat0, pl->nruns0,
-                             pl->nsrc,              pl->ntgt0,                   pl->spectra0->S, pl->spectra0->sym};
+                             pl->nsrc,              field_items(pl->ntgt0),      pl->spectra0->S, pl->spectra0->sym};
     // level-0 PadFFT: first when level 1 reads its spectra (the lattice scheme), else at the
     // head of the near field
     auto fwd0 = [&]() -> hipError_t {
@@ -472,7 +472,7 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     {
         LGF_STEP(s, launch_prod_near<T>(near0, tc.near_waves, s),
                  "prod_l0", (ns + nt0 + khat_rows(*pl->spectra0, 27)) * S0 * cs, (double)pl->near_pairs * S0 * 8.0);
-        LGF_STEP(s, (launch_ifft0<T>(n, (const C*)pl->d_uhat0, u, pl->ntgt0, s, tc.fft0_threads, pl->d_near_out)),
+        LGF_STEP(s, (launch_ifft0<T>(n, (const C*)pl->d_uhat0, u, pl->ntgt0, field_items(pl->ntgt0), s, tc.fft0_threads, pl->d_near_out)),
                  "fft_inv_l0", nt0 * (S0 * cs + n3 * es), nt0 * fft_flops(2 * n));
     }
     if (far) {
@@ -607,7 +607,7 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
               dev_alloc(pl, &pl->d_C01, 2 * p * p * 8) && dev_alloc(pl, &pl->d_At, p * n * 8) &&
               dev_alloc(pl, &pl->d_Ct, 2 * p * p * 8) &&
               dev_alloc(pl, &pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz) &&
-              dev_alloc(pl, &pl->d_uhat0, H.ntgt0 * S0 * 2 * esz) &&
+              dev_alloc(pl, &pl->d_uhat0, field_items(H.ntgt0) * S0 * 2 * esz) &&
               dev_alloc(pl, &pl->d_eval_l1, (int64_t)H.eval_l1.size() * 4) &&
               dev_alloc(pl, &pl->d_near_out, (int64_t)H.near_out.size() * 4) &&
               dev_alloc(pl, &pl->d_near_flag, (int64_t)H.near_flag.size() * 4);
