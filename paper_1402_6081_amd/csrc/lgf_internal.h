@@ -221,7 +221,7 @@ struct TuneConfig {
     int near_prefetch = 0; // 0, 1: without effect (kept in the ABI and in tuning files)
     int far_waves = 0;     // parent groups per workgroup of the level >= 1 Prod kernel: 1, 2, 4, 0 = by level size
     int far_children = 0;  // children per lane of that kernel: 8, 4, 2, 1, or 0 = by level size
-    int overlap = 0;       // far-field chain on a second stream: 1 = yes, 2 = no, 0 = default (yes)
+    int overlap = 0;       // schedule: 1 three branches, 3 two, 2 one stream, 0 = by plan and use
 };
 
 // The 1D matrices: A p x n and its transpose At n x p (blocks and level 1), C01 the two p x p
