@@ -323,6 +323,10 @@ void budget_release(int64_t bytes);
 int64_t budget_in_use();
 void budget_set(int64_t bytes);
 
+// Whether other plans' solves run beside this plan's next ones: one stream then, where the schedule
+// is the plan's choice (lgf_tuning.overlap 0; the lattice scheme keeps its own).
+void plan_set_beside_others(lgf_plan_t plan, bool beside);
+
 // Workspace bytes a plan of this layout would own (host-only work: builds the lists).
 lgf_status plan_estimate(const int32_t* ijk, int64_t nblocks, int n, int p, int levels, lgf_precision prec,
                          int64_t* bytes);

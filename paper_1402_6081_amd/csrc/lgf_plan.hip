@@ -142,6 +142,7 @@ struct lgf_plan_s {
     bool done_valid = false;
     int32_t* d_flag = nullptr;  // debug check of the input (LGF_CHECK_FINITE=1)
     int schedule = 1, graph_schedule = 3;  // the default ones: default_schedule
+    bool beside_others = false;            // plan_set_beside_others
 
     ~lgf_plan_s() {
         for (auto& b : allocs) hipFree(b.ptr);
@@ -266,7 +267,10 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     const bool far = pl->Ltop >= 1;
     // overlap: 1 three concurrent branches, 3 two (the coarse levels follow level 1 on one
     // stream), 2 a single stream, 0 the plan's default
-    const int ov = tc.overlap != 0 ? tc.overlap : active_recorder() ? pl->graph_schedule : pl->schedule;
+    const int ov = tc.overlap != 0                  ? tc.overlap
+                   : pl->beside_others && !pl->lat1 ? 2
+                   : active_recorder()              ? pl->graph_schedule
+                                                    : pl->schedule;
     const bool overlap = ov != 2;
     // streams: s = near field (level 0), s2 = level 1, s3 = levels >= 2 (the coarse levels'
     // small kernels run beside the level-1 M2L); one stream when overlap is off.  The fork and
@@ -862,6 +866,8 @@ bool budget_reserve(int64_t bytes) {
 void budget_release(int64_t bytes) { g_used.fetch_sub(bytes); }
 int64_t budget_in_use() { return g_used.load(); }
 void budget_set(int64_t bytes) { g_budget.store(bytes); }
+
+void plan_set_beside_others(lgf_plan_t plan, bool beside) { plan->beside_others = beside; }
 
 lgf_status plan_estimate(const int32_t* ijk, int64_t nblocks, int n, int p, int levels, lgf_precision prec,
                          int64_t* bytes) {
