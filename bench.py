@@ -85,8 +85,8 @@ def _time_graph(plan, f, u, steps, warmup):
 
 
 _SRC = {"prod": ["lgf_prod.hip", "lgf_device.h", "lgf_internal.h"],
-        "fft": ["lgf_fft.hip", "lgf_device.h", "lgf_internal.h"],
-        "interp": ["lgf_interp.hip", "lgf_device.h", "lgf_internal.h"]}
+        "fft": ["lgf_fft.hip", "lgf_tile.h", "lgf_device.h", "lgf_internal.h"],
+        "interp": ["lgf_interp.hip", "lgf_tile.h", "lgf_device.h", "lgf_internal.h"]}
 
 
 def _family(step):

@@ -219,7 +219,7 @@ struct TuneConfig {
     int fft0_threads = 0;  // 0 = default per tile size, else 128 / 256 / 512
     int near_waves = 4;    // waves per workgroup of the level-0 Prod kernel: 2, 4, 8
     int near_prefetch = 0; // 0, 1: without effect (kept in the ABI and in tuning files)
-    int far_waves = 0;     // parent groups per workgroup of the level >= 1 Prod kernel: 1, 2, 4, 0 = by level size
+    int far_waves = 0;     // waves (parent groups) per workgroup of the level >= 1 Prod: 1 .. 16, 0 = by level size
     int far_children = 0;  // children per lane of that kernel: 8, 4, 2, 1, or 0 = by level size
     int overlap = 0;       // schedule: 1 three branches, 3 two, 2 one stream, 0 = by plan and use
 };
