@@ -16,9 +16,8 @@
 // matrix entry from LDS for each multiply-add, made the passes LDS-bound).  On a 256^3 cube of
 // 16^3 blocks, p = 8, from one output per thread to this, FP64 and FP32: Reg to level 1 with its
 // transform 85 to 55 us (its 0.30 GB take 53 at a copy's rate) and 45 to 31, Reg up 25 to 17 and
-// 14 to 11, the final pass with its transform and Interp 106 to 77 (0.42 GB: 74) and 85 to 66
-// (node values and their passes stay in double there); at p = 17, FP64, 128^3: Reg up 63 to 36,
-// Interp down 50 to 31, the final pass 30 to 22.
+// 14 to 11, the final pass with its transform and Interp 106 to 77 (0.42 GB: 74) and 85 to 66;
+// at p = 17, FP64, 128^3: Reg up 63 to 36, Interp down 50 to 31, the final pass 30 to 22.
 #include <type_traits>
 
 #include "lgf_internal.h"
@@ -48,31 +47,39 @@ __device__ __forceinline__ Uniform<T> uniform_ptr(const T* p) {
     return (Uniform<T>)(uintptr_t)p;
 }
 
-// One pass of W waves over C columns: put(col, o, sum_k mat[o * IN + k] * load(col, k), base(col, o))
-// for o < OUT, the sum in increasing k.  A wave takes 64 columns, one per lane, and all their
-// outputs, or, with fewer groups of columns than waves, a share of the outputs; base, what the
-// outputs are added to, is read for all of them before the first is written.  mat is row-major
-// [OUT][IN] and wave-uniform.
+// How W waves share the OUT outputs of C columns: a wave takes 64 columns, one per lane, and all
+// their outputs, or, with fewer groups of columns than waves, a share of CH outputs.
+template <int OUT, int C, int W>
+struct Share {
+    static constexpr int G = (C + 63) / 64, CH = W >= 2 * G ? (OUT + W / G - 1) / (W / G) : OUT;
+    static constexpr int SPLIT = (OUT + CH - 1) / CH;  // shares, the last one with the rest
+    static constexpr int TASKS = G * SPLIT;            // of which wave w takes w, w + W, ...
+    static_assert(SPLIT * CH >= OUT && (SPLIT - 1) * CH < OUT && (SPLIT == 1 || TASKS <= W), "shares");
+    static __device__ __forceinline__ int col(int task, int lane) { return task % G * 64 + lane; }
+    static __device__ __forceinline__ int out0(int task) { return task / G * CH; }
+};
+
+// One pass: put(col, o, sum_k mat[o * IN + k] * load(col, k), base(col, o, i)) for o < OUT, the sum
+// in increasing k; output o is the i-th of its share.  base, what the outputs are added to, is read
+// for all of a share before the first is written.  mat is row-major [OUT][IN] and wave-uniform.
 template <int IN, int OUT, int C, int W, typename T, typename Load, typename Base, typename Put>
 __device__ __forceinline__ void contract_onto(int wave, int lane, Uniform<T> mat, Load load, Base base, Put put) {
-    constexpr int G = (C + 63) / 64, CH = W >= 2 * G ? (OUT + W / G - 1) / (W / G) : OUT;
-    constexpr int SPLIT = (OUT + CH - 1) / CH;  // shares of CH outputs, the last one with the rest
-    static_assert(SPLIT * CH >= OUT && (SPLIT - 1) * CH < OUT && (SPLIT == 1 || G * SPLIT <= W), "shares");
-    for (int task = wave; task < G * SPLIT; task += W) {
-        const int col = task % G * 64 + lane, o0 = task / G * CH;
+    using Sh = Share<OUT, C, W>;
+    for (int task = wave; task < Sh::TASKS; task += W) {
+        const int col = Sh::col(task, lane), o0 = Sh::out0(task);
         const bool on = C % 64 == 0 || col < C;
-        using B = std::remove_reference_t<decltype(base(0, 0))>;
-        B b[CH];
+        using B = std::remove_reference_t<decltype(base(0, 0, 0))>;
+        B b[Sh::CH];
         T v[IN];
 #pragma unroll
-        for (int i = 0; i < CH; ++i)
-            b[i] = on && (SPLIT * CH == OUT || o0 + i < OUT) ? base(col, o0 + i) : B(0);
+        for (int i = 0; i < Sh::CH; ++i)
+            b[i] = on && (Sh::SPLIT * Sh::CH == OUT || o0 + i < OUT) ? base(col, o0 + i, i) : B(0);
 #pragma unroll
         for (int k = 0; k < IN; ++k) v[k] = on ? load(col, k) : T(0);
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
+        for (int i = 0; i < Sh::CH; ++i) {
             const int o = o0 + i;
-            if (SPLIT * CH != OUT && o >= OUT) break;
+            if (Sh::SPLIT * Sh::CH != OUT && o >= OUT) break;
             T acc = T(0);
 #pragma unroll
             for (int k = 0; k < IN; ++k) acc += mat[o * IN + k] * v[k];
@@ -83,7 +90,7 @@ __device__ __forceinline__ void contract_onto(int wave, int lane, Uniform<T> mat
 template <int IN, int OUT, int C, int W, typename T, typename Load, typename Put>
 __device__ __forceinline__ void contract(int wave, int lane, Uniform<T> mat, Load load, Put put) {
     contract_onto<IN, OUT, C, W, T>(
-        wave, lane, mat, load, [](int, int) { return 0; }, [&](int col, int o, T v, int) { put(col, o, v); });
+        wave, lane, mat, load, [](int, int, int) { return 0; }, [&](int col, int o, T v, int) { put(col, o, v); });
 }
 
 // ------------------------------------------------------------------ block -> level 1
@@ -178,16 +185,25 @@ __global__ void __launch_bounds__(kRegUpThreads)
 
 // ------------------------------------------------------------------ inverse and parent -> child
 // Interp of a parent's node values (in HBM) to its child c: at(yx, z) += its value for every node
-// z, y x of the child (yx = y P + x).  Ct: [2][P][P], Ct_c[k][m] = C_c[m][k]; R: interp_values<P>() doubles.
+// z, y x of the child (yx = y P + x).  rows: the parent's rows this lane's share of the x pass takes,
+// read ahead (interp_rows).  Ct: [2][P][P], Ct_c[k][m] = C_c[m][k]; R: interp_values<P>() doubles.
 template <int P>
 constexpr int interp_values() { return P * (P * P + 1) + P * (P * P + 4); }
+template <int P, int W>
+__device__ __forceinline__ void interp_rows(const double* __restrict__ src, int wave, int lane, double (&rows)[P]) {
+    using Sh = Share<P, P * P, W>;
+    static_assert(Sh::TASKS <= W, "one share per wave");
+    const int ab = Sh::col(wave, lane);
+#pragma unroll
+    for (int d = 0; d < P; ++d) rows[d] = wave < Sh::TASKS && ab < P * P ? src[ab * P + d] : 0.0;
+}
 template <int P, int W, typename At>
-__device__ __forceinline__ void interp_child(const double* __restrict__ src, int c, Uniform<double> Ct, double* R,
-                                             int wave, int lane, At at) {
+__device__ __forceinline__ void interp_child(const double (&rows)[P], int c, Uniform<double> Ct, double* R, int wave,
+                                             int lane, At at) {
     constexpr int P2 = P * P, kX = P2 + 1, kA = P2 + 4;
     double *t1 = R, *t2 = R + P * kX;  // t1[x'][a b], t2[a][y' x']
     contract<P, P, P2, W, double>(
-        wave, lane, Ct + (c & 1) * P2, [&](int ab, int d) { return src[ab * P + d]; },
+        wave, lane, Ct + (c & 1) * P2, [&](int, int d) { return rows[d]; },
         [&](int ab, int x, double v) { t1[x * kX + ab] = v; });
     __syncthreads();
     contract<P, P, P2, W, double>(
@@ -195,31 +211,44 @@ __device__ __forceinline__ void interp_child(const double* __restrict__ src, int
         [&](int ax, int y, double v) { t2[ax / P * kA + y * P + ax % P] = v; });
     __syncthreads();
     contract_onto<P, P, P2, W, double>(
-        wave, lane, Ct + ((c >> 2) & 1) * P2, [&](int yx, int a) { return t2[a * kA + yx]; }, at,
+        wave, lane, Ct + ((c >> 2) & 1) * P2, [&](int yx, int a) { return t2[a * kA + yx]; },
+        [&](int yx, int z, int) { return at(yx, z); },
         [&](int yx, int z, double v, double before) { at(yx, z) = before + v; });
 }
 
 // The node values of interval q (rows of P values, VP apart) into V: the inverse transform of its
 // field spectrum (uhat NULL: zeros) plus Interp from its parent (par[q] = 8 J + c, -1: none;
-// up NULL: no level above).  R: max(2 tile_values, interp_values) doubles.
-template <typename T, int P, int VP, int NT>
+// up NULL: no level above).  The parent's rows, and what ahead() reads, are loaded as soon as the
+// transform's registers are free, so that their latency passes behind its last results and Interp's
+// passes: the final pass of 256^3 in FP32 66 -> 46 us (0.21 GB: 37), of 128^3 16 -> 12, FP64 within
+// 1 us (loaded before the transform they cost it occupancy: 60 us, and spheres of 6^3 blocks 30 -> 33).
+// R: max(2 tile_values, interp_values) doubles.
+template <typename T, int P, int VP, int NT, typename Ahead>
 __device__ __forceinline__ void node_values(const cplx<T>* __restrict__ uhat, int64_t nint,
                                             const double* __restrict__ up, const int32_t* __restrict__ par,
-                                            Uniform<double> Ct, int64_t q, double* R, double* V, int tid) {
+                                            Uniform<double> Ct, int64_t q, double* R, double* V, int tid,
+                                            Ahead ahead) {
     constexpr int P3 = P * P * P, P2 = P * P;
     const int pc = up ? uniform_ptr(par)[q] : -1;  // uniform
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double rows[P];
+    auto load_ahead = [&] {
+        if (pc >= 0) interp_rows<P, NT / 64>(up + (int64_t)(pc >> 3) * P3, wave, lane, rows);
+        ahead();
+    };
     if (uhat) {
         cplx<double>* buf = reinterpret_cast<cplx<double>*>(R);
         tile_inverse<T, double, P, NT>(uhat, (size_t)q, nint, buf, tid);
         __syncthreads();
+        load_ahead();
         for (int i = tid; i < P3; i += NT) V[(i / P) * VP + i % P] = staged<double, P>(buf, i / P2, i / P % P, i % P);
     } else {
+        load_ahead();
         for (int i = tid; i < P3; i += NT) V[(i / P) * VP + i % P] = 0.0;
     }
     __syncthreads();
     if (pc < 0) return;
-    interp_child<P, NT / 64>(up + (int64_t)(pc >> 3) * P3, pc & 7, Ct, R, __builtin_amdgcn_readfirstlane(tid >> 6),
-                             tid & 63,
+    interp_child<P, NT / 64>(rows, pc & 7, Ct, R, wave, lane,
                              [&](int yx, int z) -> double& { return V[(z * P + yx / P) * VP + yx % P]; });
     __syncthreads();
 }
@@ -232,7 +261,8 @@ __global__ void __launch_bounds__(kInvThreads)
     __shared__ alignas(16) double R[imax(2 * tile_values<P>(), interp_values<P>())];
     __shared__ double V[P3];
     const int64_t q = blockIdx.x;
-    node_values<T, P, P, kInvThreads>(uhat, gridDim.x, up, par, uniform_ptr(Ct), q, R, V, threadIdx.x);
+    node_values<T, P, P, kInvThreads>(uhat, gridDim.x, up, par, uniform_ptr(Ct), q, R, V, threadIdx.x,
+                                   [] {});
     for (int i = threadIdx.x; i < P3; i += kInvThreads) out[q * P3 + i] = V[i];
 }
 
@@ -295,8 +325,10 @@ __global__ void __launch_bounds__(kLatThreads)
     const int q = child8[J * 8 + c];  // uniform
     if (q < 0) return;
     double* dst = io + (int64_t)q * P3;
-    interp_child<P, kLatThreads / 64>(par + J * P3, c, uniform_ptr(Ct), R,
-                                      __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63,
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double rows[P];
+    interp_rows<P, kLatThreads / 64>(par + J * P3, wave, lane, rows);
+    interp_child<P, kLatThreads / 64>(rows, c, uniform_ptr(Ct), R, wave, lane,
                                       [&](int yx, int z) -> double& { return dst[z * P2 + yx]; });
 }
 
@@ -314,13 +346,30 @@ __global__ void k_pad_copy(const T* __restrict__ f, T* __restrict__ out, int64_t
 }
 
 // ------------------------------------------------------------------ level 1 -> block, FP64 add-back
+// The near-field values that this lane's share of the final z pass adds to (read ahead; zeros, and
+// not read, without a near field).  Every thread reads the elements it writes, so u may alias vnear.
+template <int N, int W>
+using FinalShare = Share<N, N * N, W>;
+template <typename T, int N, int W>
+__device__ __forceinline__ void near_values(const T* vnear, int64_t b, bool has_near, int wave, int lane,
+                                            T (&near)[FinalShare<N, W>::CH]) {
+    using Sh = FinalShare<N, W>;
+    static_assert(Sh::TASKS <= W, "one share per wave");
+    const int yx = Sh::col(wave, lane), z0 = Sh::out0(wave);
+    const T* v = vnear + b * (N * N * N);
+    const bool on = has_near && wave < Sh::TASKS && yx < N * N;
+#pragma unroll
+    for (int i = 0; i < Sh::CH; ++i) near[i] = on && z0 + i < N ? v[(z0 + i) * (N * N) + yx] : T(0);
+}
+
 // u[b] from the level-1 node values V (LDS, rows of P values, P + 1 apart; visible to the
-// workgroup).  At: [N][P], the rows of A^T; R: final_values<N, P>() doubles.
+// workgroup) and near (near_values).  At: [N][P], the rows of A^T; R: final_values<N, P>() doubles.
 template <int N, int P>
 constexpr int final_values() { return P * P * (N + 1) + P * (N * N + 8); }
 template <typename T, int N, int P, int W>
-__device__ __forceinline__ void final_passes(const double* V, Uniform<double> At, double* R, const T* vnear, T* u,
-                                             int64_t b, bool has_near, int wave, int lane) {
+__device__ __forceinline__ void final_passes(const double* V, Uniform<double> At, double* R,
+                                             const T (&near)[FinalShare<N, W>::CH], T* u, int64_t b, int wave,
+                                             int lane) {
     constexpr int N2 = N * N, kX = N + 1, kA = N2 + 8;
     double *t1 = R, *t2 = R + P * P * kX;  // t1[a c][x], t2[a][y x]
     contract<P, N, P * P, W, double>(
@@ -331,12 +380,10 @@ __device__ __forceinline__ void final_passes(const double* V, Uniform<double> At
         wave, lane, At, [&](int ax, int c) { return t1[(ax / N * P + c) * kX + ax % N]; },
         [&](int ax, int y, double v) { t2[ax / N * kA + y * N + ax % N] = v; });
     __syncthreads();
-    const T* v = vnear + b * (N2 * N);
     T* o = u + b * (N2 * N);
     contract_onto<P, N, N2, W, double>(
-        wave, lane, At, [&](int yx, int a) { return t2[a * kA + yx]; },
-        [&](int yx, int z) { return has_near ? v[z * N2 + yx] : T(0); },  // no near field: v is not read
-        [&](int yx, int z, double acc, T near) { o[z * N2 + yx] = (T)((double)near + acc); });
+        wave, lane, At, [&](int yx, int a) { return t2[a * kA + yx]; }, [&](int, int, int i) { return near[i]; },
+        [&](int yx, int z, double acc, T v) { o[z * N2 + yx] = (T)((double)v + acc); });
 }
 
 // The level-1 inverse transform, Interp from level 2 and the interpolation to the block in one
@@ -352,9 +399,14 @@ __global__ void __launch_bounds__(kInvThreads)
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const int64_t q = l1map ? (int64_t)uniform_ptr(l1map)[b] : b;  // level-1 interval of this block
-    node_values<T, P, P + 1, kInvThreads>(uhat, nint, up, par, uniform_ptr(Ct), q, R, V, tid);
-    final_passes<T, N, P, kInvThreads / 64>(V, uniform_ptr(At), R, vnear, u, b, !near_flag || near_flag[b],
-                                            __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
+    constexpr int W = kInvThreads / 64;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool has_near = !near_flag || near_flag[b];
+    T near[FinalShare<N, W>::CH];
+    node_values<T, P, P + 1, kInvThreads>(uhat, nint, up, par, uniform_ptr(Ct), q, R, V, tid, [&] {
+        near_values<T, N, W>(vnear, b, has_near, wave, lane, near);
+    });
+    final_passes<T, N, P, W>(V, uniform_ptr(At), R, near, u, b, wave, lane);
 }
 
 // From node values in HBM (the lattice scheme).
@@ -367,10 +419,13 @@ __global__ void __launch_bounds__(kLatThreads)
     const int tid = threadIdx.x;
     const int64_t b = blockIdx.x;
     const int64_t q = l1map ? (int64_t)uniform_ptr(l1map)[b] : b;  // level-1 interval of this block
+    constexpr int W = kLatThreads / 64;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    T near[FinalShare<N, W>::CH];
+    near_values<T, N, W>(vnear, b, !near_flag || near_flag[b], wave, lane, near);
     for (int i = tid; i < P3; i += kLatThreads) V[(i / P) * PR + i % P] = ut[q * P3 + i];
     __syncthreads();
-    final_passes<T, N, P, kLatThreads / 64>(V, uniform_ptr(At), R, vnear, u, b, !near_flag || near_flag[b],
-                                            __builtin_amdgcn_readfirstlane(tid >> 6), tid & 63);
+    final_passes<T, N, P, W>(V, uniform_ptr(At), R, near, u, b, wave, lane);
 }
 
 // ------------------------------------------------------------------ launchers
