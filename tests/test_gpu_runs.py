@@ -1,4 +1,6 @@
-"""GPU test of the level-0 Prod's runs: stacks of 2^3-block groups in z that one wave marches
+"""GPU tests of the product kernels' work splits and of the plan's schedule.
+
+The level-0 Prod's runs are stacks of 2^3-block groups in z that one wave marches
 through.  A plan's runs are longer the more groups it has, so a tall layout alone (runs of one
 group) and a batch of many copies of it (runs of up to eight) take different paths.  Every target
 adds its sources in one order whatever the run, so the two agree bit for bit; the layout alone is
@@ -89,4 +91,36 @@ def test_m2l_parent_counts(L, parents, prec):
     for fw, fc in ((1, 1), (16, 8), (4, 4), (2, 2), (8, 0)):
         plan.set_tuning(far_waves=fw, far_children=fc)
         assert torch.equal(plan.solve(fd), u), (fw, fc)
+    plan.close()
+
+
+@pytest.mark.parametrize("blocks_n", [(60, 16), (61, 16), (1023, 4), (1024, 4), (1025, 4)],
+                         ids=lambda v: "%d_of_%d3" % v)
+def test_default_schedule_and_field_stride(L, blocks_n):
+    """Sides of two lines: the plan's own schedule (one stream below 2^20 coefficients of level-0
+    spectra: 60 and 61 blocks of 16^3) against every pinned one, eager and as a graph, bit for bit;
+    and the level-0 field spectra's extra item at 1024 targets, against the oracle with the bar of
+    tolerances.py."""
+    count, n = blocks_n
+    p = 4
+    print("case: schedule", count, "blocks of", n, flush=True)
+    blocks = np.array([(i % 8, i // 8 % 8, i // 64) for i in range(count)], dtype=np.int32)
+    f = np.random.default_rng(count).standard_normal((count, n, n, n))
+    plan = L.Plan(blocks, n, p, 0, "f64")
+    fd = torch.from_numpy(f).to("cuda:0")
+    u = plan.solve(fd)
+    ref = flgf.FLGF(blocks, n, p, 0).solve(f)
+    assert rel(u.cpu().numpy(), ref) <= fp64_tol(p)
+    for ov in (0, 1, 2, 3):
+        plan.set_tuning(overlap=ov)
+        assert torch.equal(plan.solve(fd), u), ov
+        ug = torch.full_like(u, float("nan"))
+        g = plan.graph(fd, ug)
+        for _ in range(2):
+            g.launch()
+            torch.cuda.synchronize()
+            assert torch.equal(ug, u), ov
+            ug.fill_(float("nan"))
+            plan.solve(fd)
+        g.close()
     plan.close()
