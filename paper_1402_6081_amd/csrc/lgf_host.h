@@ -38,6 +38,14 @@ constexpr int spec_padded(int S) { return (S + kSpecChunk - 1) / kSpecChunk * kS
 // sentinel item beside theirs.
 constexpr int64_t field_items(int64_t n) { return n % 1024 == 0 ? n + 1 : n; }
 
+// Do the 32-bit offsets of a level-0 Prod wave that covers `chunks` consecutive chunks reach its
+// output (`items` items per chunk)?  An item's own offset is in the 64-bit base, so the last byte
+// lies chunks - 1 chunks and one item further on.  No plan with a far field is refused by it: the
+// M2L's offsets span all the level-1 intervals, each near target among them, and end first.
+constexpr bool near_fields_fit(int64_t items, int chunks, int64_t coef_bytes) {
+    return ((chunks - 1) * items + 1) * kSpecChunk * coef_bytes <= (int64_t)UINT32_MAX;
+}
+
 // Tiles of 17 nodes take the two-phase transforms, whose HBM intermediate holds
 // nbatch * m * 2m * (m + 1) complex values of 16 bytes.
 inline bool two_phase_tile(int m) { return m == 17; }

@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(64 * kNearWaves) k_prod_near_grouped(const Nea
     lane_pos(lane, my_chunk, wl);
     const bool live = my_chunk < nchunks;
     if (!live) my_chunk = unit * FPL;
-    const int w = my_chunk * 64 + wl;  // first frequency of this lane (S is a multiple of 64)
+    const int w = my_chunk * 64 + wl;  // first frequency of this lane (S is even; it may end inside the last chunk)
     // this wave's run (waves past the last run only help to fill the tile)
     const int run = wave_uniform(gb * kNearWaves + (int)(threadIdx.x >> 6));
     const bool active = run < nruns;
@@ -217,12 +217,13 @@ __global__ void __launch_bounds__(64 * kNearWaves) k_prod_near_grouped(const Nea
         }
     }
     // this lane's byte offset from an item's coefficients in the unit's first chunk: its chunk,
-    // then its frequencies; dead lanes read as live ones do and store out of range (dropped)
+    // then its frequencies; dead lanes read as live ones do and store out of range (at ~15u, above
+    // every range and with all 16 bytes below 2^32; dropped)
     const uint32_t lbytes = (uint32_t)(my_chunk - unit * FPL) * (uint32_t)(nsrc + 1) * kItemBytes<T> +
                             (uint32_t)wl * (uint32_t)sizeof(cplx<T>);
     const uint32_t sbytes = live ? (uint32_t)(my_chunk - unit * FPL) * (uint32_t)ntgt * kItemBytes<T> +
                                        (uint32_t)wl * (uint32_t)sizeof(cplx<T>)
-                                 : ~0u;
+                                 : ~15u;
     const char* const fbase = reinterpret_cast<const char*>(fhat + (int64_t)(unit * FPL) * (nsrc + 1) * 64);
     char* const ubase = reinterpret_cast<char*>(uhat + (int64_t)(unit * FPL) * ntgt * 64);
     // bytes from an item's first coefficient to the end of the lanes' last (0: reads as zeros,
@@ -720,11 +721,12 @@ static hipError_t near_nw(const NearLevel<T>& n, hipStream_t s) {
     return lgf_launch(k_prod_near_grouped<T, NW, kNearFpl<T>>, dim3(grid), dim3(64 * NW), 0, s, a);
 }
 
-// a lane's 32-bit offsets span kNearFpl consecutive chunks of the source spectra and of the output
+// a lane's 32-bit offsets span kNearFpl consecutive chunks of the source spectra, and reach one item
+// in the last of as many chunks of the output
 template <typename T>
 static bool near_fits(const NearLevel<T>& n) {
     return n.S > 0 && n.S % 2 == 0 && chunk_fits_u32<T>((n.nsrc + 1) * kNearFpl<T>) &&
-           chunk_fits_u32<T>(n.ntgt * kNearFpl<T>) && sym_fits(n.sym, n.S);
+           near_fields_fit(n.ntgt, kNearFpl<T>, sizeof(cplx<T>)) && sym_fits(n.sym, n.S);
 }
 
 template <typename T>
