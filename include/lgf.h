@@ -242,8 +242,8 @@ typedef struct {
     int32_t overlap;        /* schedule of a solve: 1 three concurrent branches (near field, level 1,
                                levels >= 2), 3 two (near field, levels >= 1), 2 one stream,
                                0 by plan: 1 for the lattice scheme, 2 for the smallest plans, else
-                               1 for eager solves and 3 for graphs.  With 3 and 2 the M2L of all
-                               levels with one tile size is one launch                               */
+                               3 for graphs and for separate sets, 1 for other eager solves.  With 3
+                               and 2 the M2L of all levels with one tile size is one launch          */
 } lgf_tuning;
 
 /*

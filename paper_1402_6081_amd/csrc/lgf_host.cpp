@@ -468,6 +468,38 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
     return U;
 }
 
+// Microseconds of an eager solve / of a graph launch, each back to back, in one stream, two and
+// three branches (16^3 blocks, p = 8, unless stated):
+//   64 blocks of 8^3, FP64 (0.15M coefficients of level-0 source spectra)   36/42    48/44    48/46
+//   40 blocks, FP32 (0.70M)                                                 62/67    62/71    61/71
+//   64 blocks, FP64 (1.1M)                                                  69/75    67/70    65/78
+//   128^3, FP64 (8.9M)                                                     232/238  198/201  208/235
+//   256^3, FP64 (71M)                                                     1506/1513 1480/1488 1442/1499
+//   128^3, lattice scheme p = 17, FP64                                     640/647  626/619  553/534
+//   8 source blocks at a corner of 1000 (27 near), FP64                    108/115  107/100  123/101
+//   48 source blocks at a corner of 1000 (100 near), FP64                  122/130  117/114  135/123
+//   41 source blocks scattered among 4096, FP64                            433/441  391/388  410/410
+//   1000 source blocks, 27 evaluated, FP64                                 238/246  238/225  246/225
+//   ring of 126 source blocks in 216, FP64                                 123/130  126/118  138/134
+//   ring of 902 source blocks in 4096, FP64                                751/758  705/710  702/739
+// Small plans lose more to the events between streams than they gain: below 2^20 coefficients of
+// the sources or near targets, whichever are more; a graph, whose edges cost less, counts every
+// evaluation block.  With two branches the merged M2L of all levels runs beside the level-0 Prod;
+// with three it starts with the level-0 transform, whose LDS tiles and its own keep each other off
+// the CUs.  A graph gains from that at every size; a single eager solve does not always (128^3
+// FP64, each solve waited for: 206 in two branches, 200 in three; batch of 48, 665 and 655), so it
+// keeps three, except where the sets differ: the near field is then the smaller part and nothing
+// is lost.  The lattice scheme's level 2 has 17^3 tiles of its own, about as long as its level 1,
+// which gain from a branch of their own.
+int default_schedule(const HostPlan& H, bool graph) {
+    if (H.lat1) return 1;
+    const bool split = !H.eval_l1.empty();
+    const int64_t S0 = spec_padded(2 * H.n * 2 * H.n * (H.n + 1));
+    const int64_t work = std::max(H.nsrc, graph ? H.neval : H.ntgt0) * S0;
+    if (work < (int64_t)1 << 20) return 2;
+    return graph || split ? 3 : 1;
+}
+
 // HBM intermediate of the two-phase transforms (levels >= 2 of a tile that does not fit one
 // workgroup's LDS); the levels run one after another on one stream and share it.
 int64_t scratch_need(const HostPlan& H) {

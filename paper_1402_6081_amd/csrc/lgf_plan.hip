@@ -511,28 +511,6 @@ hipError_t solve_dispatch(lgf_plan_s* pl, const void* f, void* u, hipStream_t s)
                                : run_solve<float>(pl, (const float*)f, (float*)u, s);
 }
 
-// The schedule of a plan that is not told one (lgf_tuning.overlap 0; every schedule gives the same
-// bits).  Microseconds of an eager solve / of a graph launch, each back to back, in one stream, two
-// and three branches:
-//   64 blocks of 8^3, FP64 (0.15M coefficients of level-0 source spectra)   36/42    48/44    48/46
-//   40 blocks of 16^3, FP32 (0.70M)                                         62/67    62/71    61/71
-//   64 blocks of 16^3, FP64 (1.1M)                                          69/75    67/70    65/78
-//   128^3 in 16^3 blocks, FP64 (8.9M)                                      232/238  198/201  208/235
-//   256^3 in 16^3 blocks, FP64 (71M)                                      1506/1513 1480/1488 1442/1499
-//   128^3, lattice scheme p = 17, FP64                                     640/647  626/619  553/534
-// Small plans lose more to the events between streams than they gain.  With two branches the
-// merged M2L of all levels runs beside the level-0 Prod; with three it starts with the level-0
-// transform, whose LDS tiles and its own keep each other off the CUs.  A graph gains from that at
-// every size; a single eager solve does not always (128^3 FP64, each solve waited for: 206 in two
-// branches, 200 in three; batch of 48, 665 and 655), so it keeps three.  The lattice scheme's
-// level 2 has 17^3 tiles of its own, about as long as its level 1, which gain from a branch of
-// their own.
-static int default_schedule(const HostPlan& H, int64_t S0, bool graph) {
-    if (H.lat1) return 1;
-    if (H.nsrc * S0 < (int64_t)1 << 20) return 2;
-    return graph ? 3 : 1;
-}
-
 lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream_t s, lgf_plan_s* pl) {
     const int n = H.n, p = H.p;
     pl->kappa = kappa;
@@ -559,8 +537,8 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
         hipEventCreateWithFlags(&pl->ev_join2, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&pl->ev_done, hipEventDisableTiming) != hipSuccess)
         return fail(LGF_ERR_DEVICE, "stream/event creation failed");
-    pl->schedule = default_schedule(H, spec_padded(2 * n * 2 * n * (n + 1)), false);
-    pl->graph_schedule = default_schedule(H, spec_padded(2 * n * 2 * n * (n + 1)), true);
+    pl->schedule = default_schedule(H, false);
+    pl->graph_schedule = default_schedule(H, true);
     pl->lv.assign(H.L + 1, LevelPlan());
     for (int l = 1; l <= H.L; ++l) {
         pl->lv[l].nint = H.lv[l].nint;

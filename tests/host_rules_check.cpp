@@ -1,9 +1,13 @@
 // The plan's rules that need no device (lgf_host.h), for tests/test_host_rules.py.  Reads one
 // query per line from stdin and prints one answer per line:
 //   fields items chunks bytes        near_fields_fit
+//   schedule n p levels edge ex ey ez step
+//                                    default_schedule, eager and graph, of the cube of edge^3 blocks;
+//                                    ex > 0: f on every step-th block of its corner of ex x ey x ez
 #include <iostream>
 #include <sstream>
 #include <string>
+#include <vector>
 
 #include "lgf_host.h"
 
@@ -20,6 +24,23 @@ int main() {
             int chunks = 0, bytes = 0;
             in >> items >> chunks >> bytes;
             std::cout << near_fields_fit(items, chunks, bytes) << "\n";
+        } else if (kind == "schedule") {
+            int n = 0, p = 0, levels = 0, edge = 0, ex = 0, ey = 0, ez = 0, step = 1;
+            in >> n >> p >> levels >> edge >> ex >> ey >> ez >> step;
+            std::vector<int32_t> all, src;
+            int k = 0;
+            for (int z = 0; z < edge; ++z)
+                for (int y = 0; y < edge; ++y)
+                    for (int x = 0; x < edge; ++x) {
+                        all.insert(all.end(), {x, y, z});
+                        if (x < ex && y < ey && z < ez && k++ % step == 0) src.insert(src.end(), {x, y, z});
+                    }
+            HostPlan H;
+            const lgf_status st = src.empty() ? build_host(all.data(), (int64_t)all.size() / 3, n, p, levels, H)
+                                              : build_host(src.data(), (int64_t)src.size() / 3, n, p, levels, H,
+                                                           all.data(), (int64_t)all.size() / 3);
+            if (st != LGF_OK) return 3;
+            std::cout << default_schedule(H, false) << " " << default_schedule(H, true) << "\n";
         } else {
             std::cerr << "unknown query " << kind << "\n";
             return 2;

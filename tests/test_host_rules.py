@@ -42,3 +42,19 @@ def test_near_fields_never_refuse_first(ask):
         assert ask("fields %d %d %d" % (most, chunks, bytes_), "fields %d %d %d" % (most // 2 + 2, chunks, bytes_),
                    "fields 1 %d %d" % (chunks, bytes_)) == [[1], [1], [1]]
     assert ask("fields %d 2 8" % (2 ** 32 // 512 - 1)) == [[0]]
+
+
+def test_default_schedule(ask):
+    """The schedule (1 three branches, 3 two, 2 one stream) of eager solves and of graphs on both
+    sides of the line of small plans: 2^20 coefficients of 16^3-block spectra (17408 each) are 60.2
+    blocks, of 8^3-block spectra (2304 each) 455.1.  Few sources do not make a plan small when they
+    have many near targets (eager) or evaluation blocks (graphs)."""
+    plain = "0 0 0 1"
+    assert ask("schedule 16 8 0 3 " + plain, "schedule 16 8 0 4 " + plain, "schedule 8 6 0 7 " + plain,
+               "schedule 8 6 0 8 " + plain) == [[2, 2], [1, 3], [2, 2], [1, 3]]
+    # separate sets: 8 sources with 27 near targets, 36 with 84, 41 scattered among 4096, one source in
+    # a small set
+    assert ask("schedule 16 8 0 10 2 2 2 1", "schedule 16 8 0 10 6 3 2 1", "schedule 16 8 0 16 16 16 16 100",
+               "schedule 16 8 0 3 1 1 1 1") == [[2, 3], [3, 3], [3, 3], [2, 2]]
+    # the lattice scheme
+    assert ask("schedule 16 17 0 2 " + plain, "schedule 16 17 0 8 " + plain) == [[1, 1], [1, 1]]
