@@ -242,8 +242,10 @@ typedef struct {
     int32_t overlap;        /* schedule of a solve: 1 three concurrent branches (near field, level 1,
                                levels >= 2), 3 two (near field, levels >= 1), 2 one stream,
                                0 by plan: 1 for the lattice scheme, 2 for the smallest plans, else
-                               3 for graphs and for separate sets, 1 for other eager solves.  With 3
-                               and 2 the M2L of all levels with one tile size is one launch          */
+                               3 for graphs and for separate sets, 1 for other eager solves; a tree
+                               cut at one level takes 1 in graphs and, eagerly, 2 in FP64 and 3 in
+                               FP32.  With 3 and 2 the M2L of all levels with one tile size is one
+                               launch                                                                */
 } lgf_tuning;
 
 /*

@@ -482,6 +482,11 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
 //   1000 source blocks, 27 evaluated, FP64                                 238/246  238/225  246/225
 //   ring of 126 source blocks in 216, FP64                                 123/130  126/118  138/134
 //   ring of 902 source blocks in 4096, FP64                                751/758  705/710  702/739
+//   125 blocks, one level, FP64                                            152/161  174/167  166/148
+//   216 blocks, one level, FP64                                            332/341  355/361  359/309
+//   125 blocks, one level, FP32                                            114/121  112/117  127/107
+//   216 blocks, one level, FP32                                            217/224  211/209  210/193
+//   125 blocks of 8^3, one level, p = 6, FP64                               77/85    88/-     88/76
 // Small plans lose more to the events between streams than they gain: below 2^20 coefficients of
 // the sources or near targets, whichever are more; a graph, whose edges cost less, counts every
 // evaluation block.  With two branches the merged M2L of all levels runs beside the level-0 Prod;
@@ -490,13 +495,16 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
 // FP64, each solve waited for: 206 in two branches, 200 in three; batch of 48, 665 and 655), so it
 // keeps three, except where the sets differ: the near field is then the smaller part and nothing
 // is lost.  The lattice scheme's level 2 has 17^3 tiles of its own, about as long as its level 1,
-// which gain from a branch of their own.
-int default_schedule(const HostPlan& H, bool graph) {
+// which gain from a branch of their own.  A tree cut at one level has the all-pairs list as its far
+// field, as long as the near field from few blocks on; beside each other the two products gain in
+// graphs, and in eager solves in FP32 alone.
+int default_schedule(const HostPlan& H, lgf_precision prec, bool graph) {
     if (H.lat1) return 1;
-    const bool split = !H.eval_l1.empty();
+    const bool one_level = H.Ltop == 1 && !H.lv[1].csr_src.empty(), split = !H.eval_l1.empty();
     const int64_t S0 = spec_padded(2 * H.n * 2 * H.n * (H.n + 1));
     const int64_t work = std::max(H.nsrc, graph ? H.neval : H.ntgt0) * S0;
-    if (work < (int64_t)1 << 20) return 2;
+    if (work < (int64_t)1 << (graph && one_level ? 18 : 20)) return 2;
+    if (one_level) return graph ? 1 : prec == LGF_F64 ? 2 : 3;
     return graph || split ? 3 : 1;
 }
 

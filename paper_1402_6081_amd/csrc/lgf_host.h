@@ -154,7 +154,7 @@ inline bool needs_util(const HostPlan& H, int l) { return H.lat1 || l >= 2; }
 
 // The schedule of a plan that is not told one: 1 three branches, 3 two, 2 one stream
 // (lgf_tuning.overlap 0; every schedule gives the same bits).
-int default_schedule(const HostPlan& H, bool graph);
+int default_schedule(const HostPlan& H, lgf_precision prec, bool graph);
 
 // HBM intermediate of the two-phase transforms and of the 17-node Reg up.
 int64_t scratch_need(const HostPlan& H);

@@ -537,8 +537,8 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
         hipEventCreateWithFlags(&pl->ev_join2, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&pl->ev_done, hipEventDisableTiming) != hipSuccess)
         return fail(LGF_ERR_DEVICE, "stream/event creation failed");
-    pl->schedule = default_schedule(H, false);
-    pl->graph_schedule = default_schedule(H, true);
+    pl->schedule = default_schedule(H, prec, false);
+    pl->graph_schedule = default_schedule(H, prec, true);
     pl->lv.assign(H.L + 1, LevelPlan());
     for (int l = 1; l <= H.L; ++l) {
         pl->lv[l].nint = H.lv[l].nint;

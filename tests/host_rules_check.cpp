@@ -1,7 +1,7 @@
 // The plan's rules that need no device (lgf_host.h), for tests/test_host_rules.py.  Reads one
 // query per line from stdin and prints one answer per line:
 //   fields items chunks bytes        near_fields_fit
-//   schedule n p levels edge ex ey ez step
+//   schedule n p levels prec edge ex ey ez step
 //                                    default_schedule, eager and graph, of the cube of edge^3 blocks;
 //                                    ex > 0: f on every step-th block of its corner of ex x ey x ez
 #include <iostream>
@@ -25,8 +25,8 @@ int main() {
             in >> items >> chunks >> bytes;
             std::cout << near_fields_fit(items, chunks, bytes) << "\n";
         } else if (kind == "schedule") {
-            int n = 0, p = 0, levels = 0, edge = 0, ex = 0, ey = 0, ez = 0, step = 1;
-            in >> n >> p >> levels >> edge >> ex >> ey >> ez >> step;
+            int n = 0, p = 0, levels = 0, prec = 0, edge = 0, ex = 0, ey = 0, ez = 0, step = 1;
+            in >> n >> p >> levels >> prec >> edge >> ex >> ey >> ez >> step;
             std::vector<int32_t> all, src;
             int k = 0;
             for (int z = 0; z < edge; ++z)
@@ -40,7 +40,8 @@ int main() {
                                               : build_host(src.data(), (int64_t)src.size() / 3, n, p, levels, H,
                                                            all.data(), (int64_t)all.size() / 3);
             if (st != LGF_OK) return 3;
-            std::cout << default_schedule(H, false) << " " << default_schedule(H, true) << "\n";
+            const lgf_precision pr = prec == 64 ? LGF_F64 : LGF_F32;
+            std::cout << default_schedule(H, pr, false) << " " << default_schedule(H, pr, true) << "\n";
         } else {
             std::cerr << "unknown query " << kind << "\n";
             return 2;

@@ -50,11 +50,21 @@ def test_default_schedule(ask):
     blocks, of 8^3-block spectra (2304 each) 455.1.  Few sources do not make a plan small when they
     have many near targets (eager) or evaluation blocks (graphs)."""
     plain = "0 0 0 1"
-    assert ask("schedule 16 8 0 3 " + plain, "schedule 16 8 0 4 " + plain, "schedule 8 6 0 7 " + plain,
-               "schedule 8 6 0 8 " + plain) == [[2, 2], [1, 3], [2, 2], [1, 3]]
-    # separate sets: 8 sources with 27 near targets, 36 with 84, 41 scattered among 4096, one source in
-    # a small set
-    assert ask("schedule 16 8 0 10 2 2 2 1", "schedule 16 8 0 10 6 3 2 1", "schedule 16 8 0 16 16 16 16 100",
-               "schedule 16 8 0 3 1 1 1 1") == [[2, 3], [3, 3], [3, 3], [2, 2]]
-    # the lattice scheme
-    assert ask("schedule 16 17 0 2 " + plain, "schedule 16 17 0 8 " + plain) == [[1, 1], [1, 1]]
+    for prec in (64, 32):
+        assert ask("schedule 16 8 0 %d 3 %s" % (prec, plain), "schedule 16 8 0 %d 4 %s" % (prec, plain),
+                   "schedule 8 6 0 %d 7 %s" % (prec, plain), "schedule 8 6 0 %d 8 %s" % (prec, plain)) == [
+            [2, 2], [1, 3], [2, 2], [1, 3]]
+        # separate sets: 8 sources with 27 near targets, 36 with 84, 41 scattered among 4096, one source
+        # in a small set
+        assert ask("schedule 16 8 0 %d 10 2 2 2 1" % prec, "schedule 16 8 0 %d 10 6 3 2 1" % prec,
+                   "schedule 16 8 0 %d 16 16 16 16 100" % prec, "schedule 16 8 0 %d 3 1 1 1 1" % prec) == [
+            [2, 3], [3, 3], [3, 3], [2, 2]]
+        # the lattice scheme
+        assert ask("schedule 16 17 0 %d 2 %s" % (prec, plain), "schedule 16 17 0 %d 8 %s" % (prec, plain)) == [
+            [1, 1], [1, 1]]
+        # one level, the all-pairs list its far field (graphs' line: 2^18 coefficients, 113.8 blocks of
+        # 8^3); two levels follow the general rule
+        eager = 2 if prec == 64 else 3
+        assert ask("schedule 16 8 1 %d 5 %s" % (prec, plain), "schedule 8 6 1 %d 4 %s" % (prec, plain),
+                   "schedule 8 6 1 %d 5 %s" % (prec, plain), "schedule 16 8 2 %d 5 %s" % (prec, plain)) == [
+            [eager, 1], [2, 2], [2, 1], [1, 3]]
