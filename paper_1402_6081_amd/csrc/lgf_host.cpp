@@ -508,6 +508,25 @@ int default_schedule(const HostPlan& H, lgf_precision prec, bool graph) {
     return graph || split ? 3 : 1;
 }
 
+// A lane that takes all 8 children reads each kernel value once for all of them, and 64 parents
+// share one kernel tile (256^3 FP64, 512 parents: 308 us, with 32 parents 338, with 4 children per
+// lane 359; 48 ragged layouts FP32, 615 parents: 137, 152, 199).  Two kinds of levels do better with
+// less per lane and workgroup (us of the M2L of all levels):
+// - Below 32 parents, 2 children per lane and 8 parents: more waves for little work (64 blocks of
+//   8^3 FP64, 8 parents: 9.0 against 12.4; 38 blocks of 16^3 FP32: 10.4 against 12.4).
+// - Few waves (parents x S / 64 with all children per lane below 1280, 1.25 per SIMD), as the few
+//   frequencies of p <= 5 give: 4 children per lane and workgroups of 8 waves.  p = 2, 216 parents
+//   (162 waves): FP64 40 -> 26, FP32 45 -> 22; p = 4, 216 (1080): 43 -> 38, 47 -> 32; p = 6, 64
+//   (1008): 33 -> 26, 31 -> 24; above, p = 7, 58 (1421): 36 -> 35, 28.7 -> 30.0; FP32 p = 3, 672
+//   (1512): 48 -> 53.  Not from 1024 parents on, where the many parents per frequency fill the chip
+//   (FP64 p = 2, 1728 parents, 1296 waves: 45 -> 49), and not for blocks of 16^3, whose level-0 Prod
+//   hides the M2L and is slowed by more of its waves (512 blocks, p = 6, FP64 eager: 184 -> 191).
+M2LVariant m2l_default(int64_t parents, int64_t S, int F, int n) {
+    if (parents < 32) return {2, 8};
+    if (n < 16 && parents < 1024 && parents * S < 64 * 1280) return {4, 256 / F};
+    return {8, 64};
+}
+
 // HBM intermediate of the two-phase transforms (levels >= 2 of a tile that does not fit one
 // workgroup's LDS); the levels run one after another on one stream and share it.
 int64_t scratch_need(const HostPlan& H) {

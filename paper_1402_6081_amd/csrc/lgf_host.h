@@ -156,6 +156,14 @@ inline bool needs_util(const HostPlan& H, int l) { return H.lat1 || l >= 2; }
 // (lgf_tuning.overlap 0; every schedule gives the same bits).
 int default_schedule(const HostPlan& H, lgf_precision prec, bool graph);
 
+// M2L variant of a launch whose largest level has `parents` parents and spectra of S
+// coefficients, F of which a wave's lanes take (8 FP64, 16 FP32), in a plan of n^3 blocks: children
+// per lane and parents per workgroup.  Every variant computes the same bits.
+struct M2LVariant {
+    int children, parents;
+};
+M2LVariant m2l_default(int64_t parents, int64_t S, int F, int n);
+
 // HBM intermediate of the two-phase transforms and of the 17-node Reg up.
 int64_t scratch_need(const HostPlan& H);
 

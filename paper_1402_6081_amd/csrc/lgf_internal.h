@@ -204,6 +204,7 @@ struct FarLevel {
     // (mask, child8, src216) by decreasing number of neighbours
     const uint32_t* mask;
     bool heavy_first;  // the parents' numbers of neighbours spread widely (HostLevel::m2l_spread)
+    int n;             // the plan's block edge
 };
 template <typename T>
 hipError_t launch_prod_far_sib_levels(const FarLevel<T>* lv, int nlev, int waves, int cpl, hipStream_t s);

@@ -296,7 +296,8 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
                            L.spectra->S,
                            L.spectra->sym,
                            Pp.d_m2l_mask,
-                           Pp.m2l_spread};
+                           Pp.m2l_spread,
+                           n};
     };
     // Interp of the lattice scheme from level l + 1 down to level l, accumulated
     auto interp = [&](int l, hipStream_t st) -> hipError_t {

@@ -804,30 +804,16 @@ static hipError_t far_cpl(const FarLevel<T>* lv, int nlev, int waves, hipStream_
     return far_nw<T, 1, CPL>(lv, nlev, s);
 }
 
-// Variant when the plan leaves it open, by the parents of the launch's largest level: from 32
-// on, all 8 children per lane and 64 parents per workgroup, which share one kernel tile (256^3
-// FP64, 512 parents: 308 us, with 32 parents 338, with 4 children per lane 359; 48 ragged layouts
-// FP32, 615 parents: 137, 152, 199; 128^3, 64 parents: FP64 50, 59, 54, FP32 33, 39, 49); below,
-// 2 children per lane and 8 parents (64 blocks of 8^3 FP64, 8 parents: 9.0 us against 12.4 with
-// all children; 38 blocks of 16^3 FP32: 10.4 against 12.4): more waves for little work.  Every
-// variant computes the same bits.
-template <typename T>
-void m2l_default(int64_t nparents, int& waves, int& cpl) {
-    const bool big = nparents >= 32;
-    if (cpl == 0) cpl = big ? 8 : 2;
-    if (waves == 0) waves = (big ? 64 : 8) / M2LShape<T>::PPW;
-}
-
 // Number of levels with parents (empty levels only at the end), or -1 where a level does not
-// fit what the kernels assume; most: parents of the largest.
+// fit what the kernels assume; most: the one with the most parents.
 template <typename T>
-static int far_check(const FarLevel<T>* lv, int nlev, int64_t& most) {
+static int far_check(const FarLevel<T>* lv, int nlev, const FarLevel<T>*& most) {
     int k = 0;
-    most = 0;
+    most = lv;
     for (int i = 0; i < nlev; ++i) {
         if (lv[i].nparents <= 0) continue;
         if (k != i || !lv[i].mask || !chunk_fits_u32<T>(lv[i].nsrc + 1) || !sym_fits(lv[i].sym, lv[i].S)) return -1;
-        most = lv[i].nparents > most ? lv[i].nparents : most;
+        if (lv[i].nparents > most->nparents) most = lv + i;
         ++k;
     }
     return k > kMaxFarSegs ? -1 : k;
@@ -835,11 +821,13 @@ static int far_check(const FarLevel<T>* lv, int nlev, int64_t& most) {
 
 template <typename T>
 hipError_t launch_prod_far_sib_levels(const FarLevel<T>* lv, int nlev, int waves, int cpl, hipStream_t s) {
-    int64_t most = 0;
+    const FarLevel<T>* most = nullptr;
     const int k = far_check<T>(lv, nlev, most);
     if (k < 0) return hipErrorInvalidValue;
     if (k == 0) return hipSuccess;
-    m2l_default<T>(most, waves, cpl);
+    const M2LVariant open = m2l_default(most->nparents, most->S, M2LShape<T>::F, most->n);
+    if (cpl == 0) cpl = open.children;
+    if (waves == 0) waves = open.parents / M2LShape<T>::PPW;
     switch (cpl) {
         case 8: return far_cpl<T, 8>(lv, k, waves, s);
         case 4: return far_cpl<T, 4>(lv, k, waves, s);

@@ -1,6 +1,7 @@
 // The plan's rules that need no device (lgf_host.h), for tests/test_host_rules.py.  Reads one
 // query per line from stdin and prints one answer per line:
 //   fields items chunks bytes        near_fields_fit
+//   m2l parents S F n                m2l_default: children per lane, parents per workgroup
 //   schedule n p levels prec edge ex ey ez step
 //                                    default_schedule, eager and graph, of the cube of edge^3 blocks;
 //                                    ex > 0: f on every step-th block of its corner of ex x ey x ez
@@ -24,6 +25,12 @@ int main() {
             int chunks = 0, bytes = 0;
             in >> items >> chunks >> bytes;
             std::cout << near_fields_fit(items, chunks, bytes) << "\n";
+        } else if (kind == "m2l") {
+            long long parents = 0, S = 0;
+            int F = 0, n = 0;
+            in >> parents >> S >> F >> n;
+            const M2LVariant v = m2l_default(parents, S, F, n);
+            std::cout << v.children << " " << v.parents << "\n";
         } else if (kind == "schedule") {
             int n = 0, p = 0, levels = 0, prec = 0, edge = 0, ex = 0, ey = 0, ez = 0, step = 1;
             in >> n >> p >> levels >> prec >> edge >> ex >> ey >> ez >> step;

@@ -68,3 +68,16 @@ def test_default_schedule(ask):
         assert ask("schedule 16 8 1 %d 5 %s" % (prec, plain), "schedule 8 6 1 %d 4 %s" % (prec, plain),
                    "schedule 8 6 1 %d 5 %s" % (prec, plain), "schedule 16 8 2 %d 5 %s" % (prec, plain)) == [
             [eager, 1], [2, 2], [2, 1], [1, 3]]
+
+
+def test_m2l_variant(ask):
+    """The M2L's default variant counts the waves that a level gives, parents x S / 64 with
+    S = 4 p^2 (p + 1), not its parents alone: with the few frequencies of p <= 5, workgroups of 64
+    parents leave most of the chip idle.  The lines: 32 and 1024 parents, 1280 waves, blocks of 16^3."""
+    S = {p: 4 * p * p * (p + 1) for p in (2, 4, 5, 8)}
+    cases = [(31, 8, 8, 2), (32, 8, 8, 4), (35, 8, 8, 4), (36, 8, 8, 8), (35, 8, 16, 8), (64, 8, 8, 8), (64, 5, 8, 4),
+             (136, 5, 4, 4), (137, 5, 4, 8), (216, 4, 12, 4), (216, 4, 16, 8), (1023, 2, 4, 4), (1024, 2, 4, 8),
+             (31, 2, 16, 2), (512, 8, 16, 8)]
+    for F in (8, 16):
+        got = ask(*["m2l %d %d %d %d" % (parents, S[p], F, n) for parents, p, n, _ in cases])
+        assert got == [[c, {2: 8, 4: 256 // F, 8: 64}[c]] for _, _, _, c in cases]
