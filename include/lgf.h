@@ -259,15 +259,18 @@ typedef struct {
  * precision, power-of-two block-count bucket) in this process; if the environment variable
  * LGF_TUNE_FILE names a file the choice is appended there and read by later processes.
  * A graph runs the schedules with other costs (dependencies resolved on the device instead
- * of host events), so a caller that launches graphs picks the overlap its graph is built
- * with by timing one graph per schedule.  Synchronous.  Errors: LGF_ERR_ARG, LGF_ERR_DEVICE.
+ * of host events), so the chosen overlap holds for eager solves alone: graphs, and a server's
+ * solves beside others, keep the plan's own schedule (overlap 0), unless lgf_plan_set_tuning
+ * pins one for every solve.  A caller that launches graphs may pick the overlap its graph is
+ * built with by timing one graph per schedule.  Synchronous.  Errors: LGF_ERR_ARG, LGF_ERR_DEVICE.
  */
 lgf_status lgf_plan_autotune(lgf_plan_t plan, const void* f, void* u, void* hip_stream, int32_t reps);
 
 /* The plan's current variants.  Errors: LGF_ERR_ARG. */
 lgf_status lgf_plan_get_tuning(lgf_plan_t plan, lgf_tuning* out);
 
-/* Pin the plan's variants by hand (HOST struct, read during the call).
+/* Pin the plan's variants by hand (HOST struct, read during the call), an overlap other than 0
+ * for eager solves, graphs and a server's solves alike.
  * Errors: LGF_ERR_ARG (a value outside the lists above). */
 lgf_status lgf_plan_set_tuning(lgf_plan_t plan, const lgf_tuning* tuning);
 

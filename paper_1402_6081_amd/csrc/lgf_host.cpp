@@ -508,6 +508,17 @@ int default_schedule(const HostPlan& H, lgf_precision prec, bool graph) {
     return graph || split ? 3 : 1;
 }
 
+// (A tuned plan's schedule is its fastest eager one, often three branches by a small margin: 64
+// blocks of 16^3, FP64, 65 us against 67 in two, but 78 against 70 as a graph; and 24 requests
+// take 1950 us in three branches each, 1530 in one stream.)
+int solve_schedule(int overlap, bool eager_only, bool lattice, bool beside_others, bool graph, int plan_eager,
+                   int plan_graph) {
+    if (overlap != 0 && !eager_only) return overlap;
+    if (beside_others && !lattice) return 2;
+    if (graph) return plan_graph;
+    return overlap != 0 ? overlap : plan_eager;
+}
+
 // A lane that takes all 8 children reads each kernel value once for all of them, and 64 parents
 // share one kernel tile (256^3 FP64, 512 parents: 308 us, with 32 parents 338, with 4 children per
 // lane 359; 48 ragged layouts FP32, 615 parents: 137, 152, 199).  Two kinds of levels do better with

@@ -156,6 +156,12 @@ inline bool needs_util(const HostPlan& H, int l) { return H.lat1 || l >= 2; }
 // (lgf_tuning.overlap 0; every schedule gives the same bits).
 int default_schedule(const HostPlan& H, lgf_precision prec, bool graph);
 
+// The schedule of one solve.  overlap: the plan's lgf_tuning.overlap, which pins every solve, or
+// where it was chosen by timing eager solves (eager_only) those alone; plan_eager and plan_graph are
+// the plan's default schedules.  Beside other plans' solves one stream, but the lattice scheme's own.
+int solve_schedule(int overlap, bool eager_only, bool lattice, bool beside_others, bool graph, int plan_eager,
+                   int plan_graph);
+
 // M2L variant of a launch whose largest level has `parents` parents and spectra of S
 // coefficients, F of which a wave's lanes take (8 FP64, 16 FP32), in a plan of n^3 blocks: children
 // per lane and parents per workgroup.  Every variant computes the same bits.

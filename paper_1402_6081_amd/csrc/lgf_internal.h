@@ -223,6 +223,7 @@ struct TuneConfig {
     int far_waves = 0;     // waves (parent groups) per workgroup of the level >= 1 Prod: 1 .. 16, 0 = by level size
     int far_children = 0;  // children per lane of that kernel: 8, 4, 2, 1, or 0 = by level size
     int overlap = 0;       // schedule: 1 three branches, 3 two, 2 one stream, 0 = by plan and use
+    bool eager_only = false;  // overlap is the autotuner's, which times eager solves by themselves (solve_schedule)
 };
 
 // The 1D matrices: A p x n and its transpose At n x p (blocks and level 1), C01 the two p x p

@@ -267,10 +267,8 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
     const bool far = pl->Ltop >= 1;
     // overlap: 1 three concurrent branches, 3 two (the coarse levels follow level 1 on one
     // stream), 2 a single stream, 0 the plan's default
-    const int ov = tc.overlap != 0                  ? tc.overlap
-                   : pl->beside_others && !pl->lat1 ? 2
-                   : active_recorder()              ? pl->graph_schedule
-                                                    : pl->schedule;
+    const int ov = solve_schedule(tc.overlap, tc.eager_only, pl->lat1, pl->beside_others, active_recorder() != nullptr,
+                                  pl->schedule, pl->graph_schedule);
     const bool overlap = ov != 2;
     // streams: s = near field (level 0), s2 = level 1, s3 = levels >= 2 (the coarse levels'
     // small kernels run beside the level-1 M2L); one stream when overlap is off.  The fork and
@@ -826,7 +824,9 @@ void apply_cached_tune(lgf_plan_s* pl) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     tune_load_file();
     auto it = g_tune.find(TuneKey{pl->n, pl->p, (int)pl->prec, bucket_of(pl->nb)});
-    if (it != g_tune.end()) pl->tune = it->second;
+    if (it == g_tune.end()) return;
+    pl->tune = it->second;
+    pl->tune.eager_only = true;  // (remembered choices are the autotuner's)
 }
 
 }  // namespace
@@ -1147,6 +1147,7 @@ lgf_status lgf_plan_autotune(lgf_plan_t plan, const void* f, void* u, void* hip_
     // (0 = the per-level default for the level >= 1 Prod knobs)
     TuneConfig best = start;
     best.overlap = 2;
+    best.eager_only = true;
     float best_ms = timed(best);
     const std::vector<std::vector<int>> opts = {{128, 256, 512}, {2, 4, 8}, {0, 1, 2, 4, 8, 16}, {0, 8, 4, 2, 1}};
     for (int sweep = 0; sweep < 2; ++sweep) {

@@ -1,6 +1,8 @@
 // The plan's rules that need no device (lgf_host.h), for tests/test_host_rules.py.  Reads one
 // query per line from stdin and prints one answer per line:
 //   fields items chunks bytes        near_fields_fit
+//   solve overlap eager_only lattice beside graph plan_eager plan_graph
+//                                    solve_schedule
 //   m2l parents S F n                m2l_default: children per lane, parents per workgroup
 //   schedule n p levels prec edge ex ey ez step
 //                                    default_schedule, eager and graph, of the cube of edge^3 blocks;
@@ -25,6 +27,10 @@ int main() {
             int chunks = 0, bytes = 0;
             in >> items >> chunks >> bytes;
             std::cout << near_fields_fit(items, chunks, bytes) << "\n";
+        } else if (kind == "solve") {
+            int v[7] = {};
+            for (int& x : v) in >> x;
+            std::cout << solve_schedule(v[0], v[1] != 0, v[2] != 0, v[3] != 0, v[4] != 0, v[5], v[6]) << "\n";
         } else if (kind == "m2l") {
             long long parents = 0, S = 0;
             int F = 0, n = 0;

@@ -81,3 +81,20 @@ def test_m2l_variant(ask):
     for F in (8, 16):
         got = ask(*["m2l %d %d %d %d" % (parents, S[p], F, n) for parents, p, n, _ in cases])
         assert got == [[c, {2: 8, 4: 256 // F, 8: 64}[c]] for _, _, _, c in cases]
+
+
+def test_tuned_schedule_is_for_eager_solves(ask):
+    """A schedule that the autotuner chose, or that a later plan inherits, serves eager solves by
+    themselves; a graph and a server's solve beside others keep the plan's rule, as without tuning.
+    One pinned by hand serves all."""
+    for lattice in (0, 1):
+        beside = 1 if lattice else 2  # (the lattice scheme keeps its own default, 1 here)
+        for overlap in (0, 1, 2, 3):
+            tuned = overlap or 1
+            # by itself, beside others, as a graph
+            assert ask(*["solve %d 1 %d %d %d 1 3" % (overlap, lattice, b, g) for b, g in ((0, 0), (0, 1))]) == [
+                [tuned], [3]]
+            pinned = overlap or None
+            assert ask(*["solve %d 0 %d %d %d 1 3" % (overlap, lattice, b, g) for b, g in ((0, 0), (1, 0), (0, 1))]) \
+                == [[pinned or 1], [pinned or beside], [pinned or 3]]
+        assert ask("solve 3 1 %d 1 0 1 3" % lattice) == [[3 if lattice else 2]]
