@@ -333,7 +333,8 @@ hipError_t run_solve(lgf_plan_s* pl, const T* f, T* u, hipStream_t s) {
         LevelPlan& L = pl->lv[l];
         const bool lists = L.pairs() > 0;
         const double nup = l == 1 ? ns : lvN(l);
-        const double rbytes = l == 1 ? ns * (n3 + p3) * es : (lvN(l - 1) + lvN(l)) * p3 * es;
+        // (the top level keeps no node values: only its spectra are written)
+        const double rbytes = (l == 1 ? ns * n3 : lvN(l - 1) * p3) * es + (L.d_ftil ? nup * p3 * es : 0.0);
         const double rflops = l == 1 ? ns * 2.0 * (p * n3 + p * p * n * n + p3 * n) : lvN(l - 1) * 6.0 * p3 * p;
         const std::string rname = "reg_l" + std::to_string(l - 1) + "_l" + std::to_string(l);
         if (!pl->lat1) {
