@@ -1,6 +1,11 @@
 // The plan's rules that need no device (lgf_host.h), for tests/test_host_rules.py.  Reads one
 // query per line from stdin and prints one answer per line:
 //   fields items chunks bytes        near_fields_fit
+//   items targets                    field_items
+//   runs n copies height...          of a batch of `copies` layouts, each a row of 2x2-block towers of
+//                                    these heights: the level-0 runs of the first layout (their groups),
+//                                    then 0, all runs, and the 4-wave workgroups that march in lockstep
+//                                    (4 equal runs of 8 and more), the others
 //   solve overlap eager_only lattice beside graph plan_eager plan_graph
 //                                    solve_schedule
 //   m2l parents S F n                m2l_default: children per lane, parents per workgroup
@@ -27,6 +32,30 @@ int main() {
             int chunks = 0, bytes = 0;
             in >> items >> chunks >> bytes;
             std::cout << near_fields_fit(items, chunks, bytes) << "\n";
+        } else if (kind == "items") {
+            long long n = 0;
+            in >> n;
+            std::cout << field_items(n) << "\n";
+        } else if (kind == "runs") {
+            int n = 0, copies = 0, h = 0;
+            in >> n >> copies;
+            std::vector<int32_t> b;
+            for (int x = 0; in >> h; x += 2)
+                for (int z = 0; z < h; ++z) b.insert(b.end(), {x, 0, z, x + 1, 0, z, x, 1, z, x + 1, 1, z});
+            std::vector<HostPlan> parts(copies);
+            for (HostPlan& P : parts)
+                if (build_host(b.data(), (int64_t)b.size() / 3, n, 4, 0, P) != LGF_OK) return 3;
+            const HostPlan H = concat(parts);
+            if (check_host(H) != LGF_OK) return 3;
+            const std::vector<int32_t>& r = H.g0_runs;
+            for (size_t k = 0; k < r.size() && H.g0_coord[4 * r[k] + 3] == 0; k += 2) std::cout << r[k + 1] << " ";
+            int lock = 0, other = 0;
+            for (size_t k = 0; k < r.size(); k += 8) {
+                bool same = k + 8 <= r.size() && r[k + 1] >= 8;
+                for (size_t j = k; same && j < k + 8; j += 2) same = r[j + 1] == r[k + 1];
+                ++(same ? lock : other);
+            }
+            std::cout << "0 " << r.size() / 2 << " " << lock << " " << other << "\n";
         } else if (kind == "solve") {
             int v[7] = {};
             for (int& x : v) in >> x;

@@ -98,3 +98,20 @@ def test_tuned_schedule_is_for_eager_solves(ask):
             assert ask(*["solve %d 0 %d %d %d 1 3" % (overlap, lattice, b, g) for b, g in ((0, 0), (1, 0), (0, 1))]) \
                 == [[pinned or 1], [pinned or beside], [pinned or 3]]
         assert ask("solve 3 1 %d 1 0 1 3" % lattice) == [[3 if lattice else 2]]
+
+
+def test_field_items(ask):
+    """The level-0 field spectra's stride: one item more at multiples of 1024 targets only."""
+    assert ask("items 1023", "items 1024", "items 1025", "items 512", "items 4096") == [
+        [1023], [1025], [1025], [512], [4097]]
+
+
+def test_runs_of_towers(ask):
+    """Towers of 16, 16, 16, 16, 10 and 5 blocks: 8, 8, 8, 8, 5 and 3 groups of 2^3.  Alone they are
+    few groups and every run is one; 25 and 171 copies of them make runs of whole towers, and
+    workgroups of four that march in lockstep (8 8 8 8) between such that do not (5 3 8 8), the last
+    one not full (tests/test_gpu_near.py solves these)."""
+    alone, many, small = ask("runs 8 1 16 16 16 16 10 5", "runs 8 25 16 16 16 16 10 5", "runs 4 171 16 16 16 16 10 5")
+    assert alone == [1] * 40 + [0, 40, 0, 10]
+    assert many == [8, 8, 8, 8, 5, 3, 0, 150, 13, 25]
+    assert small == [8, 8, 8, 8, 5, 3, 0, 1026, 86, 171]
