@@ -84,8 +84,10 @@ def _time_graph(plan, f, u, steps, warmup):
     return t1 - t0, lat
 
 
-_SRC = {"prod": ["lgf_prod.hip", "lgf_device.h", "lgf_internal.h"],
-        "fft": ["lgf_fft.hip", "lgf_tile.h", "lgf_device.h", "lgf_internal.h"],
+# What a step's HBM traffic depends on: its kernels, and the host's order of groups and parents,
+# run lengths, variants (lgf_host.cpp) and strides (lgf_host.h).
+_SRC = {"prod": ["lgf_prod.hip", "lgf_device.h", "lgf_internal.h", "lgf_host.cpp", "lgf_host.h"],
+        "fft": ["lgf_fft.hip", "lgf_tile.h", "lgf_device.h", "lgf_internal.h", "lgf_host.h"],
         "interp": ["lgf_interp.hip", "lgf_tile.h", "lgf_device.h", "lgf_internal.h"]}
 
 
