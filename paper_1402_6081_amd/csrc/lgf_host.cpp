@@ -284,15 +284,16 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
 }
 
 // Longest run of the level-0 Prod, 8, 4, 2 or 1 groups: a wave marching through R stacked groups
-// reads 2R + 2 source slabs for 2R target slabs, but leaves R times fewer waves, and below
-// about 4096 (four per SIMD) the lost waves cost more than the reads save.  Measured on
+// reads 2R + 2 source slabs for 2R target slabs, but leaves R times fewer waves.  The line is 4096
+// runs x frequency chunks in both precisions: four waves per SIMD in FP64, two in FP32, whose waves
+// take two chunks each.  Measured on
 // MI355X, us in FP64 / FP32: 16^3 blocks of 16^3, R = 1, 2, 4, 8: 782, 631, 559, 524 / 413, 337,
 // 301, 294; 8^3 blocks of 16^3, R = 1, 2, 4: 100, 86, 75 / 50, 46, 46; 4224 blocks of 6^3,
 // R = 1, 2, 4 (FP32): 35, 30, 39; 552 blocks of 8^3, R = 1, 2 (FP64): 25, 26.
 static int run_length(const HostPlan& H) {
-    const int64_t waves = H.ngroups0 * (spec_padded(2 * H.n * 2 * H.n * (H.n + 1)) / kSpecChunk);
+    const int64_t units = H.ngroups0 * (spec_padded(2 * H.n * 2 * H.n * (H.n + 1)) / kSpecChunk);
     int R = 8;
-    while (R > 1 && waves / R < 4096) R /= 2;
+    while (R > 1 && units / R < 4096) R /= 2;
     return R;
 }
 

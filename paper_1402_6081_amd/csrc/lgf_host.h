@@ -31,11 +31,12 @@ constexpr int kSpecChunk = 64;
 constexpr int spec_padded(int S) { return (S + kSpecChunk - 1) / kSpecChunk * kSpecChunk; }
 
 // Items per chunk of the level-0 field spectra of n targets.  The inverse transform reads one item
-// from every chunk at once; with a multiple of 1024 items the chunks lie a multiple of 1 MB (FP32:
-// 512 KB) apart and those reads meet in the same DRAM banks, so one item is added (256^3 in 16^3
-// blocks, 4096 -> 4097 items: FP64 288 -> 267 us, FP32 144 -> 136; up to 256 items more make no
-// further difference, and 512 -> 513 items at 128^3 none at all).  The source spectra have a
-// sentinel item beside theirs.
+// from every chunk at once; with a multiple of 1024 items, whatever their bytes, those reads meet in
+// the same memory banks, so one item is added (256^3 in 16^3 blocks, 4096 -> 4097 items: FP64 288 ->
+// 267 us, FP32 144 -> 136; up to 256 items more make no further difference).  Other multiples of
+// 512 do not need it, in neither precision nor in or beyond the last-level cache: 512 -> 513 items
+// 45.5 -> 45.1 us in FP64, 23.4 -> 23.3 in FP32, 2560 -> 2561 178.3 -> 181.1 and 95.8 -> 96.0.  The
+// source spectra have a sentinel item beside theirs.
 constexpr int64_t field_items(int64_t n) { return n % 1024 == 0 ? n + 1 : n; }
 
 // Do the 32-bit offsets of a level-0 Prod wave that covers `chunks` consecutive chunks reach its

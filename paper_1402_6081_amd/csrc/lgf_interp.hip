@@ -16,7 +16,8 @@
 // matrix entry from LDS for each multiply-add, made the passes LDS-bound).  On a 256^3 cube of
 // 16^3 blocks, p = 8, from one output per thread to this, FP64 and FP32: Reg to level 1 with its
 // transform 85 to 55 us (its 0.30 GB take 53 at a copy's rate) and 45 to 31, Reg up 25 to 17 and
-// 14 to 11, the final pass with its transform and Interp 106 to 77 (0.42 GB: 74) and 85 to 66;
+// 14 to 11, the final pass with its transform and Interp 106 to 77 (0.42 GB: 74) and 85 to 66 (46
+// since its reads go out ahead, node_values);
 // at p = 17, FP64, 128^3: Reg up 63 to 36, Interp down 50 to 31, the final pass 30 to 22.
 #include <type_traits>
 

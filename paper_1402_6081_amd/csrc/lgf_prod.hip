@@ -146,8 +146,11 @@ struct NearArgs {
     SpecSym sym;
 };
 
-// Runs long enough for a workgroup's waves to march in lockstep (measured: 256^3, runs of 8,
-// 540 -> 524 us in FP64 and 303 -> 294 us in FP32; 128^3, runs of 4, 75 -> 79 us).
+// Runs long enough for a workgroup's waves to march in lockstep.  Without and with it, us in FP64 /
+// FP32 on 16^3 blocks: 256^3, runs of 8, 526 -> 498 / 300 -> 289; shorter runs in as large plans,
+// 32 x 16 x 8 blocks (runs of 4) 515 -> 505 / 293 -> 284, 24 x 24 x 6 (of 3) 467 -> 455 / 263 -> 258;
+// but 128^3 (of 4) 69 -> 72 / 42 -> 45, and where runs differ, the separate-set ring 253 -> 257 /
+// 133 -> 137: 8 loses on none.
 constexpr int kLockstepRun = 8;
 
 template <typename T, int kNearWaves, int FPL>
