@@ -47,7 +47,7 @@ long double lagrange(int p, int k, long double t) {
 // reported count only pairs with an evaluation target (the lists of the method).  The level-0
 // groups hold evaluation blocks (numbered as given) and their sources (numbered as given).
 lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int levels, HostPlan& H,
-                      const int32_t* eval_ijk, int64_t neval) {
+                      const int32_t* eval_ijk, int64_t neval, bool part) {
     const bool split = eval_ijk != nullptr;
     if (!split) {
         eval_ijk = ijk;
@@ -168,6 +168,7 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
         // reads the level-0 source spectra (nsrc items and the sentinel)
         const int32_t sentinel = (int32_t)(l == 2 && H.lat1 ? H.nsrc : Ch.nint);
         Lv.src216.assign(216 * Lv.nint, sentinel);
+        Lv.nbr.assign(Lv.nint, 0);
         int64_t pairs = 0;
         for (int64_t i = 0; i < Lv.nint; ++i) {
             for (int e = 0; e < 27; ++e) {
@@ -178,7 +179,9 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
                 if (it == idx[l].end()) continue;
                 for (int cs = 0; cs < 8; ++cs) {
                     const int32_t q = Lv.child8[8 * it->second + cs];
-                    if (q >= 0 && H.has_src[l - 1][q]) Lv.src216[216 * i + 8 * e + cs] = q;
+                    if (q < 0 || !H.has_src[l - 1][q]) continue;
+                    Lv.src216[216 * i + 8 * e + cs] = q;
+                    if (e != 13) Lv.nbr[i] |= 1u << e;
                 }
             }
             for (int c = 0; c < 8; ++c) {
@@ -278,6 +281,7 @@ lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int lev
         }
         H.g0_tgt8[8 * g + ((P[0] & 1) | ((P[1] & 1) << 1) | ((P[2] & 1) << 2))] = act[b];
     }
+    if (part) return LGF_OK;
     order_groups(H);
     order_parents(H);
     return LGF_OK;
@@ -300,20 +304,23 @@ static int run_length(const HostPlan& H) {
 void order_groups(HostPlan& H) {
     const int64_t ng = H.ngroups0;
     const int R = run_length(H);
-    std::vector<int32_t> ord(ng);
-    for (int64_t g = 0; g < ng; ++g) ord[g] = (int32_t)g;
     const int32_t* C = H.g0_coord.data();
-    // by layout, layer of R groups, then column (y, x), then z
-    std::sort(ord.begin(), ord.end(), [&](int32_t i, int32_t j) {
-        const int32_t *a = C + 4 * i, *b = C + 4 * j;
-        const std::array<int32_t, 5> ka{a[3], a[2] / R, a[1], a[0], a[2]}, kb{b[3], b[2] / R, b[1], b[0], b[2]};
-        return ka < kb;
-    });
+    // by layout, layer of R groups, then column (y, x), then z: the groups of a layout stand together,
+    // and a coordinate is below 2^19, so each is sorted by a key of 60 bits
+    std::vector<std::pair<uint64_t, int32_t>> ord(ng);
+    for (int64_t g = 0; g < ng; ++g) {
+        const uint64_t x = C[4 * g], y = C[4 * g + 1], z = C[4 * g + 2];
+        ord[g] = {(((z / R) << 19 | y) << 19 | x) << 3 | z % R, (int32_t)g};
+    }
+    for (int64_t a = 0, b = 0; a < ng; a = b) {
+        while (b < ng && C[4 * b + 3] == C[4 * a + 3]) ++b;
+        std::sort(ord.begin() + a, ord.begin() + b);
+    }
     std::vector<int32_t> tgt(8 * ng), src(64 * ng), coord(4 * ng);
     H.g0_runs.clear();
     H.g0_flags.assign(ng, 0);
     for (int64_t g = 0; g < ng; ++g) {
-        const int32_t o = ord[g];
+        const int32_t o = ord[g].second;
         std::copy_n(&H.g0_tgt8[8 * o], 8, &tgt[8 * g]);
         std::copy_n(&H.g0_src64[64 * o], 64, &src[64 * g]);
         std::copy_n(C + 4 * o, 4, &coord[4 * g]);
@@ -341,25 +348,25 @@ void order_parents(HostPlan& H) {
             for (size_t k = 0; k < Lv.child8.size(); ++k)
                 if (Lv.child8[k] >= 0) H.lv[l - 1].par[Lv.child8[k]] = (int32_t)k;
         }
-        const int32_t sentinel = (int32_t)(l == 2 && H.lat1 ? H.nsrc : H.lv[l - 1].nint);
         const int64_t np = Lv.nint;
-        std::vector<uint32_t> mask(np, 0);
-        std::vector<int> cnt(np);
-        Lv.m2l_ord.resize(np);
+        // a stable sort by counting: parents of c neighbours begin behind those of more
+        std::array<int64_t, 28> at{};
         int64_t total = 0;
         int most = 0;
-        for (int64_t i = 0; i < np; ++i) {
-            for (int k = 0; k < 216; ++k)
-                if (Lv.src216[216 * i + k] != sentinel) mask[i] |= 1u << (k >> 3);
-            mask[i] &= ~(1u << 13);
-            cnt[i] = __builtin_popcount(mask[i]);
-            total += cnt[i];
-            most = std::max(most, cnt[i]);
-            Lv.m2l_ord[i] = (int32_t)i;
+        for (uint32_t m : Lv.nbr) {
+            const int c = __builtin_popcount(m);
+            ++at[26 - c + 1];
+            total += c;
+            most = std::max(most, c);
         }
-        std::stable_sort(Lv.m2l_ord.begin(), Lv.m2l_ord.end(), [&](int32_t a, int32_t b) { return cnt[a] > cnt[b]; });
+        for (int k = 1; k < 28; ++k) at[k] += at[k - 1];
+        Lv.m2l_ord.resize(np);
         Lv.m2l_mask.resize(np);
-        for (int64_t i = 0; i < np; ++i) Lv.m2l_mask[i] = mask[Lv.m2l_ord[i]];
+        for (int64_t i = 0; i < np; ++i) {
+            const int64_t k = at[26 - __builtin_popcount(Lv.nbr[i])]++;
+            Lv.m2l_ord[k] = (int32_t)i;
+            Lv.m2l_mask[k] = Lv.nbr[i];
+        }
         // Workgroups of the heaviest parents first where the numbers spread widely (measured, us:
         // separate-set ring FP64 196 -> 176, 552 blocks of 8^3 118 -> 100, 48 ragged layouts 140
         // -> 134); elsewhere all the parents of one frequency chunk together, whose sources then
@@ -396,6 +403,7 @@ lgf_status check_host(const HostPlan& H) {
         const int64_t ns = l == 2 && H.lat1 ? H.nsrc : nc;
         ok = within(Lv.child8, -1, nc - 1) && within(Lv.src216, 0, ns) && within(Lv.m2l_ord, 0, Lv.nint - 1) &&
              (int64_t)Lv.m2l_ord.size() == Lv.nint && (int64_t)Lv.m2l_mask.size() == Lv.nint &&
+             (int64_t)Lv.nbr.size() == Lv.nint &&
              (Lv.src216.empty() || (int64_t)Lv.src216.size() == 216 * Lv.nint);
     }
     for (int l = 1; ok && l < H.Ltop; ++l)  // parents (8 J + c) and the par list of every level below the top
@@ -451,6 +459,7 @@ HostPlan concat(const std::vector<HostPlan>& parts) {
                 const int32_t sent_in = (int32_t)P.lv[l - 1].nint, sent_out = (int32_t)U.lv[l - 1].nint;
                 for (int32_t c : A.child8) B.child8.push_back(c < 0 ? -1 : (int32_t)(c + oc));
                 for (int32_t q : A.src216) B.src216.push_back(q == sent_in ? sent_out : (int32_t)(q + oc));
+                B.nbr.insert(B.nbr.end(), A.nbr.begin(), A.nbr.end());
             }
             const int64_t ol = off[l];
             for (int32_t t : A.csr_tgt) B.csr_tgt.push_back((int32_t)(t + ol));

@@ -84,9 +84,10 @@ struct HostLevel {
     std::vector<int32_t> coords;  // [nint][3] (single layouts only; empty in unions)
     std::vector<int32_t> child8;  // [nint][8] children at level l-1 (levels >= 2)
     std::vector<int32_t> src216;  // [nint][216] children of the 27 neighbours, sentinel = N_{l-1}
+    std::vector<uint32_t> nbr;    // [nint] neighbours holding a source, bit e of 27, itself left out
     // the M2L of the level below over these parents: the parents by decreasing number of
-    // neighbours that hold a source, and in that order their children, lists and neighbours (bit
-    // e of 27, the parent itself left out); spread: the average is below two thirds of the most
+    // neighbours that hold a source, and in that order their children, lists and neighbours;
+    // spread: the average is below two thirds of the most
     std::vector<int32_t> m2l_ord;
     std::vector<uint32_t> m2l_mask;
     bool m2l_spread = false;
@@ -130,8 +131,9 @@ struct HostPlan {
 // with no evaluation block below it is never interpolated to a block, and the list sizes
 // reported count only pairs with an evaluation target (the lists of the method).  The level-0
 // groups hold evaluation blocks (numbered as given) and their sources (numbered as given).
+// part: the layout goes into a union, whose groups and parents concat puts in order.
 lgf_status build_host(const int32_t* ijk, int64_t nblocks, int n, int p, int levels, HostPlan& H,
-                      const int32_t* eval_ijk = nullptr, int64_t neval = 0);
+                      const int32_t* eval_ijk = nullptr, int64_t neval = 0, bool part = false);
 
 // Level-0 groups renumbered so that the groups of a run are consecutive, runs of neighbouring
 // columns following each other; fills g0_runs and g0_flags.

@@ -185,11 +185,53 @@ bool dev_alloc(lgf_plan_s* pl, P** out, int64_t bytes) {
     return true;
 }
 
-template <typename V>
-hipError_t upload(void* dst, const std::vector<V>& v, hipStream_t s) {
-    if (v.empty() || !dst) return hipSuccess;
-    return hipMemcpyAsync(dst, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice, s);
-}
+// A plan's lists and matrices on the device: those of up to 64 KB share one allocation and one
+// copy, as each of their own costs 5 to 10 us (40 blocks of 16^3 have 22 of them), larger ones have
+// their own.  The lists are read until the stream is synchronised.
+struct ListUpload {
+    struct Part {
+        void** dst;
+        const void* data;
+        size_t bytes, at;
+    };
+    static constexpr size_t kShared = 64 << 10, kAlign = 256;
+    std::vector<Part> parts;
+    std::vector<char> staged;
+    size_t total = 0;
+
+    template <typename P, typename V>
+    void add(P** dst, const std::vector<V>& v) {
+        const size_t bytes = v.size() * sizeof(V);
+        *dst = nullptr;
+        if (bytes == 0) return;
+        parts.push_back(Part{reinterpret_cast<void**>(dst), v.data(), bytes, total});
+        if (bytes <= kShared) total += (bytes + kAlign - 1) / kAlign * kAlign;
+    }
+    bool allocate(lgf_plan_s* pl) {
+        char* shared = nullptr;
+        bool ok = dev_alloc(pl, &shared, (int64_t)total);
+        staged.resize(total);
+        for (Part& p : parts) {
+            if (p.bytes > kShared) {
+                ok = ok && dev_alloc(pl, p.dst, (int64_t)p.bytes);
+            } else if (ok) {
+                *p.dst = shared + p.at;
+                std::memcpy(staged.data() + p.at, p.data, p.bytes);
+            }
+        }
+        return ok;
+    }
+    hipError_t copy(hipStream_t s) const {
+        hipError_t e = hipSuccess;
+        for (const Part& p : parts)
+            if (p.bytes > kShared && e == hipSuccess)
+                e = hipMemcpyAsync(*p.dst, p.data, p.bytes, hipMemcpyHostToDevice, s);
+        for (const Part& p : parts)
+            if (p.bytes <= kShared && e == hipSuccess)
+                return hipMemcpyAsync((char*)*p.dst - p.at, staged.data(), total, hipMemcpyHostToDevice, s);
+        return e;
+    }
+};
 
 // The rows of a parent list in the M2L's order of parents.
 std::vector<int32_t> m2l_sorted(const HostLevel& P, const std::vector<int32_t>& list, size_t per) {
@@ -602,76 +644,63 @@ lgf_status setup_device(HostPlan& H, lgf_precision prec, double kappa, hipStream
     const int64_t need = workspace_need(H, prec);
     if (!budget_reserve(need)) return fail(LGF_ERR_BUDGET, "plan workspace exceeds the device-memory budget");
     pl->ws_bytes = need;
-    bool ok = dev_alloc(pl, &pl->d_g0_tgt8, H.ngroups0 * 8 * 4) &&
-              dev_alloc(pl, &pl->d_g0_src64, H.ngroups0 * 64 * 4) &&
-              dev_alloc(pl, &pl->d_g0_runs, (int64_t)H.g0_runs.size() * 4) &&
-              dev_alloc(pl, &pl->d_g0_flags, H.ngroups0 * 4) && dev_alloc(pl, &pl->d_A, p * n * 8) &&
-              dev_alloc(pl, &pl->d_C01, 2 * p * p * 8) && dev_alloc(pl, &pl->d_At, p * n * 8) &&
-              dev_alloc(pl, &pl->d_Ct, 2 * p * p * 8) &&
-              dev_alloc(pl, &pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz) &&
-              dev_alloc(pl, &pl->d_uhat0, field_items(H.ntgt0) * S0 * 2 * esz) &&
-              dev_alloc(pl, &pl->d_eval_l1, (int64_t)H.eval_l1.size() * 4) &&
-              dev_alloc(pl, &pl->d_near_out, (int64_t)H.near_out.size() * 4) &&
-              dev_alloc(pl, &pl->d_near_flag, (int64_t)H.near_flag.size() * 4);
+    ListUpload lists;
+    lists.add(&pl->d_g0_tgt8, H.g0_tgt8);
+    lists.add(&pl->d_g0_src64, H.g0_src64);
+    lists.add(&pl->d_g0_runs, H.g0_runs);
+    lists.add(&pl->d_g0_flags, H.g0_flags);
+    const std::vector<float> A32(A.begin(), A.end()), C32(C01.begin(), C01.end());
+    if (prec == LGF_F64) {
+        lists.add(&pl->d_A, A);
+        lists.add(&pl->d_C01, C01);
+    } else {
+        lists.add(&pl->d_A, A32);
+        lists.add(&pl->d_C01, C32);
+    }
+    lists.add(&pl->d_At, At);
+    lists.add(&pl->d_Ct, Ct);
+    lists.add(&pl->d_eval_l1, H.eval_l1);
+    lists.add(&pl->d_near_out, H.near_out);
+    lists.add(&pl->d_near_flag, H.near_flag);
+    for (int l = 1; l <= pl->Ltop; ++l) {
+        LevelPlan& Lv = pl->lv[l];
+        const HostLevel& h = H.lv[l];
+        lists.add(&Lv.d_par, h.par);
+        if (h.csr_src.empty()) continue;
+        lists.add(&Lv.d_csr_tgt, h.csr_tgt);
+        lists.add(&Lv.d_csr_ptr, h.csr_ptr);
+        lists.add(&Lv.d_csr_src, h.csr_src);
+        lists.add(&Lv.d_csr_off, csr_off[l]);
+    }
+    std::vector<std::vector<int32_t>> src_sorted(H.L + 1), child_sorted(H.L + 1);
+    for (int l = 2; l <= topc && pl->Ltop >= 1; ++l) {
+        LevelPlan& Lv = pl->lv[l];
+        const HostLevel& h = H.lv[l];
+        Lv.m2l_spread = h.m2l_spread;
+        src_sorted[l] = m2l_sorted(h, h.src216, 216);
+        child_sorted[l] = m2l_sorted(h, h.child8, 8);
+        lists.add(&Lv.d_child8, h.child8);
+        lists.add(&Lv.d_m2l_src216, src_sorted[l]);
+        lists.add(&Lv.d_m2l_child8, child_sorted[l]);
+        lists.add(&Lv.d_m2l_mask, h.m2l_mask);
+    }
+    bool ok = lists.allocate(pl) && dev_alloc(pl, &pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz) &&
+              dev_alloc(pl, &pl->d_uhat0, field_items(H.ntgt0) * S0 * 2 * esz);
     for (int l = 1; ok && l <= pl->Ltop; ++l) {
         LevelPlan& Lv = pl->lv[l];
         const HostLevel& h = H.lv[l];
         ok = (!needs_ftil(H, l) || dev_alloc(pl, &Lv.d_ftil, Lv.nint * p3 * esz)) &&
-             (!needs_util(H, l) || dev_alloc(pl, &Lv.d_util, Lv.nint * p3 * usz)) &&
-             dev_alloc(pl, &Lv.d_par, (int64_t)h.par.size() * 4);
+             (!needs_util(H, l) || dev_alloc(pl, &Lv.d_util, Lv.nint * p3 * usz));
         if (ok && h.pairs() > 0 && l == 1 && H.lat1)
             ok = dev_alloc(pl, &Lv.d_uhat, Lv.nint * S0 * 2 * esz);  // sources: the level-0 spectra
         else if (ok && h.pairs() > 0)
             ok = dev_alloc(pl, &Lv.d_fhat, (Lv.nint + 1) * S1 * 2 * esz) &&
                  dev_alloc(pl, &Lv.d_uhat, Lv.nint * S1 * 2 * esz);
-        if (ok && !h.csr_src.empty())
-            ok = dev_alloc(pl, &Lv.d_csr_tgt, h.csr_tgt.size() * 4) &&
-                 dev_alloc(pl, &Lv.d_csr_ptr, h.csr_ptr.size() * 4) &&
-                 dev_alloc(pl, &Lv.d_csr_src, h.csr_src.size() * 4) &&
-                 dev_alloc(pl, &Lv.d_csr_off, h.csr_src.size() * 4);
     }
-    for (int l = 2; ok && l <= topc && pl->Ltop >= 1; ++l)
-        ok = dev_alloc(pl, &pl->lv[l].d_child8, H.lv[l].nint * 32) &&
-             dev_alloc(pl, &pl->lv[l].d_m2l_src216, H.lv[l].nint * 216 * 4) &&
-             dev_alloc(pl, &pl->lv[l].d_m2l_child8, H.lv[l].nint * 32) &&
-             dev_alloc(pl, &pl->lv[l].d_m2l_mask, H.lv[l].nint * 4);
     if (ok) ok = dev_alloc(pl, &pl->d_scratch, scratch_need(H));
     if (ok) ok = dev_alloc(pl, &pl->d_flag, 4);
     if (!ok) return fail(LGF_ERR_OOM, "device allocation failed for the plan workspace");
-    // (the uploads read these until the synchronisation below)
-    std::vector<std::vector<int32_t>> src_sorted(H.L + 1), child_sorted(H.L + 1);
-    hipError_t e = upload(pl->d_g0_tgt8, H.g0_tgt8, s);
-    if (e == hipSuccess) e = upload(pl->d_g0_src64, H.g0_src64, s);
-    if (e == hipSuccess) e = upload(pl->d_g0_runs, H.g0_runs, s);
-    if (e == hipSuccess) e = upload(pl->d_g0_flags, H.g0_flags, s);
-    const std::vector<float> A32(A.begin(), A.end()), C32(C01.begin(), C01.end());
-    if (e == hipSuccess) e = prec == LGF_F64 ? upload(pl->d_A, A, s) : upload(pl->d_A, A32, s);
-    if (e == hipSuccess) e = prec == LGF_F64 ? upload(pl->d_C01, C01, s) : upload(pl->d_C01, C32, s);
-    if (e == hipSuccess) e = upload(pl->d_At, At, s);
-    if (e == hipSuccess) e = upload(pl->d_Ct, Ct, s);
-    if (e == hipSuccess) e = upload(pl->d_eval_l1, H.eval_l1, s);
-    if (e == hipSuccess) e = upload(pl->d_near_out, H.near_out, s);
-    if (e == hipSuccess) e = upload(pl->d_near_flag, H.near_flag, s);
-    for (int l = 1; e == hipSuccess && l <= pl->Ltop; ++l) {
-        LevelPlan& Lv = pl->lv[l];
-        e = upload(Lv.d_par, H.lv[l].par, s);
-        if (e == hipSuccess && Lv.d_csr_tgt) {
-            e = upload(Lv.d_csr_tgt, H.lv[l].csr_tgt, s);
-            if (e == hipSuccess) e = upload(Lv.d_csr_ptr, H.lv[l].csr_ptr, s);
-            if (e == hipSuccess) e = upload(Lv.d_csr_src, H.lv[l].csr_src, s);
-            if (e == hipSuccess) e = upload(Lv.d_csr_off, csr_off[l], s);
-        }
-    }
-    for (int l = 2; e == hipSuccess && l <= topc && pl->Ltop >= 1; ++l) {
-        LevelPlan& Lv = pl->lv[l];
-        e = upload(Lv.d_child8, H.lv[l].child8, s);
-        Lv.m2l_spread = H.lv[l].m2l_spread;
-        src_sorted[l] = m2l_sorted(H.lv[l], H.lv[l].src216, 216);
-        child_sorted[l] = m2l_sorted(H.lv[l], H.lv[l].child8, 8);
-        if (e == hipSuccess) e = upload(Lv.d_m2l_src216, src_sorted[l], s);
-        if (e == hipSuccess) e = upload(Lv.d_m2l_child8, child_sorted[l], s);
-        if (e == hipSuccess) e = upload(Lv.d_m2l_mask, H.lv[l].m2l_mask, s);
-    }
+    hipError_t e = lists.copy(s);
     // the source-spectra arrays start zeroed: their last item is the zero sentinel
     if (e == hipSuccess) e = zero_fill(pl->d_fhat0, (H.nsrc + 1) * S0 * 2 * esz, s);
     // level-1 fields of the union intervals that are not sources stay zero (Reg writes the
@@ -1011,7 +1040,7 @@ lgf_status lgf_plan_create_batch(const int32_t* const* layouts, const int64_t* n
             if (nblocks[i] < 1) return fail(LGF_ERR_LAYOUT, "empty layout in batch");
             total += nblocks[i];
             if (total > (int64_t)1 << 30) return fail(LGF_ERR_ARG, "too many blocks");
-            st = build_host(layouts[i], nblocks[i], n, p, levels, parts[i]);
+            st = build_host(layouts[i], nblocks[i], n, p, levels, parts[i], nullptr, 0, true);
             if (st != LGF_OK) return st;
         }
         HostPlan U = concat(parts);

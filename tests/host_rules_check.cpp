@@ -47,6 +47,17 @@ int main() {
                 if (build_host(b.data(), (int64_t)b.size() / 3, n, 4, 0, P) != LGF_OK) return 3;
             const HostPlan H = concat(parts);
             if (check_host(H) != LGF_OK) return 3;
+            // parts left in the order of their blocks give the same union
+            for (HostPlan& P : parts)
+                if (build_host(b.data(), (int64_t)b.size() / 3, n, 4, 0, P = HostPlan(), nullptr, 0, true) != LGF_OK)
+                    return 3;
+            const HostPlan U = concat(parts);
+            bool same_lists = U.g0_runs == H.g0_runs && U.g0_src64 == H.g0_src64 && U.g0_tgt8 == H.g0_tgt8 &&
+                              U.g0_flags == H.g0_flags;
+            for (int l = 1; l <= H.L; ++l)
+                same_lists = same_lists && U.lv[l].m2l_ord == H.lv[l].m2l_ord && U.lv[l].m2l_mask == H.lv[l].m2l_mask &&
+                             U.lv[l].src216 == H.lv[l].src216 && U.lv[l].par == H.lv[l].par;
+            if (!same_lists) return 4;
             const std::vector<int32_t>& r = H.g0_runs;
             for (size_t k = 0; k < r.size() && H.g0_coord[4 * r[k] + 3] == 0; k += 2) std::cout << r[k + 1] << " ";
             int lock = 0, other = 0;
