@@ -126,8 +126,8 @@ __device__ __forceinline__ void arrived(V (&x)[N]) {
 // the run is read once instead of once per group: 2R + 2 slabs for the 2R target slabs of R
 // groups (4.5 reads per target at R = 8, 8 at R = 1).  Bound by those reads from L2, and now near
 // the HBM rate: the 256^3 Prod went 612 -> 507 us in FP64 (3.7 -> 4.5 TB/s of its 2.3 GB, 78% of
-// the 5.8 TB/s of a large elementwise copy) and 330 -> 286 us (4.0 TB/s) in FP32 with runs of 8, the 128^3 one 82 -> 71 us and 50 ->
-// 45 us with runs of 4.
+// the 5.8 TB/s of a large elementwise copy) and 330 -> 286 us (4.0 TB/s) in FP32 with runs of 8,
+// the 128^3 one 82 -> 71 us and 50 -> 45 us with runs of 4.
 template <typename T, int FPL>
 struct alignas(FPL * sizeof(cplx<T>)) LaneCoef {
     cplx<T> v[FPL];
