@@ -105,6 +105,9 @@ typedef struct {
  *               generation, FP64 final add of far and near fields)
  *   hip_stream: stream for the set-up work (hipStream_t or NULL)
  *   out       : receives the plan on success
+ * The products reach a frequency chunk's source spectra by 32-bit offsets, so a solve takes at
+ * most 4194302 source blocks and, in FP64, as many level-1 intervals (the union of the source and
+ * evaluation blocks), in FP32 8388606; above, it returns LGF_ERR_DEVICE.
  * Errors: LGF_ERR_ARG, LGF_ERR_LAYOUT, LGF_ERR_OOM, LGF_ERR_BUDGET, LGF_ERR_DEVICE.
  */
 lgf_status lgf_plan_create(const int32_t* block_ijk, int64_t nblocks, int32_t n, int32_t p,
